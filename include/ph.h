@@ -104,7 +104,8 @@ typedef struct {
     double rescue_threshold;
     int use_graph;         /* 1: capture the launch sequence of ph_forward_batch (three
                               stage graphs) and of ph_backward_batch once per set of
-                              buffers and replay it */
+                              buffers and replay it (small plans, whose forward is one
+                              or two kernels, launch those directly) */
     int plain;             /* 1: one FP32 kernel sized for the longest read, pairs
                               in output order, no binning, no rescue (baseline) */
     int force_p;           /* 0 = tuned; else lanes per pair (4, 8, 16, 32 or 64) for every
@@ -228,7 +229,8 @@ ph_status ph_validate(ph_plan *plan, const ph_problem *problem, void *stream);
 /* Kernel-level timing of the most recent ph_forward_batch / ph_backward_batch
  * on this plan, from HIP events recorded on the call's stream around each
  * stage.  ms[0] = binning, ms[1] = FP32 sweep, ms[2] = FP64 rescue,
- * ms[3] = adjoint sweep.  Synchronises the stream. */
+ * ms[3] = adjoint sweep.  A small plan's forward is one stage, reported as
+ * ms[1].  Synchronises the stream. */
 ph_status ph_plan_stage_ms(ph_plan *plan, float ms[4]);
 
 /* Number of pairs sent to an FP64 sweep by the most recent forward call,

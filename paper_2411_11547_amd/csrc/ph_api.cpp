@@ -218,6 +218,11 @@ struct ph_plan {
     bool chain_tiles = false;
     Book *d_book_img = nullptr;
     uint8_t *d_chain_codes = nullptr;
+    // small plans: one launch, one pair per wave (k_one)
+    bool one = false;
+    bool one_reads[2] = {};            // some read of up to 255 bases, some longer one
+    OneRec *d_one = nullptr;
+    uint8_t *d_one_rescued = nullptr;  // per output of the last call: 1 if the pair went to FP64
 
     int64_t *d_out_offset = nullptr;
     int16_t *d_m2bin = nullptr;
@@ -297,7 +302,7 @@ void free_plan(ph_plan *p)
     if (p->adj_exec) (void)hipGraphExecDestroy(p->adj_exec);
     if (p->adj_graph) (void)hipGraphDestroy(p->adj_graph);
     void *bufs[] = {p->d_out_offset, p->d_m2bin, p->d_bin_G, p->d_hist, p->d_recs, p->d_book, p->d_bad, p->d_rescue, p->d_lin,
-                    p->d_book_img, p->d_chain_codes,
+                    p->d_book_img, p->d_chain_codes, p->d_one, p->d_one_rescued,
                     p->d_bnd32, p->d_bnd64, p->d_long_rescue,
                     p->d_adj_recs, p->d_ws, p->d_adj_ctr, p->d_q64, p->d_ws64, p->d_grad_pair, p->d_red};
     for (auto &e : p->ev_adj)
@@ -497,6 +502,18 @@ ph_status build_adjoint(ph_plan *p)
 // of 64,000 reads against 8 haplotypes, gets 2,048.)
 constexpr int64_t kChainMinTiles = 24576;
 
+// Which way a call goes: one launch of one-pair tiles (k_one), or the binned
+// launches.  One-pair tiles fill the GPU at 5.7e12 cells a second (rows padded
+// to 64, 64 columns of fill), the binned sweeps compute 7.3e12 cells, but
+// their launches take 0.1 ms and every bin's kernel ends with its longest tile,
+// a single wave that takes 2 ns per vector instruction, about 5.5 K + 10 of them
+// per step.  Measured (forward, us, binned / one-pair): regions of 50-250 x
+// 100-1,000 bases, 16 bins, 3.1e9 cells 1,020-1,330 / 800, 6.1e9 1,719 / 1,451,
+// 1.04e10 2,252 / 2,384; one bin of 150 x 300 bases, 4.7e8 cells 288 / 164,
+// 1.3e9 396 / 406, 3.6e9 659 / 991.  The estimates are within 10% of these.
+constexpr double kOneCellsPerNs = 5700, kBinnedCellsPerNs = 7300, kOneNs = 20e3, kBinnedNs = 100e3;
+double tile_ns(int64_t cols, int P, int K) { return 2.0 * (double)(cols + P + 2) * (5.5 * K + 10); }
+
 // The FP32 work lists of a binned plan (Section III-C), built once from the
 // shape: records of every bin, bin b's range and tiles in the book image.
 // A bin's records are its chain tiles, longest chain first, then single
@@ -625,6 +642,72 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     for (uint8_t v : seen)
         if (!v) return false;
     return true;
+}
+
+// Time of the one-pair launch of a shape.
+double one_pair_ns(const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho, int32_t nb)
+{
+    double cells = 0;
+    for (int32_t q = 0; q < nb; ++q) {
+        int64_t rows = 0, cols = 0;
+        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) rows += (ro[r + 1] - ro[r] + 64) / 64 * 64;
+        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) cols += ho[h + 1] - ho[h] + 64;
+        cells += (double)rows * (double)cols;
+    }
+    return kOneNs + cells / kOneCellsPerNs;
+}
+
+// Time of a binned plan's launches: the bins run on side streams in turn.
+double binned_ns(const ph_plan *p, const std::vector<PairRec> &recs, const Book &img, const int64_t *ho)
+{
+    double stream[kSideStreams] = {};
+    const int nbins = (int)p->table.size();
+    int next = 0;
+    for (int b = 0; b < nbins; ++b) {
+        const TuneEntry &e = p->table[nbins - 1 - b];
+        int64_t cols = 0;  // of the bin's longest tile: its first chain or its first single pair
+        for (int32_t i = img.bin_rec_begin[b]; i < img.bin_rec_begin[b + 1]; ++i) {
+            const PairRec &r = recs[(size_t)i];
+            const int64_t len = r.n >= 0 ? r.n : ho[r.hap - r.n] - ho[r.hap] + (int64_t)kChainSep * (-r.n - 1);
+            cols = std::max(cols, len);
+            if (r.n >= 0) break;
+        }
+        if (cols) stream[next++ % kSideStreams] += tile_ns(cols, e.P, e.K);
+    }
+    return kBinnedNs + (double)p->cells / kBinnedCellsPerNs + *std::max_element(stream, stream + kSideStreams);
+}
+
+// The pairs of a small plan in the one-pair list, longest sweep first.  The
+// lead of a pair puts the groups of its FP32 row sum where its tile in the
+// work lists has them: that tile flushes the sum after the columns j with
+// j + lane + position = 0 mod its chunk (lane: the one that holds the row past
+// the read's last; position: the haplotype's first column in its chain), the
+// one-pair tile after those with j + lane' + lead = 0.
+std::vector<OneRec> one_list(const ph_plan *p, const std::vector<PairRec> &recs, const Book &img, const int64_t *ro,
+                             const int64_t *ho)
+{
+    std::vector<OneRec> one;
+    one.reserve((size_t)p->P);
+    const int nbins = (int)p->table.size();
+    for (int b = 0; b < nbins; ++b) {
+        const TuneEntry &e = p->table[nbins - 1 - b];
+        const int chunk = ring_chunk(e.P);
+        for (int32_t i = img.bin_rec_begin[b]; i < img.bin_rec_begin[b + 1]; ++i) {
+            const PairRec &r = recs[(size_t)i];
+            const int m = (int)(ro[r.read + 1] - ro[r.read]);
+            const int shift = m / e.K - m / ((m + 64) / 64);
+            int64_t pos = 0;
+            for (int32_t k = 0; k < (r.n < 0 ? -r.n : 1); ++k) {
+                const int32_t n = (int32_t)(ho[r.hap + k + 1] - ho[r.hap + k]);
+                const int lead = (int)(((pos + shift) % chunk + chunk) % chunk);
+                one.push_back(OneRec{r.read, r.hap + k, r.out + k, n, lead, chunk});
+                pos += n + kChainSep;
+            }
+        }
+    }
+    auto work = [&](const OneRec &r) { return (ro[r.read + 1] - ro[r.read] + 64) / 64 * ((int64_t)r.n + 64); };
+    std::stable_sort(one.begin(), one.end(), [&](const OneRec &a, const OneRec &b) { return work(a) > work(b); });
+    return one;
 }
 
 }  // namespace
@@ -770,6 +853,14 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
             if (nchain == 0 || nchain >= kChainMinTiles || cols <= 1024) break;
         }
     }
+    // small plans (reads of up to 1,023 bases, no option that names a launch)
+    std::vector<OneRec> one;
+    if (!opts.plain && !opts.force_p && !opts.single_launch && P > 0 && max_m <= kMaxReadLen &&
+        one_pair_ns(rb, hb, ro, ho, nb) <= binned_ns(p.get(), recs, img, ho)) {
+        p->one = true;
+        one = one_list(p.get(), recs, img, ro, ho);
+        for (const OneRec &r : one) p->one_reads[ro[r.read + 1] - ro[r.read] > 255] = true;
+    }
     // the first HIP calls (everything above is host work)
     HIPCHK(hipGetDevice(&p->device));
     HIPCHK(hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device));
@@ -825,32 +916,38 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
 
     // --- device scratch -------------------------------------------------------
     ph_status st;
-    if ((st = dalloc(&p->d_out_offset, nb + 1))) return st;
-    if ((st = dalloc(&p->d_m2bin, m2bin.size()))) return st;
-    if ((st = dalloc(&p->d_bin_G, kMaxBins))) return st;
-    if ((st = dalloc(&p->d_hist, kMaxKeys))) return st;
-    // binned: the lists' records, then (chain tiles) one FP64 record slot per pair
-    const int64_t nrecs = opts.plain ? P : (int64_t)recs.size() + (p->chain_tiles ? P : 0);
-    if ((st = dalloc(&p->d_recs, std::max<int64_t>(nrecs, 1)))) return st;
     if ((st = dalloc(&p->d_book, 1))) return st;
-    if (!opts.plain) {
+    if (opts.plain) {
+        if ((st = dalloc(&p->d_out_offset, nb + 1))) return st;
+        if ((st = dalloc(&p->d_m2bin, m2bin.size()))) return st;
+        if ((st = dalloc(&p->d_bin_G, kMaxBins))) return st;
+        if ((st = dalloc(&p->d_hist, kMaxKeys))) return st;
+        if ((st = dalloc(&p->d_recs, std::max<int64_t>(P, 1)))) return st;
+        HIPCHK(hipMemcpy(p->d_out_offset, out_off.data(), (nb + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(p->d_m2bin, m2bin.data(), m2bin.size() * sizeof(int16_t), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(p->d_bin_G, binG.data(), nbins * sizeof(int32_t), hipMemcpyHostToDevice));
+    } else if (p->one) {
+        if ((st = dalloc(&p->d_one, one.size()))) return st;
+        if ((st = dalloc(&p->d_one_rescued, (size_t)P))) return st;
+        HIPCHK(hipMemcpy(p->d_one, one.data(), one.size() * sizeof(OneRec), hipMemcpyHostToDevice));
+    } else {
+        // the lists' records, then (chain tiles) one FP64 record slot per pair
+        const int64_t nrecs = (int64_t)recs.size() + (p->chain_tiles ? P : 0);
+        if ((st = dalloc(&p->d_recs, std::max<int64_t>(nrecs, 1)))) return st;
         if ((st = dalloc(&p->d_book_img, 1))) return st;
         HIPCHK(hipMemcpy(p->d_book_img, &img, sizeof(Book), hipMemcpyHostToDevice));
         if (!recs.empty())
             HIPCHK(hipMemcpy(p->d_recs, recs.data(), recs.size() * sizeof(PairRec), hipMemcpyHostToDevice));
         if (p->chain_tiles && (st = dalloc(&p->d_chain_codes, (size_t)(ho[nh] + (int64_t)kChainSep * nh))))
             return st;
+        if ((st = dalloc(&p->d_rescue, (size_t)kRescueQueues * std::max<int64_t>(P, 1)))) return st;
     }
     if ((st = dalloc(&p->d_bad, 1))) return st;
-    if ((st = dalloc(&p->d_rescue, (size_t)kRescueQueues * std::max<int64_t>(P, 1)))) return st;
     if (p->long_pairs) {
         if ((st = dalloc(&p->d_bnd32, (size_t)(p->long_pairs * p->bnd_stride)))) return st;
         if ((st = dalloc(&p->d_bnd64, (size_t)(p->long_pairs * p->bnd_stride)))) return st;
         if ((st = dalloc(&p->d_long_rescue, (size_t)p->long_pairs))) return st;
     }
-    HIPCHK(hipMemcpy(p->d_out_offset, out_off.data(), (nb + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(p->d_m2bin, m2bin.data(), m2bin.size() * sizeof(int16_t), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(p->d_bin_G, binG.data(), nbins * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPCHK(hipMemset(p->d_book, 0, sizeof(Book)));
 
     HIPCHK(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
@@ -1118,6 +1215,25 @@ ph_status run_forward(ph_plan *p, const ph_problem *pb, const float *log10_param
     }
     const int v = viterbi ? 1 : 0;
 
+    if (p->one) {
+        // a small call: launched directly, one or two kernels
+        const double *lin = log10_params ? p->d_lin : nullptr;
+        SweepArgs sa = sweep_args(p, pb, lin, out_log10L, out_status);
+        sa.viterbi = v;
+        OneArgs oa{};
+        oa.recs = p->d_one;
+        oa.rescued = p->d_one_rescued;
+        HIPCHK(hipEventRecord(p->ev[0], s));
+        if (log10_params) HIPCHK(launch_prep_params(log10_params, p->nread_bases, p->d_lin, s));
+        for (int lg = 1; lg >= 0; --lg)
+            if (p->one_reads[lg]) HIPCHK(launch_one(sa, oa, lg != 0, (int)p->P, s));
+        HIPCHK(hipEventRecord(p->ev[3], s));
+        p->last_stream = s;
+        p->stages_recorded = true;
+        p->forward_done = true;
+        return PH_OK;
+    }
+
     // Each stage is captured into its own graph so that HIP events recorded on
     // the caller's stream between the three launches time the stages.
     if (p->opts.use_graph) {
@@ -1265,9 +1381,13 @@ ph_status ph_plan_stage_ms(ph_plan *p, float ms[4])
     for (int i = 0; i < 4; ++i) ms[i] = 0.0f;
     if (p->stages_recorded) {
     HIPCHK(hipEventSynchronize(p->ev[3]));
+    if (p->one) {  // one launch: no binning, and the FP64 sweeps are part of it
+        HIPCHK(hipEventElapsedTime(&ms[1], p->ev[0], p->ev[3]));
+    } else {
     HIPCHK(hipEventElapsedTime(&ms[0], p->ev[0], p->ev[1]));
     HIPCHK(hipEventElapsedTime(&ms[1], p->ev[1], p->ev[2]));
     HIPCHK(hipEventElapsedTime(&ms[2], p->ev[2], p->ev[3]));
+    }
     }
     if (p->adj_recorded) {
         HIPCHK(hipEventSynchronize(p->ev_adj[1]));
@@ -1281,6 +1401,13 @@ ph_status ph_plan_rescued(ph_plan *p, int64_t *count)
     if (!p || !count) return fail(PH_ERR_INVALID, "NULL argument");
     if (!p->forward_done) return fail(PH_ERR_STATE, "no forward call recorded");
     HIPCHK(hipEventSynchronize(p->ev[3]));
+    if (p->one) {
+        std::vector<uint8_t> went((size_t)p->P);
+        HIPCHK(hipMemcpy(went.data(), p->d_one_rescued, went.size(), hipMemcpyDeviceToHost));
+        *count = 0;
+        for (uint8_t w : went) *count += w;
+        return PH_OK;
+    }
     int32_t c[kRescueQueues], lc = 0, passed = 0;
     HIPCHK(hipMemcpy(c, p->d_book->rescue_count, sizeof(c), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&lc, &p->d_book->long_rescue_count, sizeof(lc), hipMemcpyDeviceToHost));
@@ -1435,17 +1562,31 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     const int nbins = g_na_bins;
 
     // pairs per bin and per FP64 class, from the host shape
-    int64_t bin_pairs[kMaxBins] = {}, class_pairs[kRescueClasses] = {};
+    int64_t bin_pairs[kMaxBins] = {}, class_pairs[kRescueClasses] = {}, bin_cols[kMaxBins] = {};
+    bool one_reads[2] = {};  // some read of up to 255 bases, some longer one
+    double cells = 0;
     for (int32_t q = 0; q < nb; ++q) {
         const int64_t H = hb[q + 1] - hb[q];
+        if (H == 0) continue;
+        int64_t nmax = 0;
+        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) nmax = std::max(nmax, ho[h + 1] - ho[h]);
+        const double cols = (double)(ho[hb[q + 1]] - ho[hb[q]]);
         for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
             const int m = (int)(ro[r + 1] - ro[r]);
             int e = 0;
             while (e < nbins - 1 && g_na_table[e].max_m < m) ++e;
-            bin_pairs[nbins - 1 - e] += H;
+            const int b = nbins - 1 - e;
+            bin_pairs[b] += H;
+            bin_cols[b] = std::max(bin_cols[b], nmax);
             class_pairs[rescue_class_of(m)] += H;
+            one_reads[m > 255] = true;
+            cells += m * cols;
         }
     }
+    // the binned launches run one after the other here
+    double binned = kBinnedNs + cells / kBinnedCellsPerNs;
+    for (int b = 0; b < nbins; ++b)
+        if (bin_pairs[b]) binned += tile_ns(bin_cols[b], g_na_table[nbins - 1 - b].P, g_na_table[nbins - 1 - b].K);
 
     unsigned char *base = d->base;
     Book *book = (Book *)(base + kNaBook);
@@ -1463,6 +1604,52 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     for (int e = 0; e < nbins; ++e) {
         tab.max_m[e] = (int16_t)g_na_table[e].max_m;
         tab.P[e] = (int8_t)g_na_table[e].P;
+    }
+    SweepArgs sa{};
+    sa.pb.read_offset = pb->read_offset;
+    sa.pb.read_bases = pb->read_bases;
+    sa.pb.bq = pb->base_qual;
+    sa.pb.iq = pb->ins_qual;
+    sa.pb.dq = pb->del_qual;
+    sa.pb.gq = pb->gcp_qual;
+    sa.pb.hap_offset = pb->hap_offset;
+    sa.pb.hap_bases = pb->hap_bases;
+    sa.lin_params = log10_params ? lin : nullptr;
+    sa.recs = recs;
+    sa.book = book;
+    sa.out_log10 = out_log10L;
+    sa.out_status = out_status;
+    sa.rescue_list = rescue;
+    sa.rescue_stride = P;
+    sa.threshold = 1e-28;
+    sa.floor64 = std::ldexp(1.0, -1000);
+    sa.num_bins = nbins;
+    for (int b = 0; b < nbins; ++b) sa.bins[b] = {g_na_table[nbins - 1 - b].P, g_na_table[nbins - 1 - b].K};
+    sa.plain_count = (int32_t)P;
+    sa.long_bin = -1;
+
+    if (one_pair_ns(rb, hb, ro, ho, nb) <= binned) {
+        // a small call: no binning, one pair per wave; the first pair of every
+        // batch travels in the kernel's arguments, or is summed up on the
+        // device where there are too many batches for that
+        OneArgs oa{};
+        oa.num_batches = nb;
+        oa.batch_read_begin = pb->batch_read_begin;
+        oa.batch_hap_begin = pb->batch_hap_begin;
+        if (log10_params) HIPCHK(launch_prep_params(log10_params, nbases, lin, s));
+        if (nb <= kOneBatches) {
+            int32_t first = 0;
+            for (int32_t q = 0; q < nb; ++q) {
+                oa.first[q] = first;
+                first += (rb[q + 1] - rb[q]) * (hb[q + 1] - hb[q]);
+            }
+        } else {
+            HIPCHK(launch_na_setup(pb->batch_read_begin, pb->batch_hap_begin, nb, out_off, m2bin, binG, tab, s));
+            oa.out_offset = out_off;
+        }
+        for (int lg = 1; lg >= 0; --lg)
+            if (one_reads[lg]) HIPCHK(launch_one(sa, oa, lg != 0, (int)P, s));
+        return PH_OK;
     }
     // binning (the set-up kernel writes what a plan uploads at creation;
     // kernels only, so that a caller may capture the sequence)
@@ -1488,28 +1675,6 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     HIPCHK(launch_bin_scatter(ba, s));
 
     // FP32 sweeps, longest bin first, then the FP64 rescue (all on `s`)
-    SweepArgs sa{};
-    sa.pb.read_offset = pb->read_offset;
-    sa.pb.read_bases = pb->read_bases;
-    sa.pb.bq = pb->base_qual;
-    sa.pb.iq = pb->ins_qual;
-    sa.pb.dq = pb->del_qual;
-    sa.pb.gq = pb->gcp_qual;
-    sa.pb.hap_offset = pb->hap_offset;
-    sa.pb.hap_bases = pb->hap_bases;
-    sa.lin_params = log10_params ? lin : nullptr;
-    sa.recs = recs;
-    sa.book = book;
-    sa.out_log10 = out_log10L;
-    sa.out_status = out_status;
-    sa.rescue_list = rescue;
-    sa.rescue_stride = P;
-    sa.threshold = 1e-28;
-    sa.floor64 = std::ldexp(1.0, -1000);
-    sa.num_bins = nbins;
-    for (int b = 0; b < nbins; ++b) sa.bins[b] = {g_na_table[nbins - 1 - b].P, g_na_table[nbins - 1 - b].K};
-    sa.plain_count = (int32_t)P;
-    sa.long_bin = -1;
     for (int b = 0; b < nbins; ++b) {
         if (!bin_pairs[b]) continue;
         const int G = 64 / sa.bins[b].P;

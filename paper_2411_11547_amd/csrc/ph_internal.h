@@ -153,6 +153,22 @@ struct SweepArgs {
     int32_t chain_rec_base;
 };
 
+// Small calls (one launch, one pair per wave): a pair, the PAD columns its
+// haplotype follows and the steps between two flushes of its row sum.
+struct OneRec {
+    int32_t read, hap, out, n;
+    int32_t lead, flush;
+};
+constexpr int kOneBatches = 256;  // batches whose first pairs travel in the kernel's arguments
+struct OneArgs {
+    const OneRec *recs;          // a plan's list, else NULL:
+    int32_t num_batches;
+    const int32_t *batch_read_begin, *batch_hap_begin;
+    const int64_t *out_offset;   // first pair of every batch, or NULL: first[]
+    uint8_t *rescued;            // per output: 1 if the pair went to FP64 (may be NULL)
+    int32_t first[kOneBatches];
+};
+
 // Adjoint: one record per pair, grouped by (P, K), longest haplotype first,
 // tiled G = 64/P pairs at a time; every group of a tile uses the step count S
 // of the tile's first record.  A persistent workgroup takes a tile, runs its
@@ -246,6 +262,7 @@ hipError_t launch_long32(const SweepArgs &a, int window, int grid, hipStream_t s
 hipError_t launch_long64(const SweepArgs &a, int window, int grid, hipStream_t s);
 int long32_blocks_per_cu();
 int long64_blocks_per_cu();
+hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s);
 hipError_t launch_prep_params(const float *lg, int64_t npos, double *lin, hipStream_t s);
 hipError_t launch_validate(const DevProblem &pb, int64_t nread_bases, int64_t nhap_bases,
                            int32_t *bad, hipStream_t s);

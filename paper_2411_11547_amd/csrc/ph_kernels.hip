@@ -135,13 +135,15 @@ struct RingPer {
 };
 
 template <int P>
-__device__ __forceinline__ void ring_load(uint32_t (&c)[RingPer<P>::N], int chunk, const uint8_t *hap, int n, int t)
+__device__ __forceinline__ void ring_load(uint32_t (&c)[RingPer<P>::N], int chunk, const uint8_t *hap, int n, int t,
+                                          int lead = 0)
 {
     constexpr int PER = RingPer<P>::N;
 #pragma unroll
     for (int b = 0; b < PER; ++b) {
-        const int col = chunk * RingPer<P>::CH + t * PER + b;
-        c[b] = col < n ? (uint32_t)hap[col] : 0xffffu;
+        // (the columns before the lead are PAD as well)
+        const int col = chunk * RingPer<P>::CH + t * PER + b - lead;
+        c[b] = (uint32_t)col < (uint32_t)n ? (uint32_t)hap[col] : 0xffffu;
     }
 }
 
@@ -163,6 +165,8 @@ __device__ __forceinline__ void ring_store(uint16_t *ring, int chunk, const uint
 }
 
 enum { kModeBinned = 0, kModePlain = 1, kModeRescue = 2 };
+// what a one-pair sweep leaves to do
+enum { kPairDone = 0, kPairHat64 = 1, kPairPlain64 = 2 };
 
 // One anti-diagonal step of a lane: column j = s - t + 1 of rows tK+1..tK+K.
 // M, I, D hold column j-1 on entry and column j on exit; (Md, Id, Dd) are the
@@ -498,6 +502,13 @@ struct RangeHat<double> {
 // sweep) and the plain states for pairs with a row outside the rescaled
 // states and for what the rescaled FP64 sweep passes on (plain FP64 sweep).
 //
+// One-pair mode (S, one pair per wave, P = 64, the record given by value):
+// nothing is queued; the call returns which FP64 sweep the pair needs.  The
+// FP32 sum of row m is grouped as the pair's binned tile groups it: the
+// haplotype follows one.lead PAD columns and the absorbing row is flushed every
+// one.flush steps, so its groups end at the same columns and the result is the
+// same bit for bit.
+//
 // Windowed mode (W, reads longer than kMaxReadLen; P = 64, one pair per
 // wave): the launch covers rows A.window * kLongRows + 1 .. + kLongRows of
 // the pair.  Its top boundary row (the states of the row above, columns
@@ -505,11 +516,12 @@ struct RangeHat<double> {
 // at a time in LDS, and the window's last row is written back in place
 // (column j is read at step j-1 and written at step j+62).  Only the window
 // that holds the absorbing row m+1 produces the result.
-template <typename T, int P, int K, bool W = false, bool V = false, bool H = sizeof(T) == 4>
-__device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int rec_first,
-                           int nvalid, char *lds, int bnd_slot = 0)
+template <typename T, int P, int K, bool W = false, bool V = false, bool H = sizeof(T) == 4, bool S = false>
+__device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int rec_first,
+                          int nvalid, char *lds, int bnd_slot = 0, OneRec one = OneRec())
 {
     using C = Cfg<T, P, K>;
+    static_assert(!S || (P == 64 && !W), "one-pair mode: 64 lanes, no windows");
     static_assert(!W || (P == 64 && K * P == kLongRows), "windowed sweep: 64 lanes x kLongRows / 64 rows");
     static_assert(sizeof(T) == 4 || !H || (!W && !V), "FP64 rescaled states: the binned sum-product sweep only");
     constexpr bool HAT = H;  // rescaled states (M, It, Dh)
@@ -522,7 +534,11 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
     const int ridx = gvalid ? (rec_idx_list ? rec_idx_list[rec_first + g] : rec_first + g) : 0;
 
     PairRec rec = {0, 0, 0, 0};
-    if (gvalid) rec = A.recs[ridx];
+    if constexpr (S)
+        rec = PairRec{one.read, one.hap, one.out, one.n};
+    else if (gvalid)
+        rec = A.recs[ridx];
+    const int lead = S ? one.lead : 0;
     const DevProblem &pb = A.pb;
     const double *lin = A.lin_params;
     const int64_t ro = gvalid ? pb.read_offset[rec.read] : 0;
@@ -530,14 +546,14 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
     if constexpr (W) {
         // a pair whose absorbing row lies in an earlier window is done
         gvalid = gvalid && m >= r0;
-        if (!__builtin_amdgcn_readfirstlane((int)gvalid)) return;
+        if (!__builtin_amdgcn_readfirstlane((int)gvalid)) return kPairDone;
     }
     const bool fin = !W || m < r0 + kLongRows;  // this window holds row m + 1
     // Chain tile (FP32 binned sweep, records with n < 0): every group of the
     // tile sweeps its read against the same NH haplotypes h0, h0 + 1, ... of
     // its batch in turn, along their code stream; lane i holds the length of
     // haplotype h0 + i, Lc is the stream's length up to the last haplotype's end.
-    constexpr bool CHN = kChains && HAT && !W && sizeof(T) == 4;
+    constexpr bool CHN = kChains && HAT && !W && !S && sizeof(T) == 4;
     bool chain = false;
     int NH = 1, h0 = 0, nvec = 0, Lc = 0;
     if constexpr (CHN) {
@@ -561,9 +577,11 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
     T *top = (T *)(lds + C::E_BYTES + C::G * C::RING_BYTES);  // windowed: [3][64] staged boundary values
 
     // the longest haplotype (chain) of the wave sets the number of steps
-    int nmax = nring;
+    int nmax = nring + lead;
+    if constexpr (!S) {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) nmax = max(nmax, __shfl_xor(nmax, off));
+        for (int off = 1; off < 64; off <<= 1) nmax = max(nmax, __shfl_xor(nmax, off));
+    }
     nmax = __builtin_amdgcn_readfirstlane(nmax);
 
     // ---- prologue: parameters of my rows, my slice of the E table ----------
@@ -774,8 +792,8 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
     __syncthreads();
     {
         uint32_t c0[RingPer<P>::N], c1[RingPer<P>::N];
-        ring_load<P>(c0, 0, hap, nring, t);
-        ring_load<P>(c1, 1, hap, nring, t);
+        ring_load<P>(c0, 0, hap, nring, t, lead);
+        ring_load<P>(c1, 1, hap, nring, t, lead);
         ring_store<P>(ring, 0, c0, t, C::CODE_BYTES, chain);
         ring_store<P>(ring, 1, c1, t, C::CODE_BYTES, chain);
     }
@@ -869,9 +887,24 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
         }
     };
 
+    // the absorbing row's Dh (Viterbi: its running maximum) moves into the
+    // FP64 accumulator; nothing else reads it
+    auto flush_row = [&]() {
+        T dm = 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            dm = r == rml ? D[r] : dm;
+            D[r] = r == rml ? (T)0 : D[r];
+        }
+        if constexpr (V)
+            acc = fmax(acc, (double)dm);
+        else
+            acc += (double)dm;
+    };
+
     for (int s0 = 0; s0 < total; s0 += CH) {
         uint32_t ahead[RingPer<P>::N];
-        ring_load<P>(ahead, s0 / CH + 2, hap, nring, t);
+        ring_load<P>(ahead, s0 / CH + 2, hap, nring, t, lead);
         if constexpr (W) {
             // lane t stages the boundary row at column s0 + 1 + t, which
             // lane 0 takes at step s0 + t (zero in window 0: the row-0
@@ -902,7 +935,8 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
                 (const volatile __attribute__((address_space(3))) uint16_t *)hp;
             int u = 0;
             for (;;) {
-                const int stop = (CHN && rs_next - s0 < cnt) ? rs_next - s0 : cnt;
+                const int stop = (CHN && rs_next - s0 < cnt) ? rs_next - s0
+                                 : (S && u == 0 && one.flush < cnt) ? one.flush : cnt;
                 for (; u < stop; u += 2) {
                     load_lam<T, P, K>(lb, ebase_lane + hv[u + 1]);
                     if constexpr (W) {
@@ -919,19 +953,9 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
                 }
                 if (u >= cnt) break;
                 if constexpr (CHN) chain_clear();
+                if constexpr (S) flush_row();
             }
-            // the absorbing row's Dh (Viterbi: its running maximum) moves
-            // into the FP64 accumulator; nothing else reads it
-            T dm = 0;
-#pragma unroll
-            for (int r = 0; r < K; ++r) {
-                dm = r == rml ? D[r] : dm;
-                D[r] = r == rml ? (T)0 : D[r];
-            }
-            if constexpr (V)
-                acc = fmax(acc, (double)dm);
-            else
-                acc += (double)dm;
+            flush_row();
         } else {
             T part = 0;
             for (int u = 0; u < cnt; u += 2) {
@@ -985,8 +1009,34 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
                     A.out_status[out] = 0;
                 }
             }
-            return;
+            return kPairDone;
         }
+    }
+    if constexpr (S) {
+        // the result, or which FP64 sweep the pair needs, from the lane that
+        // holds the sum
+        int need = kPairDone;
+        if (owner) {
+            bool ok;
+            uint8_t st = 1;
+            if constexpr (sizeof(T) == 4) {
+                ok = !gbad && (acc >= A.threshold) && (acc <= 3.0e38);
+                need = ok ? kPairDone : (gbad || V) ? kPairPlain64 : kPairHat64;
+                st = 0;
+            } else if constexpr (HAT) {
+                ok = !gbad && acc >= A.floor64 && acc <= 1.0e300;
+                need = ok ? kPairDone : kPairPlain64;
+            } else {
+                ok = true;
+                st = acc >= A.floor64 ? 1 : 2;
+            }
+            if (ok) {
+                A.out_log10[rec.out] = log10(acc) - (double)kExp * 0.30102999566398119521;
+                if (A.out_status) A.out_status[rec.out] = st;
+            }
+        }
+        __syncthreads();  // the tables in LDS are rebuilt by the pair's next sweep
+        return __builtin_amdgcn_readlane(need, HAT ? __builtin_amdgcn_readfirstlane(m / K) : P - 1);
     }
     if (gvalid && owner && fin) {
         const double lg = log10(acc) - (double)kExp * 0.30102999566398119521;
@@ -1026,6 +1076,7 @@ __device__ void sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int 
             }
         }
     }
+    return kPairDone;
 }
 
 // ---------------------------------------------------------------------------
@@ -1171,6 +1222,96 @@ __global__ __launch_bounds__(64) void k_long64(SweepArgs A)
     while (item < count) {
         sweep_tile<double, 64, 16, true, V>(A, A.long_rescue_list, item, 1, lds, item);
         item = next_tile(&bk->long64_counter[A.window]);
+    }
+}
+
+// Small calls: one launch, one pair per wave, 64 lanes x ceil((m + 1) / 64)
+// rows; a pair that leaves the FP32 range is redone in FP64 by its own wave.
+// What bounds a small call is not the GPU's rate but the chain of launches and
+// the length of one tile: a wave issues at most one vector instruction per 5
+// clocks, so a step of 16 rows takes 0.2 us and one tile of 350 columns 77 us,
+// a step of 4 rows 0.06 us.  Reads of up to 255 bases (LONG = false) and of
+// 256 to 1023 are two launches, each present only if the shape has such reads:
+// the first keeps the tables (12.9 KB in FP64) and registers of 4 rows per
+// lane, 12 waves per CU.
+//
+// The pair of a wave: record blockIdx.x of the plan's list, or (no plan) pair
+// blockIdx.x in output order, found in the first pair of every batch, with
+// the lead of the built-in table's tile (16 lanes x ceil((m + 1) / 16) rows up to
+// 255 bases).
+template <bool LONG, bool V, bool FREE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3))) void k_one(SweepArgs A, OneArgs L)
+{
+    constexpr int KHI = LONG ? 16 : 4;
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES];
+    OneRec one;
+    if constexpr (FREE) {
+        const int k = blockIdx.x;
+        int lo = 0, hi = L.num_batches;  // largest q with first pair <= k
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            const int first = L.out_offset ? (int)L.out_offset[mid] : L.first[mid];
+            if (first <= k) lo = mid; else hi = mid;
+        }
+        const int local = k - (L.out_offset ? (int)L.out_offset[lo] : L.first[lo]);
+        const int h0 = L.batch_hap_begin[lo], nh = L.batch_hap_begin[lo + 1] - h0;
+        one.read = L.batch_read_begin[lo] + local / nh;
+        one.hap = h0 + local % nh;
+        one.out = k;
+        one.n = (int)(A.pb.hap_offset[one.hap + 1] - A.pb.hap_offset[one.hap]);
+    } else {
+        one = L.recs[blockIdx.x];
+    }
+    const int m = (int)(A.pb.read_offset[one.read + 1] - A.pb.read_offset[one.read]);
+    if ((m > 255) != LONG) return;
+    const int K = (m + 64) / 64;
+    if constexpr (FREE) {
+        one.lead = LONG ? 0 : (m / ((m + 16) / 16) - m / K) & 31;
+        one.flush = LONG ? 64 : 32;
+    }
+    int need = kPairDone;
+    switch (K) {
+#define PH_ONE(k) \
+    case k: \
+        if constexpr (LONG == (k > 4)) need = sweep_tile<float, 64, k, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one); \
+        break;
+        PH_ONE(1) PH_ONE(2) PH_ONE(3) PH_ONE(4) PH_ONE(5) PH_ONE(6) PH_ONE(7) PH_ONE(8)
+        PH_ONE(9) PH_ONE(10) PH_ONE(11) PH_ONE(12) PH_ONE(13) PH_ONE(14) PH_ONE(15) PH_ONE(16)
+#undef PH_ONE
+    default: break;
+    }
+    if (L.rescued && threadIdx.x == 0) L.rescued[one.out] = need != kPairDone;
+    if (need == kPairDone) return;
+    // FP64, in the rescue classes' configurations (2, 4, 8 or 16 rows per lane)
+    one.lead = 0;
+    one.flush = 64;
+    if constexpr (!V) {
+        if (need == kPairHat64) {
+            if constexpr (!LONG) {
+                if (m < 128)
+                    need = sweep_tile<double, 64, 2, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                else
+                    need = sweep_tile<double, 64, 4, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+            } else {
+                if (m < 512)
+                    need = sweep_tile<double, 64, 8, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                else
+                    need = sweep_tile<double, 64, 16, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+            }
+        }
+    }
+    if (need == kPairPlain64) {
+        if constexpr (!LONG) {
+            if (m < 128)
+                sweep_tile<double, 64, 2, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+            else
+                sweep_tile<double, 64, 4, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+        } else {
+            if (m < 512)
+                sweep_tile<double, 64, 8, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+            else
+                sweep_tile<double, 64, 16, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+        }
     }
 }
 
@@ -1538,6 +1679,19 @@ hipError_t launch_long64(const SweepArgs &a, int window, int grid, hipStream_t s
     else
         hipLaunchKernelGGL(k_long64<false>, dim3(grid), dim3(64), 0, s, b);
     return hipGetLastError();
+}
+
+hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s)
+{
+#define PH_LONE(lg, v, f)                                                                    \
+    if (long_reads == lg && (a.viterbi != 0) == v && (l.recs == nullptr) == f) {               \
+        hipLaunchKernelGGL((k_one<lg, v, f>), dim3(pairs), dim3(64), 0, s, a, l);              \
+        return hipGetLastError();                                                            \
+    }
+    PH_LONE(false, false, false) PH_LONE(true, false, false) PH_LONE(false, true, false) PH_LONE(true, true, false)
+    PH_LONE(false, false, true) PH_LONE(true, false, true)
+#undef PH_LONE
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_na_setup(const int32_t *rb, const int32_t *hb, int32_t nb, int64_t *out_offset,
