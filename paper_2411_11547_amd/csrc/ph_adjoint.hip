@@ -505,17 +505,7 @@ __device__ __forceinline__ void adj_stage_ck(const float *ck, int q, int lane, f
                                          (__attribute__((address_space(3))) void *)(ckl + v * 64), 4, 0, 0);
 }
 
-// s_waitcnt on gfx9: vmcnt(0) (every vector memory operation of the wave,
-// LDS copies included, has completed), lgkmcnt(0) (every LDS read has
-// returned); each also a compiler barrier for memory
-__device__ __forceinline__ void wait_vm0()
-{
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0x0f70);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// vmcnt(N) for N < 64: at most N vector memory operations of the wave
+// s_waitcnt on gfx9, each also a compiler barrier for memory: vmcnt(N) for N < 64: at most N vector memory operations of the wave
 // still outstanding
 template <int N>
 __device__ __forceinline__ void wait_vm()
@@ -526,6 +516,7 @@ __device__ __forceinline__ void wait_vm()
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// lgkmcnt(0): every LDS read has returned
 __device__ __forceinline__ void wait_lgkm0()
 {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);

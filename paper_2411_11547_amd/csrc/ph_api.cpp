@@ -202,11 +202,12 @@ struct ph_plan {
     int rescue_grid[2][kRescueClasses] = {};  // [rescaled FP64, plain FP64] per class
     int plain_K = 0, plain_grid = 0;
     // reads longer than kMaxReadLen: one extra bin swept in windows
-    int long_bin = -1, windows = 0, long_grid = 0, long64_grid = 0;
+    int long_bin = -1, long_K = 0, windows = 0, windows64 = 0, long_grid = 0, long64_grid = 0;
     int64_t long_pairs = 0, bnd_stride = 0;
     float *d_bnd32 = nullptr;
     double *d_bnd64 = nullptr;
     int32_t *d_long_rescue = nullptr;
+    int32_t *d_progress = nullptr;  // columns done of every window: FP32, FP64 rescaled, FP64 plain
     int split_at = -1;     // offset of the haplotype-length split table in d_m2bin (-1: none)
     std::vector<std::pair<int, int>> launch_order;  // FP32 stage: (bin, side stream) in launch order
     bool single = false;   // one persistent FP32 launch over all bins
@@ -214,6 +215,7 @@ struct ph_plan {
     // binned mode: work lists built from the shape at plan creation, with
     // chain tiles; the call copies the book image and writes the chain codes
     std::vector<int64_t> bin_tiles;    // tiles per bin
+    std::vector<int64_t> bin_cols;     // columns of each bin's longest tile
     int32_t chain_rec_base = 0;        // records of the lists; FP64 records of chain pairs follow
     bool chain_tiles = false;
     Book *d_book_img = nullptr;
@@ -303,7 +305,7 @@ void free_plan(ph_plan *p)
     if (p->adj_graph) (void)hipGraphDestroy(p->adj_graph);
     void *bufs[] = {p->d_out_offset, p->d_m2bin, p->d_bin_G, p->d_hist, p->d_recs, p->d_book, p->d_bad, p->d_rescue, p->d_lin,
                     p->d_book_img, p->d_chain_codes, p->d_one, p->d_one_rescued,
-                    p->d_bnd32, p->d_bnd64, p->d_long_rescue,
+                    p->d_bnd32, p->d_bnd64, p->d_long_rescue, p->d_progress,
                     p->d_adj_recs, p->d_ws, p->d_adj_ctr, p->d_q64, p->d_ws64, p->d_grad_pair, p->d_red};
     for (auto &e : p->ev_adj)
         if (e) (void)hipEventDestroy(e);
@@ -609,6 +611,7 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     recs.clear();
     recs.reserve(pool.size());
     p->bin_tiles.assign(nbins, 0);
+    p->bin_cols.assign(nbins, 0);
     p->chain_tiles = false;
     chain_tile_count = 0;
     int64_t tiles = 0;
@@ -621,6 +624,8 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
             for (int g = 0; g < t.count; ++g) recs.push_back(pool[(size_t)t.first + g]);
         for (const Tile &t : singles[b]) recs.push_back(pool[(size_t)t.first]);
         const int G = 64 / binP(b);
+        for (const auto *l : {&chain_tiles[b], &singles[b]})
+            if (!l->empty()) p->bin_cols[b] = std::max(p->bin_cols[b], l->front().len);
         p->bin_tiles[b] = (int64_t)chain_tiles[b].size() + ((int64_t)singles[b].size() + G - 1) / G;
         p->chain_tiles = p->chain_tiles || !chain_tiles[b].empty();
         chain_tile_count += (int64_t)chain_tiles[b].size();
@@ -658,21 +663,14 @@ double one_pair_ns(const int32_t *rb, const int32_t *hb, const int64_t *ro, cons
 }
 
 // Time of a binned plan's launches: the bins run on side streams in turn.
-double binned_ns(const ph_plan *p, const std::vector<PairRec> &recs, const Book &img, const int64_t *ho)
+double binned_ns(const ph_plan *p)
 {
     double stream[kSideStreams] = {};
     const int nbins = (int)p->table.size();
     int next = 0;
     for (int b = 0; b < nbins; ++b) {
         const TuneEntry &e = p->table[nbins - 1 - b];
-        int64_t cols = 0;  // of the bin's longest tile: its first chain or its first single pair
-        for (int32_t i = img.bin_rec_begin[b]; i < img.bin_rec_begin[b + 1]; ++i) {
-            const PairRec &r = recs[(size_t)i];
-            const int64_t len = r.n >= 0 ? r.n : ho[r.hap - r.n] - ho[r.hap] + (int64_t)kChainSep * (-r.n - 1);
-            cols = std::max(cols, len);
-            if (r.n >= 0) break;
-        }
-        if (cols) stream[next++ % kSideStreams] += tile_ns(cols, e.P, e.K);
+        if (p->bin_cols[b]) stream[next++ % kSideStreams] += tile_ns(p->bin_cols[b], e.P, e.K);
     }
     return kBinnedNs + (double)p->cells / kBinnedCellsPerNs + *std::max_element(stream, stream + kSideStreams);
 }
@@ -789,12 +787,11 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
         p->table = default_table(opts.force_p);
     }
     if (max_m > kMaxReadLen) {
-        // the longest bin: 64 lanes x 16 rows per window, never tuned
+        // the longest bin, swept in windows, never tuned
         if (opts.plain) return fail(PH_ERR_UNSUPPORTED, "plain mode supports reads up to %d bases", kMaxReadLen);
         if ((int)p->table.size() >= kMaxBins) return fail(PH_ERR_INVALID, "too many bins");
         p->table.push_back(TuneEntry{kMaxLongReadLen, 64, kLongRows / 64});
         p->long_bin = 0;  // bins are numbered longest first
-        p->windows = max_m / kLongRows + 1;
     }
     const int nbins = (int)p->table.size();
     if (max_m > p->table.back().max_m)
@@ -818,7 +815,7 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
         split[kMaxBins + b] = (int16_t)(e.n_split ? b - 1 : b);
         any_split = any_split || e.n_split;
     }
-    int64_t cells = 0;
+    int64_t cells = 0, few_items = 0;  // few_items: windows of the long pairs at kLongK32Few rows per lane
     for (int32_t q = 0; q < nb; ++q) {
         const int64_t H = hb[q + 1] - hb[q];
         int64_t nsum = 0;
@@ -829,6 +826,7 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
             cells += (int64_t)m * nsum;
             if (bin == p->long_bin) {  // every pair of the long bin gets a boundary slot
                 p->long_pairs += H;
+                few_items += H * (m / (64 * kLongK32Few) + 1);
                 for (int32_t h = hb[q]; h < hb[q + 1]; ++h)
                     p->bnd_stride = std::max<int64_t>(p->bnd_stride, 3 * (ho[h + 1] - ho[h] + 1));
             } else {
@@ -837,6 +835,12 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
         }
     }
     p->cells = cells;
+    // 3 waves per SIMD of 4-row windows fill the GPU; more items than that take
+    // 16 rows per lane
+    p->long_K = few_items <= 3072 ? kLongK32Few : kLongK32Many;
+    p->windows = max_m / (64 * p->long_K) + 1;
+    p->windows64 = max_m / (64 * kLongK64) + 1;
+    p->bnd_stride = (p->bnd_stride + 11) / 12 * 12;
     // the split table travels behind the length map in the same device array
     if (any_split) {
         p->split_at = (int)m2bin.size();
@@ -856,7 +860,7 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
     // small plans (reads of up to 1,023 bases, no option that names a launch)
     std::vector<OneRec> one;
     if (!opts.plain && !opts.force_p && !opts.single_launch && P > 0 && max_m <= kMaxReadLen &&
-        one_pair_ns(rb, hb, ro, ho, nb) <= binned_ns(p.get(), recs, img, ho)) {
+        one_pair_ns(rb, hb, ro, ho, nb) <= binned_ns(p.get())) {
         p->one = true;
         one = one_list(p.get(), recs, img, ro, ho);
         for (const OneRec &r : one) p->one_reads[ro[r.read + 1] - ro[r.read] > 255] = true;
@@ -888,8 +892,9 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
             if (p->bin_grid[b]) p->launch_order.push_back({b, next++ % kSideStreams});
     }
     if (p->long_pairs) {
-        p->long_grid = (int)std::min<int64_t>(p->long_pairs, (int64_t)p->cus * long32_blocks_per_cu());
-        p->long64_grid = (int)std::min<int64_t>(p->long_pairs, (int64_t)p->cus * long64_blocks_per_cu());
+        p->long_grid =
+            (int)std::min<int64_t>(p->long_pairs * p->windows, (int64_t)p->cus * long32_blocks_per_cu(p->long_K));
+        p->long64_grid = (int)std::min<int64_t>(p->long_pairs * p->windows64, (int64_t)p->cus * long64_blocks_per_cu());
     }
     if (opts.single_launch && !opts.plain) {
         bool ok = true;
@@ -946,7 +951,8 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
     if (p->long_pairs) {
         if ((st = dalloc(&p->d_bnd32, (size_t)(p->long_pairs * p->bnd_stride)))) return st;
         if ((st = dalloc(&p->d_bnd64, (size_t)(p->long_pairs * p->bnd_stride)))) return st;
-        if ((st = dalloc(&p->d_long_rescue, (size_t)p->long_pairs))) return st;
+        if ((st = dalloc(&p->d_long_rescue, (size_t)p->long_pairs * 2))) return st;
+        if ((st = dalloc(&p->d_progress, (size_t)(p->long_pairs * (p->windows + 2 * p->windows64))))) return st;
     }
     HIPCHK(hipMemset(p->d_book, 0, sizeof(Book)));
 
@@ -1040,6 +1046,7 @@ SweepArgs sweep_args(ph_plan *p, const ph_problem *pb, const double *lin, double
     a.long_bin = p->long_pairs ? p->long_bin : -1;
     a.bnd_stride = p->bnd_stride;
     a.long_rescue_list = p->d_long_rescue;
+    a.long_plain_list = p->d_long_rescue ? p->d_long_rescue + p->long_pairs : nullptr;
     a.chain_codes = p->d_chain_codes;
     a.chain_rec_base = p->chain_rec_base;
     a.chain_recs = p->chain_tiles ? p->d_recs + p->chain_rec_base : nullptr;
@@ -1065,6 +1072,8 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
             // the work lists come from plan creation: the book's bin ranges,
             // zero cursors, and the chain code stream of this call's haplotypes
             HIPCHK(launch_book_copy(p->d_book, p->d_book_img, s));
+            if (p->long_pairs)  // no window has written a column
+                HIPCHK(launch_zero_f32((float *)p->d_progress, p->long_pairs * (p->windows + 2 * p->windows64), s));
             if (p->chain_tiles)
                 HIPCHK(launch_chain_codes(pb->hap_offset, pb->hap_bases, p->nh, p->d_chain_codes, s));
         }
@@ -1075,7 +1084,7 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
             HIPCHK(launch_fwd32_single(sa, p->single_grid, s));
         } else {
             // the bins on side streams forked from s, in the plan's launch
-            // order; the windows of the long bin run in order on one stream
+            // order
             HIPCHK(hipEventRecord(p->fork, s));
             bool used[kSideStreams] = {};
             for (const auto &bk : p->launch_order) {
@@ -1087,7 +1096,9 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
                 if (b == p->long_bin && p->long_pairs) {
                     SweepArgs la = sa;
                     la.bnd = p->d_bnd32;
-                    for (int w = 0; w < p->windows; ++w) HIPCHK(launch_long32(la, w, p->long_grid, p->side[k]));
+                    la.windows = p->windows;
+                    la.progress = p->d_progress;
+                    HIPCHK(launch_long32(la, p->long_K, p->long_grid, p->side[k]));
                 } else {
                     HIPCHK(launch_fwd32(sa, sa.bins[b].P, sa.bins[b].K, b, p->bin_grid[b], p->side[k]));
                 }
@@ -1107,7 +1118,11 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
         if (p->long_pairs) {
             SweepArgs la = sa;
             la.bnd = p->d_bnd64;
-            for (int w = 0; w < p->windows; ++w) HIPCHK(launch_long64(la, w, p->long64_grid, s));
+            la.windows = p->windows64;
+            la.progress = p->d_progress + p->long_pairs * p->windows;
+            HIPCHK(launch_long64(la, true, p->long64_grid, s));
+            la.progress += p->long_pairs * p->windows64;
+            HIPCHK(launch_long64(la, false, p->long64_grid, s));
         }
     }
     return PH_OK;
@@ -1408,13 +1423,14 @@ ph_status ph_plan_rescued(ph_plan *p, int64_t *count)
         for (uint8_t w : went) *count += w;
         return PH_OK;
     }
-    int32_t c[kRescueQueues], lc = 0, passed = 0;
+    int32_t c[kRescueQueues], lc = 0, lp = 0, passed = 0;
     HIPCHK(hipMemcpy(c, p->d_book->rescue_count, sizeof(c), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&lc, &p->d_book->long_rescue_count, sizeof(lc), hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpy(&lp, &p->d_book->long_plain_count, sizeof(lp), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&passed, &p->d_book->rescue_passed, sizeof(passed), hipMemcpyDeviceToHost));
-    // pairs of reads longer than 1023 bases (windowed FP64 sweep), plus both
-    // sets of queues, less the pairs the rescaled sweep passed on (counted twice)
-    *count = lc - passed;
+    // pairs of reads longer than 1023 bases (windowed FP64 sweeps), plus both
+    // sets of queues, less the pairs the rescaled sweeps passed on (counted twice)
+    *count = (int64_t)lc + lp - passed;
     for (int i = 0; i < kRescueQueues; ++i) *count += c[i];
     return PH_OK;
 }

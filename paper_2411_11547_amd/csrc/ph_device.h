@@ -140,6 +140,25 @@ __device__ __forceinline__ int next_tile(int32_t *cursor)
     return __builtin_amdgcn_readlane(t, 0);
 }
 
+// the same with a 64-bit cursor
+__device__ __forceinline__ uint64_t next_item(unsigned long long *cursor)
+{
+    unsigned long long t = 0;
+    if (threadIdx.x == 0) t = atomicAdd(cursor, 1ull);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)t, 0);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(t >> 32), 0);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// s_waitcnt on gfx9: vmcnt(0), every vector memory operation of the wave (LDS
+// copies included) has completed; also a compiler barrier for memory
+__device__ __forceinline__ void wait_vm0()
+{
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // Parameters of one read row in linear space.  Phred mode decodes the
 // quality bytes through the FP64 table; explicit mode reads the row's
 // exponentiated parameters, written once per call by k_prep_params.

@@ -32,11 +32,12 @@ constexpr int kRescueClasses = 4;        // FP64 sweep: 64 lanes x {2, 4, 8, 16}
 // set, one with a row outside the rescaled states into the second; the
 // rescaled FP64 sweep passes on what leaves its own range to the second.
 constexpr int kRescueQueues = 2 * kRescueClasses;
-// Longer reads run in windows of kLongRows rows (64 lanes x 16 rows): the
-// window's top boundary row comes from HBM, its bottom row goes back there
+// Longer reads run in windows of 64 K rows (64 lanes x K rows): the window's
+// top boundary row comes from memory, its bottom row goes back there.  K by the number of long pairs
+// (see k_long32).  The FP32 row sums are grouped as in windows of kLongRows rows.
 constexpr int kLongRows = 1024;
-constexpr int kMaxWindows = 64;
-constexpr int kMaxLongReadLen = kLongRows * kMaxWindows - 1;
+constexpr int kLongK32Few = 4, kLongK32Many = 16, kLongK64 = 4;
+constexpr int kMaxLongReadLen = 65535;
 
 // One read/haplotype pair: indices into the problem and into the output.
 // In a chain tile of the FP32 sweep (n < 0) a record stands for the read
@@ -101,9 +102,11 @@ struct Book {
     int32_t rescue_count[kRescueQueues];   // FP64 queue lengths
     int32_t rescue_counter[kRescueQueues]; // FP64 sweep work cursors
     int32_t rescue_passed;                 // pairs the rescaled FP64 sweep passed on
-    int32_t long_counter[kMaxWindows];     // FP32 windowed passes: work cursor per window
-    int32_t long64_counter[kMaxWindows];   // FP64 windowed passes: work cursor per window
-    int32_t long_rescue_count;             // FP64 queue of long pairs
+    int32_t long_rescue_count;             // FP64 queues of long pairs: rescaled states,
+    int32_t long_plain_count;              // plain states
+    unsigned long long long_next;          // work cursors of the windowed sweeps: FP32,
+    unsigned long long long64_next;        // FP64 rescaled,
+    unsigned long long long_plain_next;    // FP64 plain
 };
 
 struct BinArgs {
@@ -139,18 +142,25 @@ struct SweepArgs {
     int32_t mode;                // 0 binned FP32 + rescue, 1 plain FP32, 2 FP64 rescue
     int32_t rescue_class;        // FP64: which queue
     int32_t plain_count;         // plain: number of records (tiles of 1 pair)
-    // reads longer than kMaxReadLen: bin `long_bin`, windows of kLongRows rows
+    // reads longer than kMaxReadLen: bin `long_bin`, swept in windows
     int32_t long_bin;            // -1 if none
-    int32_t window;              // window of this launch
-    void *bnd;                   // boundary rows, [pair slot][n_max + 1][3] of T
-    int64_t bnd_stride;          // elements per pair slot
-    int32_t *long_rescue_list;   // FP64 queue of long pairs (record indices)
+    int32_t windows;             // work items per pair (windows of the longest read)
+    void *bnd;                   // boundary rows, [pair slot][bnd_stride] of T
+    int64_t bnd_stride;          // elements per pair slot: 3 (n_max + 1) and more
+    int32_t *progress;           // [pair slot][windows] columns of its last row that a window has written
+    int32_t *long_rescue_list;   // FP64 queues of long pairs (record indices): rescaled,
+    int32_t *long_plain_list;    // plain
     int32_t viterbi;             // 1: max-product score (Viterbi) instead of the likelihood
     // chain tiles: the code stream, and where the FP64 records of their
     // pairs go (pair `out` of a chain at record chain_rec_base + out)
     const uint8_t *chain_codes;
     PairRec *chain_recs;
     int32_t chain_rec_base;
+};
+
+// Windowed sweep: the pair's boundary slot and the window of a work item.
+struct WinRec {
+    int32_t slot, w;
 };
 
 // Small calls (one launch, one pair per wave): a pair, the PAD columns its
@@ -258,9 +268,9 @@ hipError_t launch_fwd32_single(const SweepArgs &a, int grid, hipStream_t s);
 int fwd32_single_blocks_per_cu();
 bool single_supported(int P, int K);
 hipError_t launch_fwd64(const SweepArgs &a, int cls, bool rescaled, int grid, hipStream_t s);
-hipError_t launch_long32(const SweepArgs &a, int window, int grid, hipStream_t s);
-hipError_t launch_long64(const SweepArgs &a, int window, int grid, hipStream_t s);
-int long32_blocks_per_cu();
+hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s);
+hipError_t launch_long64(const SweepArgs &a, bool rescaled, int grid, hipStream_t s);
+int long32_blocks_per_cu(int K);
 int long64_blocks_per_cu();
 hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s);
 hipError_t launch_prep_params(const float *lg, int64_t npos, double *lin, hipStream_t s);

@@ -242,71 +242,9 @@ __device__ __forceinline__ float max_nonneg(float a, float b)
     return __builtin_bit_cast(float, max(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
 }
 
-// The same step with the rescaled states (M, It, Dh) of the FP32 sweeps;
-// lam holds alpha_i lambda_ij, ci, cd, ke and ep the coefficients cI, cD, kE
-// and eps of the file header.  (eM, eI, eD) are added to the values received
-// from the lane above: the first lane's row-0 boundary (eI = beta_1 / n,
-// scaled, enters through It with cI = 1 on the read's first row) or, in
-// windowed mode, the stored boundary row; zero in the other lanes.
-//
-// Groups of 4 and 8 lanes: the first lane of a group other than lanes 0, 16,
-// 32, 48 receives the previous group's last row, which may be that pair's
-// absorbing row or the row below it.  keep is 0 in the first lane of every
-// group and all ones elsewhere; it clears the received M and It there.  The
-// received Dh needs no mask: it meets cD = 0 on the read's first row.
-//
-// Viterbi mode (V): every sum a maximum, as in cell_step; the rescaling by
-// positive per-row factors commutes with the maximum, and every value is
-// non-negative (max_nonneg).
-template <typename T, int P, int K, bool W = false, bool V = false>
-__device__ __forceinline__ void cell_step_hat(T (&M)[K], T (&I)[K], T (&D)[K], T &Md, T &Id, T &Dd,
-                                              const T *lam, const T (&ci)[K], const T (&cd)[K],
-                                              const T (&ke)[K], const T (&ep)[K], T eI, uint32_t keep,
-                                              T eM = 0, T eD = 0)
-{
-    T Mu = shift_up<P>(M[K - 1]);
-    T Iu = shift_up<P>(I[K - 1]);
-    T Du = shift_up<P>(D[K - 1]);
-    if constexpr (P < 16) {
-        Mu = __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, Mu) & keep);
-        Iu = __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, Iu) & keep);
-    }
-    Iu += eI;
-    if constexpr (W) {
-        Mu += eM;
-        Du += eD;
-    }
-    T mup = Mu, iup = Iu, mdg = Md, idg = Id, ddg = Dd;
-#pragma unroll
-    for (int r = 0; r < K; ++r) {
-        const T mo = M[r], io = I[r], dol = D[r];
-        T mn, in, dn;
-        if constexpr (V) {
-            mn = lam[r] * max_nonneg(max_nonneg(mdg, ci[r] * idg), cd[r] * ddg);
-            in = max_nonneg(mup, ke[r] * iup);
-            dn = max_nonneg(mo, ep[r] * dol);
-        } else {
-            T x = fma(cd[r], ddg, mdg);
-            x = fma(ci[r], idg, x);
-            mn = lam[r] * x;
-            in = fma(ke[r], iup, mup);
-            dn = fma(ep[r], dol, mo);
-        }
-        M[r] = mn;
-        I[r] = in;
-        D[r] = dn;
-        mdg = mo;
-        idg = io;
-        ddg = dol;
-        mup = mn;
-        iup = in;
-    }
-    Md = Mu;
-    Id = Iu;
-    Dd = Du;
-}
-
-// cell_step_hat with the first row's sums formed by the lane above: at the
+// One step with the rescaled states (M, It, Dh); lam holds alpha_i
+// lambda_ij, ci, cd, ke and ep the coefficients cI, cD, kE and eps of the file
+// header.  At the
 // start of a step every lane forms, from its last row's (M, It, Dh) at its
 // column, the two sums the next lane's first row needs,
 //   X = M + cD' Dh + cI' It  and  Y = M + kE' It
@@ -314,17 +252,28 @@ __device__ __forceinline__ void cell_step_hat(T (&M)[K], T (&I)[K], T (&D)[K], T
 // X and Y instead of the three states: two lane shifts per step instead of
 // three (four DPP moves instead of six in FP64).  The receiving row then
 // costs M = lam X (X of the step before, held in Xd), It = Y and the Dh
-// update; the sums are the same operations in the same order as in
-// cell_step_hat, so the results are bit-identical.  In the first lane of a
-// group X is the row-0 boundary value eX (the It edge, cI = 1 on the read's
-// first row; Xd starts at eX) and Y is 0 (kE = 0 there).  Not used by the
-// windowed sweep, whose first lane takes a stored row.
-template <typename T, int P, int K, bool V = false>
+// update.  In the first lane of a group X is the row-0 boundary value eX (the
+// It edge, cI = 1 on the read's first row; Xd starts at eX) and Y is 0 (kE = 0
+// there).
+//
+// Groups of 4 and 8 lanes: the first lane of a group other than lanes 0, 16,
+// 32, 48 receives sums of the previous group's last row, which may be that
+// pair's absorbing row or the row below it.  keep is 0 in the first lane of
+// every group and all ones elsewhere; it clears the received X and Y there.
+//
+// Windowed mode (W): the first lane takes the stored sums (tX, tY) of the row
+// above the window at its column, and the last lane's X and Y, of the column
+// it holds on entry, are what the next window takes (X and Y on return).
+//
+// Viterbi mode (V): every sum a maximum, as in cell_step; the rescaling by
+// positive per-row factors commutes with the maximum, and every value is
+// non-negative (max_nonneg).
+template <typename T, int P, int K, bool V = false, bool W = false>
 __device__ __forceinline__ void cell_step_hx(T (&M)[K], T (&I)[K], T (&D)[K], T &Xd, const T *lam,
                                              const T (&ci)[K], const T (&cd)[K], const T (&ke)[K],
-                                             const T (&ep)[K], T cib, T cdb, T keb, T eX, uint32_t keep)
+                                             const T (&ep)[K], T cib, T cdb, T keb, T eX, uint32_t keep, T &X, T &Y,
+                                             T tX = 0, T tY = 0)
 {
-    T X, Y;
     if constexpr (V) {
         X = max_nonneg(max_nonneg(M[K - 1], cib * I[K - 1]), cdb * D[K - 1]);
         Y = max_nonneg(M[K - 1], keb * I[K - 1]);
@@ -332,11 +281,17 @@ __device__ __forceinline__ void cell_step_hx(T (&M)[K], T (&I)[K], T (&D)[K], T 
         X = fma(cib, I[K - 1], fma(cdb, D[K - 1], M[K - 1]));
         Y = fma(keb, I[K - 1], M[K - 1]);
     }
-    T Yu = shift_up<P>(Y);
+    T Yu;
+    if constexpr (W)
+        Yu = shift_up_or<P>(tY, Y);
+    else
+        Yu = shift_up<P>(Y);
     if constexpr (P < 16) Yu = __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, Yu) & keep);
     T mdg = M[0], idg = I[0], ddg = D[0];
     M[0] = lam[0] * Xd;
-    if constexpr (P < 16) {
+    if constexpr (W) {
+        Xd = shift_up_or<P>(tX, X);
+    } else if constexpr (P < 16) {
         Xd = __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, shift_up<P>(X)) & keep) + eX;
     } else {
         // the first lane keeps its X, which is eX at every step
@@ -388,46 +343,113 @@ __device__ __forceinline__ double from_next_lane(double v)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// One step of the windowed sweep (64 lanes): lane 0 takes the staged
-// boundary values of its column, and the last lane writes the window's last
-// row at its column back to the boundary slot unless this is the final window.
+// A device-scope exchange of one value between the waves of two windows: the
+// relaxed atomics go to the point where the XCDs' caches agree.
+__device__ __forceinline__ void put_shared(float2 *p, float2 v)
+{
+    __hip_atomic_store((uint64_t *)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_shared(const float2 *p)
+{
+    return __builtin_bit_cast(float2, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void put_shared(double *p, double v)
+{
+    __hip_atomic_store((uint64_t *)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_shared(const double *p)
+{
+    return __builtin_bit_cast(double, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// The boundary row between two windows of a long read.  Rescaled states: the
+// sums X and Y of the next window's first row (FP32: a float2 per column; FP64:
+// two rows of doubles); plain states (FP64): M, I and D, three rows.  A
+// window's wave stages the columns of a chunk in `top` (LDS), takes them one
+// per step, collects what its last lane hands on in `bot` and writes that
+// back a chunk at a time, in place: it has read a column 63 steps before it
+// overwrites it, and only the next window, which waits for the window's
+// progress, reads what was written.
+template <typename T, bool H>
+struct Boundary {
+    static constexpr int NV = H ? 2 : 3;
+    static constexpr int kBehind = H ? 63 : 62;  // bot[u] of chunk s0 is column s0 + u - kBehind
+    static constexpr int LDS_BYTES = 2 * NV * 64 * sizeof(T);
+    T *row;
+    int64_t plane;
+    T next[NV];  // the lane's column of the next chunk
+    __device__ __forceinline__ void open(void *slot, int64_t stride)
+    {
+        row = (T *)slot;
+        plane = stride / 3;
+    }
+    __device__ __forceinline__ void fetch(int j)
+    {
+        if constexpr (sizeof(T) == 4) {
+            const float2 v = get_shared((const float2 *)row + j);
+            next[0] = v.x;
+            next[1] = v.y;
+        } else {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) next[v] = get_shared(row + v * plane + j);
+        }
+    }
+    __device__ __forceinline__ void none(T x)
+    {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) next[v] = v == 0 ? x : (T)0;
+    }
+    __device__ __forceinline__ void stage(char *lds, int t) const
+    {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) ((T *)lds)[v * 64 + t] = next[v];
+    }
+    __device__ __forceinline__ void write(const char *lds, int u, int j) const
+    {
+        const T *bot = (const T *)lds + NV * 64 + u;
+        if constexpr (sizeof(T) == 4) {
+            put_shared((float2 *)row + j, make_float2(bot[0], bot[64]));
+        } else {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) put_shared(row + v * plane + j, bot[v * 64]);
+        }
+    }
+};
+
+// One step of the windowed sweep with the plain states (64 lanes): lane 0
+// takes the staged boundary values of its column, the last lane leaves its new
+// ones in `bot`.
 template <typename T, int K, bool V>
 __device__ __forceinline__ void window_step(T (&M)[K], T (&I)[K], T (&D)[K], T &Md, T &Id, T &Dd, const T *lam,
                                             const T (&al)[K], const T (&be)[K], const T (&de)[K],
                                             const T (&ep)[K], const T (&zt)[K], T epI0, T edge, T &acc,
-                                            const T *top, int u, int t, bool fin, T *bnd, int s, int n)
+                                            char *win, int u, int t)
 {
+    T *top = (T *)win, *bot = top + 192;
     const T tM = top[u], tI = top[64 + u], tD = top[128 + u];
     const bool first = t == 0;
     cell_step<T, 64, K, true, V>(M, I, D, Md, Id, Dd, lam, al, be, de, ep, zt, epI0, first ? tD + edge : (T)0,
                                  acc, first ? tM : (T)0, first ? tI : (T)0);
-    const int j = s - 62;  // the last lane's column
-    if (!fin && t == 63 && j >= 1 && j <= n) {
-        T *b = bnd + (int64_t)j * 3;
-        b[0] = M[K - 1];
-        b[1] = I[K - 1];
-        b[2] = D[K - 1];
+    if (t == 63) {
+        bot[u] = M[K - 1];
+        bot[64 + u] = I[K - 1];
+        bot[128 + u] = D[K - 1];
     }
 }
 
-// window_step with the rescaled states: the staged boundary row holds
-// (M, It, Dh) and the row-0 boundary enters through It.
+// The same with the rescaled states.
 template <typename T, int K, bool V>
-__device__ __forceinline__ void window_step_hat(T (&M)[K], T (&I)[K], T (&D)[K], T &Md, T &Id, T &Dd,
-                                                const T *lam, const T (&ci)[K], const T (&cd)[K],
-                                                const T (&ke)[K], const T (&ep)[K], T edge, const T *top, int u,
-                                                int t, bool fin, T *bnd, int s, int n)
+__device__ __forceinline__ void window_step_hx(T (&M)[K], T (&I)[K], T (&D)[K], T &Xd, const T *lam,
+                                               const T (&ci)[K], const T (&cd)[K], const T (&ke)[K],
+                                               const T (&ep)[K], T cib, T cdb, T keb, char *win, int u, int t)
 {
-    const T tM = top[u], tI = top[64 + u], tD = top[128 + u];
-    const bool first = t == 0;
-    cell_step_hat<T, 64, K, true, V>(M, I, D, Md, Id, Dd, lam, ci, cd, ke, ep, first ? tI + edge : (T)0, ~0u,
-                                     first ? tM : (T)0, first ? tD : (T)0);
-    const int j = s - 62;  // the last lane's column
-    if (!fin && t == 63 && j >= 1 && j <= n) {
-        T *b = bnd + (int64_t)j * 3;
-        b[0] = M[K - 1];
-        b[1] = I[K - 1];
-        b[2] = D[K - 1];
+    T *top = (T *)win, *bot = top + 128;
+    T X, Y;
+    cell_step_hx<T, 64, K, V, true>(M, I, D, Xd, lam, ci, cd, ke, ep, cib, cdb, keb, (T)0, ~0u, X, Y, top[u],
+                                    top[64 + u]);
+    if (t == 63) {
+        bot[u] = X;
+        bot[64 + u] = Y;
     }
 }
 
@@ -465,11 +487,12 @@ __device__ __forceinline__ bool hat_coef(const RowPar &p, const RowPar &pp, doub
     return ok;
 }
 
-// read row i >= 1 (0-based) at read offset ro cannot be carried by the FP32
-// rescaled states (see hat_coef)
+// read row i >= 1 (0-based) at read offset ro cannot be carried by the rescaled
+// states of T (see hat_coef)
+template <typename T>
 __device__ __forceinline__ bool hat_row_unsafe(const DevProblem &pb, const double *lin, int64_t ro, int i)
 {
-    if (lin) {
+    if (lin || sizeof(T) == 8) {
         double fac, ci, cd, ke;
         return !hat_coef(load_row(pb, lin, ro + i, c_prob), load_row(pb, lin, ro + i - 1, c_prob), fac, ci, cd,
                          ke);
@@ -478,6 +501,31 @@ __device__ __forceinline__ bool hat_row_unsafe(const DevProblem &pb, const doubl
     const int64_t pos = ro + i;
     return !hat_coef(c_pf[pb.iq[pos - 1]], c_pf[pb.dq[pos - 1]], c_pf[pb.iq[pos]], c_pf[pb.dq[pos]],
                      c_pf[pb.gq[pos]], c_1mpf[pb.gq[pos]], fac, ci, cd, ke);
+}
+
+// cI, cD and kE of read row i >= 1 (0-based), as the prologue of the sweep sets
+// them: the row above is read row i - 1, row m absorbs, later rows are zero.
+template <typename T>
+__device__ __forceinline__ void row_coef(const DevProblem &pb, const double *lin, int64_t ro, int m, int i, T &ci,
+                                         T &cd, T &ke)
+{
+    const int64_t pos = ro + min(i, m - 1), pa = ro + min(i - 1, m - 1);
+    T fac, c1, c2, k, dp;
+    if (lin || sizeof(T) == 8) {
+        const RowPar pp = load_row(pb, lin, pa, c_prob);
+        double f, d1, d2, dk;
+        hat_coef(load_row(pb, lin, pos, c_prob), pp, f, d1, d2, dk);
+        fac = (T)f, c1 = (T)d1, c2 = (T)d2, k = (T)dk, dp = (T)pp.d;
+    } else {
+        float f, d1, d2, dk;
+        hat_coef(c_pf[pb.iq[pa]], c_pf[pb.dq[pa]], c_pf[pb.iq[pos]], c_pf[pb.dq[pos]], c_pf[pb.gq[pos]],
+                 c_1mpf[pb.gq[pos]], f, d1, d2, dk);
+        fac = f, c1 = d1, c2 = d2, k = dk, dp = c_pf[pb.iq[pa]];
+    }
+    (void)fac;
+    ci = i < m ? c1 : i == m ? dp : (T)0;
+    cd = i < m ? c2 : (T)0;
+    ke = i < m ? k : (T)0;
 }
 
 // Start scale of the rescaled states: FP32 2^120 (as the plain states); FP64
@@ -510,26 +558,28 @@ struct RangeHat<double> {
 // same bit for bit.
 //
 // Windowed mode (W, reads longer than kMaxReadLen; P = 64, one pair per
-// wave): the launch covers rows A.window * kLongRows + 1 .. + kLongRows of
-// the pair.  Its top boundary row (the states of the row above, columns
-// 0..n) is read from the pair's slot `bnd_slot` of A.bnd, staged a chunk
-// at a time in LDS, and the window's last row is written back in place
-// (column j is read at step j-1 and written at step j+62).  Only the window
-// that holds the absorbing row m+1 produces the result.
+// wave): the wave sweeps the 64 K rows of window win.w of the pair against the
+// whole haplotype, while the waves of the windows above and below do theirs:
+// it follows the window above by what that window's progress count allows and
+// counts its own columns for the window below (see Boundary and k_long32).
+// Only the window that holds the absorbing row m+1 produces the result; its
+// FP32 sum is grouped as in windows of 1,024 rows with 16 rows per lane (a
+// lead, as in one-pair mode), so that it does not depend on K.
 template <typename T, int P, int K, bool W = false, bool V = false, bool H = sizeof(T) == 4, bool S = false>
 __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int rec_first,
-                          int nvalid, char *lds, int bnd_slot = 0, OneRec one = OneRec())
+                          int nvalid, char *lds, OneRec one = OneRec(), WinRec win = WinRec())
 {
     using C = Cfg<T, P, K>;
     static_assert(!S || (P == 64 && !W), "one-pair mode: 64 lanes, no windows");
-    static_assert(!W || (P == 64 && K * P == kLongRows), "windowed sweep: 64 lanes x kLongRows / 64 rows");
-    static_assert(sizeof(T) == 4 || !H || (!W && !V), "FP64 rescaled states: the binned sum-product sweep only");
+    static_assert(!W || P == 64, "windowed sweep: 64 lanes");
+    constexpr int WR = P * K;  // rows of a window
+    static_assert(sizeof(T) == 4 || !H || !V, "FP64 rescaled states: the sum-product sweep only");
     constexpr bool HAT = H;  // rescaled states (M, It, Dh)
     constexpr int kExp = HAT ? RangeHat<T>::kExp : Range<T>::kExp;
     const int lane = threadIdx.x;
     const int g = lane / P;
     const int t = lane % P;
-    const int r0 = W ? A.window * kLongRows : 0;  // first row of the window (0-based)
+    const int r0 = W ? win.w * WR : 0;  // first row of the window (0-based)
     bool gvalid = g < nvalid;
     const int ridx = gvalid ? (rec_idx_list ? rec_idx_list[rec_first + g] : rec_first + g) : 0;
 
@@ -538,7 +588,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         rec = PairRec{one.read, one.hap, one.out, one.n};
     else if (gvalid)
         rec = A.recs[ridx];
-    const int lead = S ? one.lead : 0;
+    int lead = S ? one.lead : 0;
     const DevProblem &pb = A.pb;
     const double *lin = A.lin_params;
     const int64_t ro = gvalid ? pb.read_offset[rec.read] : 0;
@@ -548,7 +598,11 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         gvalid = gvalid && m >= r0;
         if (!__builtin_amdgcn_readfirstlane((int)gvalid)) return kPairDone;
     }
-    const bool fin = !W || m < r0 + kLongRows;  // this window holds row m + 1
+    const bool fin = !W || m < r0 + WR;  // this window holds row m + 1
+    if constexpr (W && sizeof(T) == 4) {
+        const int last = m % kLongRows;
+        if (fin) lead = (last / 16 - (m - r0) / K) & 63;
+    }
     // Chain tile (FP32 binned sweep, records with n < 0): every group of the
     // tile sweeps its read against the same NH haplotypes h0, h0 + 1, ... of
     // its batch in turn, along their code stream; lane i holds the length of
@@ -573,8 +627,17 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     const int64_t ho = gvalid ? pb.hap_offset[rec.hap] : 0;
     const uint8_t *hap = chain ? A.chain_codes + ho + (int64_t)kChainSep * h0 : pb.hap_bases + ho;
     const int nring = chain ? Lc : n;  // columns of the ring's source
-    T *bnd = W ? (T *)A.bnd + (int64_t)bnd_slot * A.bnd_stride : nullptr;
-    T *top = (T *)(lds + C::E_BYTES + C::G * C::RING_BYTES);  // windowed: [3][64] staged boundary values
+    // windowed: the boundary row, its staging areas, the progress counts of the pair
+    Boundary<T, HAT> bnd;
+    char *wlds = lds + C::E_BYTES + C::G * C::RING_BYTES;
+    int32_t *prog = nullptr;
+    bool early = false;  // the next boundary values are on their way
+    int seen = 0;        // the window above's progress, as last known
+    int ahead_prog = 0;  // and as loaded at the start of the last chunk
+    if constexpr (W) {
+        bnd.open((T *)A.bnd + (int64_t)win.slot * A.bnd_stride, A.bnd_stride);
+        prog = A.progress + (int64_t)win.slot * A.windows + win.w;
+    }
 
     // the longest haplotype (chain) of the wave sets the number of steps
     int nmax = nring + lead;
@@ -781,7 +844,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     if constexpr (HAT) {
         if constexpr (W) {
             if (fin)
-                for (int i = 1 + t; i < r0; i += 64) bad = bad || hat_row_unsafe(pb, lin, ro, i);
+                for (int i = 1 + t; i < r0; i += 64) bad = bad || hat_row_unsafe<T>(pb, lin, ro, i);
         }
         const uint64_t bm = __ballot(bad);
         const uint64_t gm = P == 64 ? ~0ull : (((1ull << P) - 1) << (g * P));
@@ -806,13 +869,17 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     // row above the lane's first row at column j-1 = 0: the first lane's
     // row-0 boundary (the edge value) sits in It (rescaled) or Dt (plain)
     T Md = 0, Id = HAT ? edge : (T)0, Dd = HAT ? (T)0 : edge;
-    // rescaled states outside the windowed sweep (cell_step_hx): the first
-    // row's X at column 0, and the next lane's first-row coefficients
+    // rescaled states (cell_step_hx): the first row's X at column 0, and the
+    // next lane's first-row coefficients
     T Xd = edge, cib = 0, cdb = 0, keb = 0;
-    if constexpr (HAT && !W) {
+    if constexpr (HAT) {
         cib = from_next_lane(ci[0]);
         cdb = from_next_lane(cd[0]);
         keb = from_next_lane(ke[0]);
+    }
+    if constexpr (HAT && W) {
+        // the last lane's next row is the next window's first
+        if (t == 63 && !fin) row_coef<T>(pb, lin, ro, m, base + K, cib, cdb, keb);
     }
     // row-m sum (Viterbi: maximum).  Plain states: each chunk of CH steps
     // in T, then FP64.  Rescaled states: the absorbing row's Dh, flushed
@@ -902,26 +969,55 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             acc += (double)dm;
     };
 
+    // Windowed: before the steps s .. s + CH - 1 lane t stages column s + 1 + t -
+    // lead, which lane 0 takes at step s + t (in window 0 the row-0 boundary).  The
+    // columns were loaded a chunk earlier if the window above was that far
+    // ahead; else the wave waits for it.  (Exchanges every 16 or 32 steps let a
+    // window follow closer but cost more than that gains: 2.00 and 1.77 ms against
+    // 1.58 for the FP32 sweep of 53 pairs.)
+    const T first_edge = W && HAT ? __shfl(edge, 0) : (T)0;  // what lane 0 of window 0 takes
+    (void)first_edge;
+    auto take_columns = [&](int s) {
+        if (r0 == 0) {
+            bnd.none(HAT ? first_edge : (T)0);
+        } else if (!early) {
+            const int need = __builtin_amdgcn_readfirstlane(min(n, s + CH - lead)), j = s + 1 + t - lead;
+            // (ends: the window above was handed out before this one, to a
+            // wave that is running and waits for windows above only)
+            while ((seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(prog - 1, __ATOMIC_RELAXED,
+                                                                            __HIP_MEMORY_SCOPE_AGENT))) < need)
+                __builtin_amdgcn_s_sleep(1);
+            bnd.none(0);
+            if (j >= 1 && j <= n) bnd.fetch(j);
+        } else {
+            seen = __builtin_amdgcn_readfirstlane(ahead_prog);
+        }
+        bnd.stage(wlds, t);
+        early = false;
+        if (r0 > 0) {
+            if (seen >= __builtin_amdgcn_readfirstlane(min(n, s + 2 * CH - lead))) {
+                const int j = s + CH + 1 + t - lead;
+                early = true;
+                bnd.none(0);
+                if (j >= 1 && j <= n) bnd.fetch(j);
+            }
+            ahead_prog = __hip_atomic_load(prog - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    };
+    // after them, the columns handed on in these steps, and once they have
+    // arrived the count of columns that the window below may read
+    auto give_columns = [&](int s, int steps) {
+        const int j = s + t - (Boundary<T, HAT>::kBehind);
+        if (t < steps && j >= 1 && j <= n) bnd.write(wlds, t, j);
+        wait_vm0();
+        const int columns = s + CH < total ? s + CH - 1 - (Boundary<T, HAT>::kBehind) : 0x7fffffff;
+        if (t == 0) __hip_atomic_store(prog, columns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     for (int s0 = 0; s0 < total; s0 += CH) {
         uint32_t ahead[RingPer<P>::N];
         ring_load<P>(ahead, s0 / CH + 2, hap, nring, t, lead);
-        if constexpr (W) {
-            // lane t stages the boundary row at column s0 + 1 + t, which
-            // lane 0 takes at step s0 + t (zero in window 0: the row-0
-            // boundary comes from `edge`)
-            const int j = s0 + 1 + t;
-            T v0 = 0, v1 = 0, v2 = 0;
-            if (r0 > 0 && j <= n) {
-                const T *b = bnd + (int64_t)j * 3;
-                v0 = b[0];
-                v1 = b[1];
-                v2 = b[2];
-            }
-            top[t] = v0;
-            top[64 + t] = v1;
-            top[128 + t] = v2;
-            __syncthreads();
-        }
+        if constexpr (W) take_columns(s0);
         const uint16_t *hp = ring + ((s0 - t) & (4 * CH - 1));
         const int cnt = min(CH, total - s0);
         T la[C::KP], lb[C::KP];
@@ -940,15 +1036,14 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                 for (; u < stop; u += 2) {
                     load_lam<T, P, K>(lb, ebase_lane + hv[u + 1]);
                     if constexpr (W) {
-                        window_step_hat<T, K, V>(M, I, D, Md, Id, Dd, la, ci, cd, ke, ep, edge, top, u, t, fin, bnd,
-                                                 s0 + u, n);
+                        window_step_hx<T, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, wlds, u, t);
                         load_lam<T, P, K>(la, ebase_lane + hv[u + 2]);
-                        window_step_hat<T, K, V>(M, I, D, Md, Id, Dd, lb, ci, cd, ke, ep, edge, top, u + 1, t,
-                                                 fin, bnd, s0 + u + 1, n);
+                        window_step_hx<T, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, wlds, u + 1, t);
                     } else {
-                        cell_step_hx<T, P, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, edge, keep);
+                        T X, Y;
+                        cell_step_hx<T, P, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
                         load_lam<T, P, K>(la, ebase_lane + hv[u + 2]);
-                        cell_step_hx<T, P, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, edge, keep);
+                        cell_step_hx<T, P, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
                     }
                 }
                 if (u >= cnt) break;
@@ -961,11 +1056,10 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             for (int u = 0; u < cnt; u += 2) {
                 load_lam<T, P, K>(lb, ebase_lane + hp[u + 1]);
                 if constexpr (W) {
-                    window_step<T, K, V>(M, I, D, Md, Id, Dd, la, al, be, de, ep, zt, epI0, edge, part, top, u, t,
-                                         fin, bnd, s0 + u, n);
+                    window_step<T, K, V>(M, I, D, Md, Id, Dd, la, al, be, de, ep, zt, epI0, edge, part, wlds, u, t);
                     load_lam<T, P, K>(la, ebase_lane + hp[u + 2]);
-                    window_step<T, K, V>(M, I, D, Md, Id, Dd, lb, al, be, de, ep, zt, epI0, edge, part, top, u + 1,
-                                         t, fin, bnd, s0 + u + 1, n);
+                    window_step<T, K, V>(M, I, D, Md, Id, Dd, lb, al, be, de, ep, zt, epI0, edge, part, wlds, u + 1,
+                                         t);
                 } else {
                     cell_step<T, P, K, false, V>(M, I, D, Md, Id, Dd, la, al, be, de, ep, zt, epI0, edge, part);
                     load_lam<T, P, K>(la, ebase_lane + hp[u + 2]);
@@ -979,6 +1073,9 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         }
         ring_store<P>(ring, s0 / CH + 2, ahead, t, C::CODE_BYTES, chain);
         __syncthreads();
+        if constexpr (W) {
+            if (!fin) give_columns(s0, cnt);
+        }
     }
 
     // ---- epilogue: the lane that holds the row-m sum writes it ---------------
@@ -1047,6 +1144,10 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             if (!gbad && acc >= A.floor64 && acc <= 1.0e300) {
                 A.out_log10[rec.out] = lg;
                 if (A.out_status) A.out_status[rec.out] = 1;
+            } else if (W) {
+                const int slot = atomicAdd(&A.book->long_plain_count, 1);
+                A.long_plain_list[slot] = ridx;
+                atomicAdd(&A.book->rescue_passed, 1);
             } else {
                 const int q = kRescueClasses + cls;
                 const int slot = atomicAdd(&A.book->rescue_count[q], 1);
@@ -1060,7 +1161,10 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             A.out_log10[rec.out] = lg;
             const bool ok = !gbad && (acc >= A.threshold) && (acc <= 3.0e38);
             if (A.mode == kModeBinned && !ok) {
-                if (W) {
+                if (W && (gbad || V)) {
+                    const int slot = atomicAdd(&A.book->long_plain_count, 1);
+                    A.long_plain_list[slot] = ridx;
+                } else if (W) {
                     const int slot = atomicAdd(&A.book->long_rescue_count, 1);
                     A.long_rescue_list[slot] = ridx;
                 } else {
@@ -1194,34 +1298,53 @@ __global__ __launch_bounds__(64) void k_fwd64(SweepArgs A)
     }
 }
 
-// Windowed sweeps of reads longer than kMaxReadLen: one launch per window of
-// kLongRows rows, in window order on one stream.  FP32: the tiles of the
-// long bin (one pair each, slot = position in the bin); FP64: the long-pair
-// rescue queue (slot = queue position).  A pair whose rows end in an earlier
-// window is skipped.
-template <bool V>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_long32(SweepArgs A)
+// Windowed sweeps of reads longer than kMaxReadLen, all windows of all pairs
+// in one launch: a window of 64 K rows follows the one above it through the
+// boundary row, so the windows of a pair run as a pipeline.  (One launch per
+// window of 1,024 rows kept one wave per pair busy: 53 pairs of 1,100-8,000 x
+// 3,000-9,000 bases took 19.7 ms in FP32 and 39 ms in FP64.)  What bounds it with few pairs
+// is the length of one pair's pipeline, n steps plus about 250 for each window,
+// at the 5 clocks a wave takes for an instruction: few rows per lane make short
+// steps and more waves.  Plans with many long pairs take 16 rows per lane, which
+// costs fewer instructions per cell.
+//
+// Work items are (pair, window), a pair's windows in a row and the first window first,
+// handed out in that order by one counter: the window above an item was handed
+// out before it, to a wave that is running and itself waits only for windows
+// further up, so every wait ends, whatever part of the grid is resident.
+// FP32: the pairs of the long bin (slot = position in the bin); FP64: the
+// long-pair queues (slot = queue position).
+template <int K, bool V>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K > 8 ? 2 : 4))) void k_long32(SweepArgs A)
 {
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<float, 64, 16>::LDS_BYTES + 3 * 64 * sizeof(float)];
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<float, 64, K>::LDS_BYTES + Boundary<float, true>::LDS_BYTES];
     Book *bk = A.book;
-    const int rb = bk->bin_rec_begin[A.long_bin], re = bk->bin_rec_begin[A.long_bin + 1];
-    int tile = next_tile(&bk->long_counter[A.window]);
-    while (tile < re - rb) {
-        sweep_tile<float, 64, 16, true, V>(A, nullptr, rb + tile, 1, lds, tile);
-        tile = next_tile(&bk->long_counter[A.window]);
+    const int rb = bk->bin_rec_begin[A.long_bin];
+    const uint64_t items = (uint64_t)(bk->bin_rec_begin[A.long_bin + 1] - rb) * A.windows;
+    for (uint64_t item = next_item(&bk->long_next); item < items; item = next_item(&bk->long_next)) {
+        WinRec win;
+        win.slot = (int)(item / (uint32_t)A.windows);
+        win.w = (int)(item % (uint32_t)A.windows);
+        sweep_tile<float, 64, K, true, V>(A, nullptr, rb + win.slot, 1, lds, OneRec(), win);
     }
 }
 
-template <bool V>
+// H: the rescaled states over the long pairs that left the FP32 range, then the
+// plain ones over those with a row outside the rescaled states and what the
+// first pass leaves.
+template <bool V, bool H>
 __global__ __launch_bounds__(64) void k_long64(SweepArgs A)
 {
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, 16>::LDS_BYTES + 3 * 64 * sizeof(double)];
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, kLongK64>::LDS_BYTES + Boundary<double, H>::LDS_BYTES];
     Book *bk = A.book;
-    const int count = bk->long_rescue_count;
-    int item = next_tile(&bk->long64_counter[A.window]);
-    while (item < count) {
-        sweep_tile<double, 64, 16, true, V>(A, A.long_rescue_list, item, 1, lds, item);
-        item = next_tile(&bk->long64_counter[A.window]);
+    const uint64_t items = (uint64_t)(H ? bk->long_rescue_count : bk->long_plain_count) * A.windows;
+    unsigned long long *next = H ? &bk->long64_next : &bk->long_plain_next;
+    for (uint64_t item = next_item(next); item < items; item = next_item(next)) {
+        WinRec win;
+        win.slot = (int)(item / (uint32_t)A.windows);
+        win.w = (int)(item % (uint32_t)A.windows);
+        sweep_tile<double, 64, kLongK64, true, V, H>(A, H ? A.long_rescue_list : A.long_plain_list, win.slot, 1, lds,
+                                                     OneRec(), win);
     }
 }
 
@@ -1273,7 +1396,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3
     switch (K) {
 #define PH_ONE(k) \
     case k: \
-        if constexpr (LONG == (k > 4)) need = sweep_tile<float, 64, k, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one); \
+        if constexpr (LONG == (k > 4)) need = sweep_tile<float, 64, k, false, V, true, true>(A, nullptr, 0, 1, lds, one); \
         break;
         PH_ONE(1) PH_ONE(2) PH_ONE(3) PH_ONE(4) PH_ONE(5) PH_ONE(6) PH_ONE(7) PH_ONE(8)
         PH_ONE(9) PH_ONE(10) PH_ONE(11) PH_ONE(12) PH_ONE(13) PH_ONE(14) PH_ONE(15) PH_ONE(16)
@@ -1289,28 +1412,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3
         if (need == kPairHat64) {
             if constexpr (!LONG) {
                 if (m < 128)
-                    need = sweep_tile<double, 64, 2, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                    need = sweep_tile<double, 64, 2, false, V, true, true>(A, nullptr, 0, 1, lds, one);
                 else
-                    need = sweep_tile<double, 64, 4, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                    need = sweep_tile<double, 64, 4, false, V, true, true>(A, nullptr, 0, 1, lds, one);
             } else {
                 if (m < 512)
-                    need = sweep_tile<double, 64, 8, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                    need = sweep_tile<double, 64, 8, false, V, true, true>(A, nullptr, 0, 1, lds, one);
                 else
-                    need = sweep_tile<double, 64, 16, false, V, true, true>(A, nullptr, 0, 1, lds, 0, one);
+                    need = sweep_tile<double, 64, 16, false, V, true, true>(A, nullptr, 0, 1, lds, one);
             }
         }
     }
     if (need == kPairPlain64) {
         if constexpr (!LONG) {
             if (m < 128)
-                sweep_tile<double, 64, 2, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+                sweep_tile<double, 64, 2, false, V, false, true>(A, nullptr, 0, 1, lds, one);
             else
-                sweep_tile<double, 64, 4, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+                sweep_tile<double, 64, 4, false, V, false, true>(A, nullptr, 0, 1, lds, one);
         } else {
             if (m < 512)
-                sweep_tile<double, 64, 8, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+                sweep_tile<double, 64, 8, false, V, false, true>(A, nullptr, 0, 1, lds, one);
             else
-                sweep_tile<double, 64, 16, false, V, false, true>(A, nullptr, 0, 1, lds, 0, one);
+                sweep_tile<double, 64, 16, false, V, false, true>(A, nullptr, 0, 1, lds, one);
         }
     }
 }
@@ -1657,27 +1780,34 @@ hipError_t launch_fwd64(const SweepArgs &a, int cls, bool rescaled, int grid, hi
     return hipGetLastError();
 }
 
-hipError_t launch_long32(const SweepArgs &a, int window, int grid, hipStream_t s)
+hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s)
 {
     SweepArgs b = a;
-    b.window = window;
     b.mode = kModeBinned;
-    if (b.viterbi)
-        hipLaunchKernelGGL(k_long32<true>, dim3(grid), dim3(64), 0, s, b);
-    else
-        hipLaunchKernelGGL(k_long32<false>, dim3(grid), dim3(64), 0, s, b);
-    return hipGetLastError();
+#define PH_LL(k)                                                                       \
+    if (K == k) {                                                                      \
+        if (b.viterbi)                                                                 \
+            hipLaunchKernelGGL((k_long32<k, true>), dim3(grid), dim3(64), 0, s, b);    \
+        else                                                                           \
+            hipLaunchKernelGGL((k_long32<k, false>), dim3(grid), dim3(64), 0, s, b);   \
+        return hipGetLastError();                                                      \
+    }
+    PH_LL(kLongK32Few) PH_LL(kLongK32Many)
+#undef PH_LL
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_long64(const SweepArgs &a, int window, int grid, hipStream_t s)
+hipError_t launch_long64(const SweepArgs &a, bool rescaled, int grid, hipStream_t s)
 {
     SweepArgs b = a;
-    b.window = window;
     b.mode = kModeRescue;
+    if (b.viterbi && rescaled) return hipSuccess;  // the max-product score uses the plain queue only
     if (b.viterbi)
-        hipLaunchKernelGGL(k_long64<true>, dim3(grid), dim3(64), 0, s, b);
+        hipLaunchKernelGGL((k_long64<true, false>), dim3(grid), dim3(64), 0, s, b);
+    else if (rescaled)
+        hipLaunchKernelGGL((k_long64<false, true>), dim3(grid), dim3(64), 0, s, b);
     else
-        hipLaunchKernelGGL(k_long64<false>, dim3(grid), dim3(64), 0, s, b);
+        hipLaunchKernelGGL((k_long64<false, false>), dim3(grid), dim3(64), 0, s, b);
     return hipGetLastError();
 }
 
@@ -1741,8 +1871,12 @@ int plain32_blocks_per_cu(int K)
     return 1;
 }
 
-int long32_blocks_per_cu() { return occupancy((const void *)k_long32<false>); }
-int long64_blocks_per_cu() { return occupancy((const void *)k_long64<false>); }
+int long32_blocks_per_cu(int K)
+{
+    return K == kLongK32Few ? occupancy((const void *)k_long32<kLongK32Few, false>)
+                            : occupancy((const void *)k_long32<kLongK32Many, false>);
+}
+int long64_blocks_per_cu() { return occupancy((const void *)k_long64<false, false>); }
 
 int fwd64_blocks_per_cu(int cls, bool rescaled)
 {

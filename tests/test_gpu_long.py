@@ -178,3 +178,33 @@ def test_maximum_read_length():
     say(f"  log10 L {ref}, statuses {st}")
     assert np.all(np.isfinite(ref))
     check_against_oracle(prob, got, st, ref=ref)
+
+
+def test_many_long_pairs_equal_few():
+    """A plan with many long pairs sweeps windows of 16 rows per lane, one with
+    few windows of 4: the same FP32 results bit for bit (edges of both
+    window sizes, haplotypes shorter and longer than a chunk of columns)."""
+    rng = np.random.default_rng(31)
+    ref = rng.choice(list("ACGT"), size=2600)
+
+    def read(m):
+        r = ref[20:20 + m].copy()
+        err = rng.random(m) < 0.002
+        r[err] = rng.choice(list("ACGT"), size=int(err.sum()))
+        return "".join(r)
+
+    reads = [read(m) for m in (1024, 1025, 1279, 1280, 1281, 1535, 1536, 1999, 2047, 2048, 2049)]
+    haps = ["".join(ref[:n]) for n in (1, 63, 64, 65, 300, 1200, 2300, 2600)]
+    few = wl.from_strings([(reads, haps)], base_q=37)
+    many = wl.from_strings([(reads, haps)] + [(reads[:1], haps[:4])] * 160, base_q=37)
+    gf, sf = gpu_forward(few)
+    gm, sm = gpu_forward(many)
+    k = few.num_pairs
+    check_against_oracle(few, gf, sf)
+    assert np.array_equal(sf, sm[:k])
+    fp32 = sf == binding.PAIR_FP32
+    say(f"  {int(fp32.sum())} FP32 pairs of {k}, {many.num_pairs} pairs in the larger plan")
+    assert fp32.sum() >= 10
+    assert np.array_equal(gf[fp32], gm[:k][fp32])
+    ok = sf == binding.PAIR_FP64
+    assert np.abs(gf[ok] - gm[:k][ok]).max() <= 1e-9
