@@ -34,7 +34,7 @@
 // current block runs (global_load_lds), so the reload costs neither
 // registers nor a wait on memory.
 //
-// One persistent workgroup per slot takes a tile (G = 64/P pairs of one
+// One persistent workgroup per slot takes a tile (G = 64/P pairs of a
 // (P, K) configuration), runs the checkpointed forward into its own slice of
 // the workspace and then the reverse sweep; the slice is read back soon after
 // it is written, in reverse order, and waves in the forward phase (stores)
@@ -806,53 +806,83 @@ __device__ __forceinline__ void adj_emit_zero(const AdjArgs &A, const AdjPair<T,
 }
 
 // ---------------------------------------------------------------------------
-// FP32 pass: a persistent grid drains the tiles of one (P, K) configuration.
-// Groups past the end of the record list mirror group 0 and emit nothing.
+// FP32 pass: a persistent grid drains tiles, longest first.  Groups past the
+// end of a configuration's record list mirror group 0 and emit nothing.
+//
+// Two kernels: k_adj32 takes the tiles of all (P, K) configurations of a plan
+// in one launch, k_adj32_one those of one.  A launch per configuration ends
+// each of them with its own long tiles (a step of 32 lanes x 5 rows takes a wave
+// 0.4 us), one after the other: 60 regions with reads of 50-250 bases, six
+// configurations, 23,734 pairs, took 3.28 ms, in one launch 1.83 ms; 1,923
+// pairs with reads of 60-300 bases 1.79 ms of training step, 0.67 ms.  A kernel of its own has fewer
+// spills, and 3 waves per SIMD with up to 3 rows per lane: 0.71 against 0.74 ms on
+// 10,000 pairs of one configuration, 10.42 against 10.54 ms on 300 regions.
 // ---------------------------------------------------------------------------
-#ifndef PH_ADJ_WAVES
-#define PH_ADJ_WAVES 2
-#endif
 template <int P, int K>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 3 ? 3 : PH_ADJ_WAVES))) void k_adj32(AdjArgs A)
+__device__ __forceinline__ void adj_tile(const AdjArgs &A, const AdjRun &run, int tile, char *lds, float *ck)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int G = 64 / P;
     const int g = (int)threadIdx.x / P;
-    float *ck = A.ws + (int64_t)blockIdx.x * A.ws_stride;
-    for (int tile = next_tile(A.tile_next); tile < A.ntiles; tile = next_tile(A.tile_next)) {
-        const int first = tile * G, idx = first + g;
-        const bool valid = idx < A.nrec;
-        const AdjRec rec = A.recs[valid ? idx : first];
-        AdjPair<float, P, K> pr;
-        pr.init(A, lds, rec, __builtin_amdgcn_readlane(rec.S, 0), A.hs_bytes);
-        const double acc = adj_forward<float, P, K, kAdjC * kAdjR>(pr, ck);
-        // the absorbing row's lane holds the sum; a group with a beta below
-        // 2^-20 goes to the FP64 pass like a pair outside the FP32 range
-        const double Ls = __shfl(acc, g * P + min(pr.m / K, P - 1));
-        const uint64_t badm = __ballot(pr.bad);
-        const uint64_t gm = P == 64 ? ~0ull : (((1ull << P) - 1) << (g * P));
-        const bool good = (badm & gm) == 0 && (Ls >= A.threshold) && (Ls <= 3.0e38);
-        const int SB = good ? AdjRange<float>::kProd - ilogb(Ls) : 0;
-        AdjSums<float, K> sums;
-        adj_backward<float, P, K, kAdjC, kAdjR>(pr, ck, good ? ldexpf(1.f, SB) : 0.f, sums);
-        const double u = valid ? A.grad_in[rec.out] : 0.0;
-        if (!valid) {
-            // a group past the end of the records mirrors group 0: no output
-        } else if (u == 0.0) {  // a pair with u = 0 contributes nothing, whatever its range
-            adj_emit_zero<float, P, K>(A, pr);
-        } else {
-            if (good) {
-                adj_emit<float, P, K>(A, pr, u, 1.0 / ldexp(Ls, SB), sums);
-            } else if (pr.t == 0) {
-                // outside the FP32 range: queued for the FP64 pass, class
-                // K64 - 1 with K64 = ceil((m + 1) / 64) rows per lane
-                const int cls = (pr.m + 64) / 64 - 1;
-                const int slot = atomicAdd(&A.q64_count[cls], 1);
-                A.q64[(int64_t)cls * A.q64_stride + slot] = (int32_t)(A.rec_base + idx);
-            }
+    const int first = tile * G, idx = first + g;
+    const bool valid = idx < run.nrec;
+    const AdjRec rec = A.all_recs[run.rec_begin + (valid ? idx : first)];
+    AdjPair<float, P, K> pr;
+    pr.init(A, lds, rec, __builtin_amdgcn_readlane(rec.S, 0), run.hs_bytes);
+    const double acc = adj_forward<float, P, K, kAdjC * kAdjR>(pr, ck);
+    // the absorbing row's lane holds the sum; a group with a beta below
+    // 2^-20 goes to the FP64 pass like a pair outside the FP32 range
+    const double Ls = __shfl(acc, g * P + min(pr.m / K, P - 1));
+    const uint64_t badm = __ballot(pr.bad);
+    const uint64_t gm = P == 64 ? ~0ull : (((1ull << P) - 1) << (g * P));
+    const bool good = (badm & gm) == 0 && (Ls >= A.threshold) && (Ls <= 3.0e38);
+    const int SB = good ? AdjRange<float>::kProd - ilogb(Ls) : 0;
+    AdjSums<float, K> sums;
+    adj_backward<float, P, K, kAdjC, kAdjR>(pr, ck, good ? ldexpf(1.f, SB) : 0.f, sums);
+    const double u = valid ? A.grad_in[rec.out] : 0.0;
+    if (!valid) {
+        // a group past the end of the records mirrors group 0: no output
+    } else if (u == 0.0) {  // a pair with u = 0 contributes nothing, whatever its range
+        adj_emit_zero<float, P, K>(A, pr);
+    } else {
+        if (good) {
+            adj_emit<float, P, K>(A, pr, u, 1.0 / ldexp(Ls, SB), sums);
+        } else if (pr.t == 0) {
+            // outside the FP32 range: queued for the FP64 pass, class
+            // K64 - 1 with K64 = ceil((m + 1) / 64) rows per lane
+            const int cls = (pr.m + 64) / 64 - 1;
+            const int slot = atomicAdd(&A.q64_count[cls], 1);
+            A.q64[(int64_t)cls * A.q64_stride + slot] = (int32_t)(run.rec_begin + idx);
         }
-        __syncthreads();  // LDS tables are rebuilt for the next tile
     }
+    __syncthreads();  // LDS tables are rebuilt for the next tile
+}
+
+#define PH_ADJ_CONFIGS(X) X(32, 1) X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 5)
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_adj32(AdjArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *ck = A.ws + (int64_t)blockIdx.x * A.ws_stride;
+    for (int i = next_tile(A.tile_next); i < A.ntiles; i = next_tile(A.tile_next)) {
+        const AdjTile tl = A.tiles[i];
+        const AdjRun run = A.runs[tl.run];
+        switch (run.P * 8 + run.K) {
+#define PH_AT(p, k) \
+    case p * 8 + k: adj_tile<p, k>(A, run, tl.tile, lds, ck); break;
+            PH_ADJ_CONFIGS(PH_AT)
+#undef PH_AT
+        default: break;
+        }
+    }
+}
+
+template <int P, int K>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 3 ? 3 : 2))) void k_adj32_one(AdjArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *ck = A.ws + (int64_t)blockIdx.x * A.ws_stride;
+    const AdjRun run = A.runs[0];
+    for (int i = next_tile(A.tile_next); i < A.ntiles; i = next_tile(A.tile_next)) adj_tile<P, K>(A, run, i, lds, ck);
 }
 
 // ---------------------------------------------------------------------------
@@ -922,8 +952,6 @@ __global__ __launch_bounds__(64) void k_zero_i32(int32_t *p, int n)
     for (int i = threadIdx.x; i < n; i += 64) p[i] = 0;
 }
 
-#define PH_ADJ_CONFIGS(X) X(32, 1) X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(64, 3) X(64, 4) X(64, 5)
-
 bool adj_supported(int P, int K)
 {
 #define PH_AS(p, k) if (P == p && K == k) return true;
@@ -949,27 +977,23 @@ static int occupancy(const void *fn, size_t lds)
     return nb;
 }
 
-hipError_t launch_adj32(const AdjArgs &a, int P, int K, int grid, hipStream_t s)
+// P = 0: the tiles of all configurations
+static const void *adj32_kernel(int P, int K)
 {
-    const size_t lds = (size_t)adj_e_bytes(P, K) + (size_t)(64 / P) * a.hs_bytes + (size_t)adj_ck_lds_bytes(K);
-#define PH_LA(p, k)                                                              \
-    if (P == p && K == k) {                                                      \
-        hipLaunchKernelGGL((k_adj32<p, k>), dim3(grid), dim3(64), lds, s, a);   \
-        return hipGetLastError();                                                \
-    }
-    PH_ADJ_CONFIGS(PH_LA)
-#undef PH_LA
-    return hipErrorInvalidValue;
+#define PH_AK(p, k) if (P == p && K == k) return (const void *)k_adj32_one<p, k>;
+    PH_ADJ_CONFIGS(PH_AK)
+#undef PH_AK
+    return (const void *)k_adj32;
 }
 
-// resident workgroups per CU, from registers (LDS is small next to 160 KB)
-int adj32_blocks_per_cu(int P, int K)
+hipError_t launch_adj32(const AdjArgs &a, int P, int K, int lds, int grid, hipStream_t s)
 {
-#define PH_AO(p, k) if (P == p && K == k) return occupancy((const void *)k_adj32<p, k>, 0);
-    PH_ADJ_CONFIGS(PH_AO)
-#undef PH_AO
-    return 1;
+    AdjArgs args = a;
+    void *p[] = {&args};
+    return hipLaunchKernel(adj32_kernel(P, K), dim3(grid), dim3(64), p, (size_t)lds, s);
 }
+
+int adj32_blocks_per_cu(int P, int K, int lds) { return occupancy(adj32_kernel(P, K), (size_t)lds); }
 
 int adj64_blocks_per_cu(int K)
 {

@@ -89,6 +89,10 @@ hipError_t g_lut_adj_status = hipSuccess;
 constexpr int64_t kAdjWsFloats = (int64_t)1 << 30;    // 4 GiB, FP32 pass
 constexpr int64_t kAdjWs64Doubles = (int64_t)1 << 28;  // 2 GiB, FP64 pass
 
+// adjoint tiles of more steps are launched apart: up to here the LDS of 8
+// workgroups fits a CU
+constexpr int kAdjLongSteps = 1280;
+
 int rescue_class_of(int m) { return m < 128 ? 0 : m < 256 ? 1 : m < 512 ? 2 : 3; }
 
 // The library's own bin table, shortest reads first: 16 lanes x K rows
@@ -256,19 +260,20 @@ struct ph_plan {
     std::vector<int64_t> h_ro, h_ho, h_out_off;
 
     // adjoint: records grouped by (P, K) configuration, tiled G = 64/P at a
-    // time; one persistent launch per configuration, each workgroup with its
-    // own checkpoint slice
-    struct AdjRun {
-        int P, K;
-        int64_t rec_begin;
-        int32_t nrec, ntiles, hs_bytes, grid;
-        int64_t ws_stride;  // floats per workgroup
+    // time; persistent launches over the tiles of all configurations or of one,
+    // each workgroup with its own checkpoint slice
+    struct AdjLaunch {
+        std::vector<AdjRun> runs;
+        int64_t tile_begin = 0;
+        int32_t ntiles = 0, lds = 0, grid = 0;
+        int64_t ws_stride = 0;  // floats per workgroup
     };
     bool adj_built = false;
     ph_status adj_status = PH_OK;
     std::string adj_error;
-    std::vector<AdjRun> adj_runs;
+    std::vector<AdjLaunch> adj_launches;
     AdjRec *d_adj_recs = nullptr;
+    AdjTile *d_adj_tiles = nullptr;
     float *d_ws = nullptr;
     // gradients of reads with several pairs: per-pair rows, then a
     // fixed-order sum per read (no float atomics)
@@ -276,7 +281,7 @@ struct ph_plan {
     AdjRedRead *d_red = nullptr;
     int32_t n_red = 0;
     bool adj_zero = false;  // some read has no pair: its rows are zeroed
-    int32_t *d_adj_ctr = nullptr;  // [2][kAdj64Classes] FP64 queue lengths, cursors; then one cursor per run
+    int32_t *d_adj_ctr = nullptr;  // [2][kAdj64Classes] FP64 queue lengths, cursors; then the tile cursors
     // FP64 pass over the pairs the FP32 pass leaves out: queues per class,
     // [2][kAdj64Classes] counters (lengths, cursors), per-workgroup checkpoints
     int32_t *d_q64 = nullptr;
@@ -306,7 +311,7 @@ void free_plan(ph_plan *p)
     void *bufs[] = {p->d_out_offset, p->d_m2bin, p->d_bin_G, p->d_hist, p->d_recs, p->d_book, p->d_bad, p->d_rescue, p->d_lin,
                     p->d_book_img, p->d_chain_codes, p->d_one, p->d_one_rescued,
                     p->d_bnd32, p->d_bnd64, p->d_long_rescue, p->d_progress,
-                    p->d_adj_recs, p->d_ws, p->d_adj_ctr, p->d_q64, p->d_ws64, p->d_grad_pair, p->d_red};
+                    p->d_adj_recs, p->d_adj_tiles, p->d_ws, p->d_adj_ctr, p->d_q64, p->d_ws64, p->d_grad_pair, p->d_red};
     for (auto &e : p->ev_adj)
         if (e) (void)hipEventDestroy(e);
     for (void *b : bufs)
@@ -344,24 +349,30 @@ ph_status check_problem(const ph_plan *p, const ph_problem *pb)
     return PH_OK;
 }
 
-// Adjoint configuration of a read length: 32 lanes x K <= 5 rows, then 64 x K.
-bool adj_config(int m, int &P, int &K)
+// Adjoint configuration of a read length: 32 lanes x K <= 5 rows, then 64 x K;
+// wide: 64 lanes x K for every read.
+bool adj_config(int m, bool wide, int &P, int &K)
 {
-#ifdef PH_ADJ_WIDE
-    if (false) {
-#else
-    if (m + 1 <= 32 * 5) {
-#endif
+    if (!wide && m + 1 <= 32 * 5) {
         P = 32;
         K = (m + 1 + 31) / 32;
     } else if (m + 1 <= 64 * 5) {
         P = 64;
-        K = std::max(3, (m + 1 + 63) / 64);
+        K = (m + 1 + 63) / 64;
+        if (!wide) K = std::max(3, K);
     } else {
         return false;
     }
     return adj_supported(P, K);
 }
+
+// Calls of no more pairs than that take 64 lanes for each: every tile is under
+// way at once and shorter (1,923 pairs with reads of 60-300 bases: 0.65 ms
+// against 0.67; 23,734 pairs 2.16 against 1.83, 10,000 of 150 bases 1.00 against 0.74).
+constexpr int64_t kAdjWidePairs = 2048;
+// From this many tiles on the ends of the launches count less than what a
+// kernel for every configuration gains.
+constexpr int64_t kAdjApartTiles = 32768;
 
 ph_status build_adjoint(ph_plan *p)
 {
@@ -373,6 +384,7 @@ ph_status build_adjoint(ph_plan *p)
     };
     std::vector<Item> items;
     items.reserve((size_t)p->P);
+    const bool wide = p->P <= kAdjWidePairs;
     std::vector<AdjRedRead> red;
     int64_t grow = 0;  // per-pair gradient rows handed out so far
     std::vector<char> has_pair(p->nr, 0);
@@ -381,7 +393,7 @@ ph_status build_adjoint(ph_plan *p)
         for (int32_t r = p->h_rb[q]; r < p->h_rb[q + 1]; ++r) {
             const int m = (int)(p->h_ro[r + 1] - p->h_ro[r]);
             int P = 0, K = 0;
-            if (!adj_config(m, P, K)) {
+            if (!adj_config(m, wide, P, K)) {
                 p->adj_status = PH_ERR_UNSUPPORTED;
                 p->adj_error = "adjoint supports reads up to 319 bases";
                 return p->adj_status;
@@ -418,42 +430,89 @@ ph_status build_adjoint(ph_plan *p)
         return a.r.out < b.r.out;
     });
     std::vector<AdjRec> recs(items.size());
+    struct Timed {
+        int64_t time;
+        AdjTile tile;
+    };
+    // the configurations of tiles of up to kAdjLongSteps steps, and of longer
+    // ones, which need more LDS and longer slices
+    std::vector<Timed> tiles[2];
+    std::vector<AdjRun> runs[2];
+    std::vector<int> run_steps[2];  // most steps of each
     size_t i = 0;
-    int64_t ws_total = 0;
     while (i < items.size()) {
         const int P = items[i].P, K = items[i].K, G = 64 / P;
-        size_t end = i;
-        while (end < items.size() && items[end].P == P && items[end].K == K) ++end;
-        ph_plan::AdjRun run{P, K, (int64_t)i, (int32_t)(end - i), 0, 0, 0, 0};
-        int S_max = 0;
-        for (size_t a = i; a < end; a += G) {
-            const size_t b = std::min(end, a + G);
-            // the tile's first record has its longest haplotype
-            // steps: every lane reaches column n + 2 (the absorbing row of
-            // the rescaled states sums column n into column n + 2), rounded up
-            // to whole checkpoint intervals
+        // steps of the tile that starts at record a, whose haplotype is its
+        // longest: every lane reaches column n + 2 (the absorbing row of the
+        // rescaled states sums column n into column n + 2), rounded up to whole
+        // checkpoint intervals
+        auto steps = [&](size_t a) {
             constexpr int CK = kAdjC * kAdjR;  // steps per checkpoint
-            const int S = ((items[a].r.n + P + 1 + CK - 1) / CK) * CK;
-            for (size_t k = a; k < b; ++k) {
-                recs[k] = items[k].r;
-                recs[k].S = S;
+            return ((items[a].r.n + P + 1 + CK - 1) / CK) * CK;
+        };
+        const int S_max = steps(i);
+        const int group = S_max > kAdjLongSteps ? 1 : 0;
+        AdjRun run{P, K, 0, ((S_max + P + 2 + 15) / 16) * 16, (int64_t)i};  // one code byte per column
+        size_t a = i;
+        const size_t before = tiles[group].size();
+        while (a < items.size() && items[a].P == P && items[a].K == K && (steps(a) > kAdjLongSteps) == (group == 1)) {
+            size_t b = a;
+            const int S = steps(a);
+            for (; b < items.size() && b < a + G && items[b].P == P && items[b].K == K; ++b) {
+                recs[b] = items[b].r;
+                recs[b].S = S;
             }
-            run.ntiles += 1;
-            S_max = std::max(S_max, S);
+            // about 40 instructions per row and step, 25 for the step itself
+            tiles[group].push_back(
+                Timed{(int64_t)S * (40 * K + 25), {(int32_t)runs[group].size(), (int32_t)((a - i) / G)}});
+            a = b;
         }
-        run.hs_bytes = ((S_max + P + 2 + 15) / 16) * 16;  // one code byte per column
+        run.nrec = (int32_t)(a - i);
+        // (each configuration's tiles come longest first)
+        std::inplace_merge(tiles[group].begin(), tiles[group].begin() + before, tiles[group].end(),
+                           [](const Timed &x, const Timed &y) { return x.time > y.time; });
         if ((int64_t)adj_e_bytes(P, K) + (int64_t)G * run.hs_bytes + adj_ck_lds_bytes(K) > 64 * 1024) {
             p->adj_status = PH_ERR_UNSUPPORTED;
             p->adj_error = "haplotype too long for the adjoint sweep";
             return p->adj_status;
         }
-        run.ws_stride = ((int64_t)(S_max / (kAdjC * kAdjR)) * (3 * K + 3) * 64 + 63) / 64 * 64;
-        const int64_t resident = (int64_t)p->cus * adj32_blocks_per_cu(P, K);
-        run.grid = (int32_t)std::max<int64_t>(
-            1, std::min<int64_t>({(int64_t)run.ntiles, resident, kAdjWsFloats / run.ws_stride}));
-        ws_total = std::max(ws_total, (int64_t)run.grid * run.ws_stride);
-        p->adj_runs.push_back(run);
-        i = end;
+        runs[group].push_back(run);
+        run_steps[group].push_back(S_max);
+        i = a;
+    }
+    std::vector<AdjTile> order;
+    int64_t ws_total = 0;
+    // one launch over the runs first .. last of a group
+    auto add_launch = [&](int group, size_t first, size_t last, int64_t ntiles) {
+        ph_plan::AdjLaunch L;
+        for (size_t k = first; k <= last; ++k) {
+            const AdjRun &r = runs[group][k];
+            L.runs.push_back(r);
+            L.lds = std::max(L.lds, adj_e_bytes(r.P, r.K) + 64 / r.P * r.hs_bytes + adj_ck_lds_bytes(r.K));
+            L.ws_stride = std::max<int64_t>(
+                L.ws_stride, ((int64_t)(run_steps[group][k] / (kAdjC * kAdjR)) * (3 * r.K + 3) * 64 + 63) / 64 * 64);
+        }
+        L.tile_begin = (int64_t)order.size();
+        L.ntiles = (int32_t)ntiles;
+        const bool one = L.runs.size() == 1;
+        L.grid = (int32_t)std::max<int64_t>(
+            1, std::min<int64_t>(
+                   {ntiles, (int64_t)p->cus * adj32_blocks_per_cu(one ? L.runs[0].P : 0, L.runs[0].K, L.lds),
+                    kAdjWsFloats / L.ws_stride}));
+        ws_total = std::max(ws_total, (int64_t)L.grid * L.ws_stride);
+        p->adj_launches.push_back(L);
+    };
+    for (int g = 1; g >= 0; --g) {
+        if (tiles[g].empty()) continue;
+        if (runs[g].size() == 1 || (int64_t)tiles[g].size() >= kAdjApartTiles) {
+            for (size_t k = 0; k < runs[g].size(); ++k) {
+                const int G = 64 / runs[g][k].P;
+                add_launch(g, k, k, ((int64_t)runs[g][k].nrec + G - 1) / G);
+            }
+        } else {
+            add_launch(g, 0, runs[g].size() - 1, (int64_t)tiles[g].size());
+            for (const Timed &x : tiles[g]) order.push_back(x.tile);
+        }
     }
     // FP64 pass: sized for the longest haplotype and the largest class of
     // the plan; the grid is bounded by the workspace budget
@@ -482,13 +541,16 @@ ph_status build_adjoint(ph_plan *p)
     ph_status st;
     if ((st = dalloc(&p->d_adj_recs, recs.size()))) return p->adj_status = st;
     if ((st = dalloc(&p->d_ws, (size_t)std::max<int64_t>(ws_total, 1)))) return p->adj_status = st;
-    if ((st = dalloc(&p->d_adj_ctr, (size_t)2 * kAdj64Classes + p->adj_runs.size()))) return p->adj_status = st;
+    if ((st = dalloc(&p->d_adj_tiles, order.size()))) return p->adj_status = st;
+    if ((st = dalloc(&p->d_adj_ctr, (size_t)2 * kAdj64Classes + p->adj_launches.size()))) return p->adj_status = st;
     if ((st = dalloc(&p->d_q64, (size_t)kAdj64Classes * p->q64_stride))) return p->adj_status = st;
     if ((st = dalloc(&p->d_ws64, (size_t)p->grid64 * p->ws64_stride))) return p->adj_status = st;
     if ((st = dalloc(&p->d_grad_pair, (size_t)std::max<int64_t>(grow, 1) * 7))) return p->adj_status = st;
     if ((st = dalloc(&p->d_red, std::max<size_t>(red.size(), 1)))) return p->adj_status = st;
     p->n_red = (int32_t)red.size();
     hipError_t e = hipMemcpy(p->d_adj_recs, recs.data(), recs.size() * sizeof(AdjRec), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !order.empty())
+        e = hipMemcpy(p->d_adj_tiles, order.data(), order.size() * sizeof(AdjTile), hipMemcpyHostToDevice);
     if (e != hipSuccess) return p->adj_status = fail(PH_ERR_HIP, "hipMemcpy: %s", hipGetErrorString(e));
     if (!red.empty()) {
         e = hipMemcpy(p->d_red, red.data(), red.size() * sizeof(AdjRedRead), hipMemcpyHostToDevice);
@@ -684,27 +746,35 @@ double binned_ns(const ph_plan *p)
 std::vector<OneRec> one_list(const ph_plan *p, const std::vector<PairRec> &recs, const Book &img, const int64_t *ro,
                              const int64_t *ho)
 {
-    std::vector<OneRec> one;
-    one.reserve((size_t)p->P);
+    struct Item {
+        int64_t work;
+        OneRec r;
+    };
+    std::vector<Item> items;
+    items.reserve((size_t)p->P);
     const int nbins = (int)p->table.size();
     for (int b = 0; b < nbins; ++b) {
         const TuneEntry &e = p->table[nbins - 1 - b];
         const int chunk = ring_chunk(e.P);
         for (int32_t i = img.bin_rec_begin[b]; i < img.bin_rec_begin[b + 1]; ++i) {
             const PairRec &r = recs[(size_t)i];
-            const int m = (int)(ro[r.read + 1] - ro[r.read]);
-            const int shift = m / e.K - m / ((m + 64) / 64);
+            const int m = (int)(ro[r.read + 1] - ro[r.read]), K = (m + 64) / 64;
+            const int shift = m / e.K - m / K;
             int64_t pos = 0;
             for (int32_t k = 0; k < (r.n < 0 ? -r.n : 1); ++k) {
                 const int32_t n = (int32_t)(ho[r.hap + k + 1] - ho[r.hap + k]);
                 const int lead = (int)(((pos + shift) % chunk + chunk) % chunk);
-                one.push_back(OneRec{r.read, r.hap + k, r.out + k, n, lead, chunk});
+                items.push_back(Item{K * ((int64_t)n + 64), OneRec{r.read, r.hap + k, r.out + k, n, lead, chunk}});
                 pos += n + kChainSep;
             }
         }
     }
-    auto work = [&](const OneRec &r) { return (ro[r.read + 1] - ro[r.read] + 64) / 64 * ((int64_t)r.n + 64); };
-    std::stable_sort(one.begin(), one.end(), [&](const OneRec &a, const OneRec &b) { return work(a) > work(b); });
+    std::sort(items.begin(), items.end(), [](const Item &a, const Item &b) {
+        return a.work != b.work ? a.work > b.work : a.r.out < b.r.out;
+    });
+    std::vector<OneRec> one;
+    one.reserve(items.size());
+    for (const Item &i : items) one.push_back(i.r);
     return one;
 }
 
@@ -1144,15 +1214,14 @@ void drop_graphs(ph_plan *p)
 
 // The adjoint's launch sequence: parameter preparation, zeroing of the
 // counters (and of the gradient when some read has no pair; kernels, so that
-// the sequence can be captured), one persistent FP32 launch per (P, K)
-// configuration, the FP64 launches of the classes present, then the
+// the sequence can be captured), the persistent FP32 launches, the FP64 launches of the classes present, then the
 // fixed-order sum of the per-pair rows of reads with several pairs.
 ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_params,
                            const double *grad_log10L, float *grad_params, hipStream_t s)
 {
     if (log10_params) HIPCHK(launch_prep_params(log10_params, p->nread_bases, p->d_lin, s));
     if (p->adj_zero) HIPCHK(launch_zero_f32(grad_params, p->nread_bases * 7, s));
-    HIPCHK(launch_zero_i32(p->d_adj_ctr, 2 * kAdj64Classes + (int)p->adj_runs.size(), s));
+    HIPCHK(launch_zero_i32(p->d_adj_ctr, 2 * kAdj64Classes + (int)p->adj_launches.size(), s));
     AdjArgs a{};
     a.pb.read_offset = pb->read_offset;
     a.pb.read_bases = pb->read_bases;
@@ -1177,16 +1246,14 @@ ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_
     a.ws64_stride = p->ws64_stride;
     a.hs_bytes64 = p->hs_bytes64;
     a.floor64 = std::ldexp(1.0, -1000);
-    for (size_t k = 0; k < p->adj_runs.size(); ++k) {
-        const auto &run = p->adj_runs[k];
-        a.recs = p->d_adj_recs + run.rec_begin;
-        a.rec_base = run.rec_begin;
-        a.nrec = run.nrec;
-        a.ntiles = run.ntiles;
-        a.hs_bytes = run.hs_bytes;
+    for (size_t k = 0; k < p->adj_launches.size(); ++k) {
+        const ph_plan::AdjLaunch &L = p->adj_launches[k];
+        for (size_t r = 0; r < L.runs.size(); ++r) a.runs[r] = L.runs[r];
+        a.tiles = p->d_adj_tiles + L.tile_begin;
+        a.ntiles = L.ntiles;
         a.tile_next = p->d_adj_ctr + 2 * kAdj64Classes + k;
-        a.ws_stride = run.ws_stride;
-        HIPCHK(launch_adj32(a, run.P, run.K, run.grid, s));
+        a.ws_stride = L.ws_stride;
+        HIPCHK(launch_adj32(a, L.runs.size() == 1 ? L.runs[0].P : 0, L.runs[0].K, L.lds, L.grid, s));
     }
     // pairs out of the FP32 range, per class (a class whose queue stayed
     // empty exits at once)

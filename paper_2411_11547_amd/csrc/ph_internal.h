@@ -216,14 +216,27 @@ struct AdjRedRead {
     int32_t m, H;
 };
 
+// The records of one (P, K) configuration, and a tile of one: records
+// G tile .. G tile + G - 1 of its list.
+struct AdjRun {
+    int32_t P, K;
+    int32_t nrec;
+    int32_t hs_bytes;       // LDS bytes per group for the staged haplotype codes (one per column)
+    int64_t rec_begin;      // in all_recs
+};
+struct AdjTile {
+    int32_t run, tile;
+};
+constexpr int kAdjMaxRuns = 10;
+
 struct AdjArgs {
     DevProblem pb;
     const double *lin_params;
-    const AdjRec *recs;     // records of one (P, K) configuration
-    int64_t rec_base;       // index of recs[0] in all_recs
-    int32_t nrec, ntiles;
-    int32_t hs_bytes;       // LDS bytes per group for the staged haplotype codes (one per column)
-    int32_t *tile_next;     // work cursor of this launch
+    const AdjRec *all_recs;
+    AdjRun runs[kAdjMaxRuns];
+    const AdjTile *tiles;   // longest first (a launch of one configuration: its tiles in order)
+    int32_t ntiles;
+    int32_t *tile_next;     // work cursor
     float *ws;              // [grid][ws_stride] per-workgroup checkpoints
     int64_t ws_stride;
     const double *grad_in;  // per output pair
@@ -231,7 +244,6 @@ struct AdjArgs {
     float *grad_pair;       // per-pair rows x 7 (reads with several pairs)
     double threshold;       // FP32 scaled-sum range floor
     // FP64 pass over the pairs the FP32 pass left out
-    const AdjRec *all_recs;
     int32_t *q64;           // [kAdj64Classes][q64_stride] indices into all_recs
     int64_t q64_stride;
     int32_t *q64_count;     // [kAdj64Classes] queue lengths
@@ -245,9 +257,9 @@ struct AdjArgs {
 hipError_t upload_luts_adjoint();
 bool adj_supported(int P, int K);
 int adj_e_bytes(int P, int K);
-int adj_ck_lds_bytes(int K);  // FP32 pass: LDS checkpoint buffer per workgroup
-hipError_t launch_adj32(const AdjArgs &a, int P, int K, int grid, hipStream_t s);
-int adj32_blocks_per_cu(int P, int K);
+int adj_ck_lds_bytes(int K);  // FP32 pass: LDS checkpoint buffers per workgroup
+hipError_t launch_adj32(const AdjArgs &a, int P, int K, int lds, int grid, hipStream_t s);
+int adj32_blocks_per_cu(int P, int K, int lds);
 int adj64_blocks_per_cu(int K);
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 hipError_t launch_adj_reduce(const AdjRedRead *reads, int32_t nreads, const float *grad_pair, float *grad_out,
