@@ -102,10 +102,10 @@ typedef struct {
      * corresponds to log10 L of about -64.1.  <= 0 selects the default;
      * +inf sends every pair to the FP64 sweep. */
     double rescue_threshold;
-    int use_graph;         /* 1: capture the launch sequence of ph_forward_batch (three
-                              stage graphs) and of ph_backward_batch once per set of
-                              buffers and replay it (small plans, whose forward is one
-                              or two kernels, launch those directly) */
+    int use_graph;         /* 1: capture the FP32 launches of ph_forward_batch and the
+                              launch sequence of ph_backward_batch once per set of
+                              buffers and replay them (small plans, whose forward is
+                              one or two kernels, launch those directly) */
     int plain;             /* 1: one FP32 kernel sized for the longest read, pairs
                               in output order, no binning, no rescue (baseline) */
     int force_p;           /* 0 = tuned; else lanes per pair (4, 8, 16, 32 or 64) for every

@@ -6,15 +6,17 @@
 // III-B/III-C), counts the pairs of every length bin, and allocates the
 // device scratch.  A forward call then enqueues, on the caller's stream:
 //   1. (explicit-parameter mode) exponentiation of the log10 parameters;
-//   2. on-device binning: histogram, scan and scatter of the pairs by
-//      (length bin, haplotype length), Section III-A stage 3 / Section III-C;
+//   2. the call's preparation: the book of the work lists, which were built by
+//      (length bin, haplotype length) at plan creation (Section III-A stage 3 /
+//      Section III-C), and the chain code stream;
 //   3. one persistent FP32 sweep per non-empty bin, longest bin first, as
 //      parallel branches (Section III-C runs one kernel per index list on its
 //      own stream);
 //   4. the FP64 sweep over the pairs whose FP32 sum fell below the rescue
-//      threshold, one persistent launch per read-length class.
-// The whole sequence is captured once into a HIP graph and replayed while
-// the problem and output pointers stay the same.
+//      threshold, one persistent launch for reads of up to 255 bases and one per
+//      longer class.
+// The FP32 launches are captured once into a HIP graph and replayed while the
+// problem and output pointers stay the same.  Small calls are one launch (k_one).
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -94,6 +96,11 @@ constexpr int64_t kAdjWs64Doubles = (int64_t)1 << 28;  // 2 GiB, FP64 pass
 constexpr int kAdjLongSteps = 1280;
 
 int rescue_class_of(int m) { return m < 128 ? 0 : m < 256 ? 1 : m < 512 ? 2 : 3; }
+// pairs of the classes that a rescue launch sweeps
+int64_t rescue_pairs(const int64_t *class_pairs, int group)
+{
+    return group == 0 ? class_pairs[0] + class_pairs[1] : class_pairs[group + 1];
+}
 
 // The library's own bin table, shortest reads first: 16 lanes x K rows
 // (K = 1..16) up to 255 bases, then 64 lanes x K rows (K = 5..16).  Written
@@ -203,7 +210,7 @@ struct ph_plan {
     std::vector<TuneEntry> table;      // bin b = table[table.size()-1-b] (longest first)
     std::vector<int> bin_grid;         // persistent grid per bin (0 = empty)
     int64_t class_pairs[kRescueClasses] = {0, 0, 0, 0};
-    int rescue_grid[2][kRescueClasses] = {};  // [rescaled FP64, plain FP64] per class
+    int rescue_grid[kRescueGroups] = {};
     int plain_K = 0, plain_grid = 0;
     // reads longer than kMaxReadLen: one extra bin swept in windows
     int long_bin = -1, long_K = 0, windows = 0, windows64 = 0, long_grid = 0, long64_grid = 0;
@@ -247,9 +254,9 @@ struct ph_plan {
     hipEvent_t ev[kStageEvents] = {};
     bool stages_recorded = false;
 
-    // stage graphs of the forward ([0]) and of the Viterbi score ([1])
-    hipGraph_t graph[2][3] = {};
-    hipGraphExec_t exec[2][3] = {};
+    // FP32 stage graphs of the forward ([0]) and of the Viterbi score ([1])
+    hipGraph_t graph[2] = {};
+    hipGraphExec_t exec[2] = {};
     std::vector<const void *> graph_key[2];
 
     hipStream_t last_stream = nullptr;
@@ -301,11 +308,10 @@ namespace {
 void free_plan(ph_plan *p)
 {
     if (!p) return;
-    for (int v = 0; v < 2; ++v)
-        for (int i = 0; i < 3; ++i) {
-            if (p->exec[v][i]) (void)hipGraphExecDestroy(p->exec[v][i]);
-            if (p->graph[v][i]) (void)hipGraphDestroy(p->graph[v][i]);
-        }
+    for (int v = 0; v < 2; ++v) {
+        if (p->exec[v]) (void)hipGraphExecDestroy(p->exec[v]);
+        if (p->graph[v]) (void)hipGraphDestroy(p->graph[v]);
+    }
     if (p->adj_exec) (void)hipGraphExecDestroy(p->adj_exec);
     if (p->adj_graph) (void)hipGraphDestroy(p->adj_graph);
     void *bufs[] = {p->d_out_offset, p->d_m2bin, p->d_bin_G, p->d_hist, p->d_recs, p->d_book, p->d_bad, p->d_rescue, p->d_lin,
@@ -980,11 +986,8 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
             p->single_grid = (int)std::min<int64_t>(tiles, (int64_t)p->cus * fwd32_single_blocks_per_cu());
         }
     }
-    for (int c = 0; c < kRescueClasses; ++c)
-        if (p->class_pairs[c])
-            for (int v = 0; v < 2; ++v)
-                p->rescue_grid[v][c] =
-                    (int)std::min<int64_t>(p->class_pairs[c], (int64_t)p->cus * fwd64_blocks_per_cu(c, v == 0));
+    for (int g = 0; g < kRescueGroups; ++g)
+        p->rescue_grid[g] = (int)std::min<int64_t>(rescue_pairs(p->class_pairs, g), (int64_t)p->cus * rescue_blocks_per_cu(g));
     p->plain_K = (max_m + 1 + 63) / 64;
     if (p->plain_K < 1) p->plain_K = 1;
     p->plain_grid = (int)std::min<int64_t>(std::max<int64_t>(P, 1), (int64_t)p->cus * plain32_blocks_per_cu(p->plain_K));
@@ -1141,11 +1144,10 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
         } else {
             // the work lists come from plan creation: the book's bin ranges,
             // zero cursors, and the chain code stream of this call's haplotypes
-            HIPCHK(launch_book_copy(p->d_book, p->d_book_img, s));
+            HIPCHK(launch_prepare(p->d_book, p->d_book_img, pb->hap_offset, pb->hap_bases, p->nh,
+                                  p->chain_tiles ? p->d_chain_codes : nullptr, s));
             if (p->long_pairs)  // no window has written a column
                 HIPCHK(launch_zero_f32((float *)p->d_progress, p->long_pairs * (p->windows + 2 * p->windows64), s));
-            if (p->chain_tiles)
-                HIPCHK(launch_chain_codes(pb->hap_offset, pb->hap_bases, p->nh, p->d_chain_codes, s));
         }
     } else if (stage == 1) {
         if (p->opts.plain) {
@@ -1180,11 +1182,8 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
             }
         }
     } else if (!p->opts.plain) {
-        for (int c = 0; c < kRescueClasses; ++c)
-            if (p->rescue_grid[0][c]) HIPCHK(launch_fwd64(sa, c, true, p->rescue_grid[0][c], s));
-        // after every rescaled launch: the plain queues also hold what those passed on
-        for (int c = 0; c < kRescueClasses; ++c)
-            if (p->rescue_grid[1][c]) HIPCHK(launch_fwd64(sa, c, false, p->rescue_grid[1][c], s));
+        for (int g = 0; g < kRescueGroups; ++g)
+            if (p->rescue_grid[g]) HIPCHK(launch_rescue(sa, g, p->rescue_grid[g], s));
         if (p->long_pairs) {
             SweepArgs la = sa;
             la.bnd = p->d_bnd64;
@@ -1198,18 +1197,33 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
     return PH_OK;
 }
 
-void drop_graphs(ph_plan *p)
+// (a graph that may still run is waited for before it goes)
+void drop_stage_graph(ph_plan *p, int v)
 {
-    for (int v = 0; v < 2; ++v) {
-        for (int i = 0; i < 3; ++i) {
-            if (p->exec[v][i]) { (void)hipGraphExecDestroy(p->exec[v][i]); p->exec[v][i] = nullptr; }
-            if (p->graph[v][i]) { (void)hipGraphDestroy(p->graph[v][i]); p->graph[v][i] = nullptr; }
-        }
-        p->graph_key[v].clear();
+    if (p->exec[v]) {
+        if (p->stages_recorded) (void)hipEventSynchronize(p->ev[3]);
+        (void)hipGraphExecDestroy(p->exec[v]);
+        p->exec[v] = nullptr;
     }
-    if (p->adj_exec) { (void)hipGraphExecDestroy(p->adj_exec); p->adj_exec = nullptr; }
+    if (p->graph[v]) { (void)hipGraphDestroy(p->graph[v]); p->graph[v] = nullptr; }
+    p->graph_key[v].clear();
+}
+
+void drop_adjoint_graph(ph_plan *p)
+{
+    if (p->adj_exec) {
+        if (p->adj_recorded) (void)hipEventSynchronize(p->ev_adj[1]);
+        (void)hipGraphExecDestroy(p->adj_exec);
+        p->adj_exec = nullptr;
+    }
     if (p->adj_graph) { (void)hipGraphDestroy(p->adj_graph); p->adj_graph = nullptr; }
     p->adj_graph_key.clear();
+}
+
+void drop_graphs(ph_plan *p)
+{
+    for (int v = 0; v < 2; ++v) drop_stage_graph(p, v);
+    drop_adjoint_graph(p);
 }
 
 // The adjoint's launch sequence: parameter preparation, zeroing of the
@@ -1263,15 +1277,6 @@ ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_
     return PH_OK;
 }
 
-void drop_stage_graphs(ph_plan *p, int v)
-{
-    for (int i = 0; i < 3; ++i) {
-        if (p->exec[v][i]) { (void)hipGraphExecDestroy(p->exec[v][i]); p->exec[v][i] = nullptr; }
-        if (p->graph[v][i]) { (void)hipGraphDestroy(p->graph[v][i]); p->graph[v][i] = nullptr; }
-    }
-    p->graph_key[v].clear();
-}
-
 // The forward call and the Viterbi call: the same three stages, with the
 // sum (forward) or the maximum (Viterbi) in the sweeps, each mode with its
 // own stage graphs.
@@ -1316,47 +1321,43 @@ ph_status run_forward(ph_plan *p, const ph_problem *pb, const float *log10_param
         return PH_OK;
     }
 
-    // Each stage is captured into its own graph so that HIP events recorded on
-    // the caller's stream between the three launches time the stages.
-    if (p->opts.use_graph) {
+    // The FP32 stage (one launch per bin, on side streams) is captured into a
+    // graph; the stages before and after it are a launch or two.  HIP events
+    // recorded on the caller's stream around the stages time them.
+    const bool graph = p->opts.use_graph != 0;
+    if (graph) {
         std::vector<const void *> key = {pb->batch_read_begin, pb->batch_hap_begin, pb->read_offset,
                                          pb->read_bases, pb->base_qual, pb->ins_qual, pb->del_qual,
                                          pb->gcp_qual, pb->hap_offset, pb->hap_bases, log10_params,
                                          out_log10L, out_status};
-        if (!p->exec[v][0] || key != p->graph_key[v]) {
-            drop_stage_graphs(p, v);
-            for (int stage = 0; stage < 3; ++stage) {
-                HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
-                st = enqueue_stage(p, stage, pb, log10_params, out_log10L, out_status, p->cap, viterbi);
-                hipGraph_t g = nullptr;
-                hipError_t e = hipStreamEndCapture(p->cap, &g);
-                if (st != PH_OK) { if (g) (void)hipGraphDestroy(g); drop_stage_graphs(p, v); return st; }
-                if (e != hipSuccess) {
-                    drop_stage_graphs(p, v);
-                    return fail(PH_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-                }
-                p->graph[v][stage] = g;
-                e = hipGraphInstantiate(&p->exec[v][stage], g, nullptr, nullptr, 0);
-                if (e != hipSuccess) {
-                    drop_stage_graphs(p, v);
-                    return fail(PH_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-                }
+        if (!p->exec[v] || key != p->graph_key[v]) {
+            drop_stage_graph(p, v);
+            HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
+            st = enqueue_stage(p, 1, pb, log10_params, out_log10L, out_status, p->cap, viterbi);
+            hipGraph_t g = nullptr;
+            hipError_t e = hipStreamEndCapture(p->cap, &g);
+            if (st != PH_OK) { if (g) (void)hipGraphDestroy(g); return st; }
+            if (e != hipSuccess) return fail(PH_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+            p->graph[v] = g;
+            e = hipGraphInstantiate(&p->exec[v], g, nullptr, nullptr, 0);
+            if (e != hipSuccess) {
+                p->exec[v] = nullptr;
+                drop_stage_graph(p, v);
+                return fail(PH_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
             }
             p->graph_key[v] = key;
         }
-        for (int stage = 0; stage < 3; ++stage) {
-            HIPCHK(hipEventRecord(p->ev[stage], s));
-            HIPCHK(hipGraphLaunch(p->exec[v][stage], s));
-        }
-        HIPCHK(hipEventRecord(p->ev[3], s));
-    } else {
-        for (int stage = 0; stage < 3; ++stage) {
-            HIPCHK(hipEventRecord(p->ev[stage], s));
+    }
+    for (int stage = 0; stage < 3; ++stage) {
+        HIPCHK(hipEventRecord(p->ev[stage], s));
+        if (stage == 1 && graph) {
+            HIPCHK(hipGraphLaunch(p->exec[v], s));
+        } else {
             st = enqueue_stage(p, stage, pb, log10_params, out_log10L, out_status, s, viterbi);
             if (st != PH_OK) return st;
         }
-        HIPCHK(hipEventRecord(p->ev[3], s));
     }
+    HIPCHK(hipEventRecord(p->ev[3], s));
     p->last_stream = s;
     p->stages_recorded = true;
     p->forward_done = true;
@@ -1405,8 +1406,7 @@ ph_status ph_backward_batch(ph_plan *p, const ph_problem *pb, const float *log10
                                          pb->del_qual, pb->gcp_qual, pb->hap_offset, pb->hap_bases,
                                          log10_params, grad_log10L, grad_params};
         if (!p->adj_exec || key != p->adj_graph_key) {
-            if (p->adj_exec) { (void)hipGraphExecDestroy(p->adj_exec); p->adj_exec = nullptr; }
-            if (p->adj_graph) { (void)hipGraphDestroy(p->adj_graph); p->adj_graph = nullptr; }
+            drop_adjoint_graph(p);
             HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
             st = enqueue_backward(p, pb, log10_params, grad_log10L, grad_params, p->cap);
             hipGraph_t g = nullptr;
@@ -1495,8 +1495,8 @@ ph_status ph_plan_rescued(ph_plan *p, int64_t *count)
     HIPCHK(hipMemcpy(&lc, &p->d_book->long_rescue_count, sizeof(lc), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&lp, &p->d_book->long_plain_count, sizeof(lp), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&passed, &p->d_book->rescue_passed, sizeof(passed), hipMemcpyDeviceToHost));
-    // pairs of reads longer than 1023 bases (windowed FP64 sweeps), plus both
-    // sets of queues, less the pairs the rescaled sweeps passed on (counted twice)
+    // pairs of reads longer than 1023 bases (windowed FP64 sweeps), less those
+    // the rescaled sweep passed on (counted twice), plus both sets of queues
     *count = (int64_t)lc + lp - passed;
     for (int i = 0; i < kRescueQueues; ++i) *count += c[i];
     return PH_OK;
@@ -1547,7 +1547,7 @@ struct NaDevice {
     unsigned char *base = nullptr;  // device address of `scratch` on this device
     int cus = 0;
     int fwd32_cap[kMaxBins] = {};   // persistent grid cap of each built-in bin (bin order)
-    int fwd64_cap[2][kRescueClasses] = {};
+    int rescue_cap[kRescueGroups] = {};
 };
 
 std::mutex g_na_mu;
@@ -1571,8 +1571,7 @@ ph_status na_device_setup(int dev, NaDevice *&out)
             const TuneEntry &e = g_na_table[g_na_bins - 1 - b];
             d.fwd32_cap[b] = d.cus * std::max(1, fwd32_blocks_per_cu(e.P, e.K));
         }
-        for (int c = 0; c < kRescueClasses; ++c)
-            for (int v = 0; v < 2; ++v) d.fwd64_cap[v][c] = d.cus * std::max(1, fwd64_blocks_per_cu(c, v == 0));
+        for (int g = 0; g < kRescueGroups; ++g) d.rescue_cap[g] = d.cus * std::max(1, rescue_blocks_per_cu(g));
         d.base = (unsigned char *)ptr;
         d.ready = true;
     }
@@ -1764,10 +1763,10 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
         const int grid = (int)std::min<int64_t>((bin_pairs[b] + G - 1) / G, d->fwd32_cap[b]);
         HIPCHK(launch_fwd32(sa, sa.bins[b].P, sa.bins[b].K, b, grid, s));
     }
-    for (int v = 0; v < 2; ++v)
-        for (int c = 0; c < kRescueClasses; ++c)
-            if (class_pairs[c])
-                HIPCHK(launch_fwd64(sa, c, v == 0, (int)std::min<int64_t>(class_pairs[c], d->fwd64_cap[v][c]), s));
+    for (int g = 0; g < kRescueGroups; ++g) {
+        const int64_t pairs = rescue_pairs(class_pairs, g);
+        if (pairs) HIPCHK(launch_rescue(sa, g, (int)std::min<int64_t>(pairs, d->rescue_cap[g]), s));
+    }
     return PH_OK;
 }
 

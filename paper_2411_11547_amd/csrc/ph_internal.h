@@ -27,10 +27,11 @@ constexpr int kBuckets = 128;            // haplotype-length buckets per bin
 constexpr int kMaxKeys = kMaxBins * kBuckets;
 constexpr int kMaxReadLen = 1023;        // 64 lanes x 16 rows minus the absorbing row
 constexpr int kRescueClasses = 4;        // FP64 sweep: 64 lanes x {2, 4, 8, 16} rows
+constexpr int kRescueGroups = 3;         // its launches: classes 0 and 1, class 2, class 3
 // FP64 queues: [rescaled-state FP64 sweep | plain-state FP64 sweep] x class.
 // The FP32 sweep queues a pair that leaves the FP32 range into the first
-// set, one with a row outside the rescaled states into the second; the
-// rescaled FP64 sweep passes on what leaves its own range to the second.
+// set, one with a row outside the rescaled states into the second; what leaves
+// the rescaled FP64 sweep's own range is redone in plain states by its wave.
 constexpr int kRescueQueues = 2 * kRescueClasses;
 // Longer reads run in windows of 64 K rows (64 lanes x K rows): the window's
 // top boundary row comes from memory, its bottom row goes back there.  K by the number of long pairs
@@ -101,7 +102,7 @@ struct Book {
     int32_t bin_counter[kMaxBins];         // FP32 sweep work cursor of every bin
     int32_t rescue_count[kRescueQueues];   // FP64 queue lengths
     int32_t rescue_counter[kRescueQueues]; // FP64 sweep work cursors
-    int32_t rescue_passed;                 // pairs the rescaled FP64 sweep passed on
+    int32_t rescue_passed;                 // long pairs the rescaled FP64 sweep passed on
     int32_t long_rescue_count;             // FP64 queues of long pairs: rescaled states,
     int32_t long_plain_count;              // plain states
     unsigned long long long_next;          // work cursors of the windowed sweeps: FP32,
@@ -140,7 +141,6 @@ struct SweepArgs {
     int32_t num_bins;
     BinCfg bins[kMaxBins];
     int32_t mode;                // 0 binned FP32 + rescue, 1 plain FP32, 2 FP64 rescue
-    int32_t rescue_class;        // FP64: which queue
     int32_t plain_count;         // plain: number of records (tiles of 1 pair)
     // reads longer than kMaxReadLen: bin `long_bin`, swept in windows
     int32_t long_bin;            // -1 if none
@@ -279,7 +279,7 @@ hipError_t launch_plain32(const SweepArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_fwd32_single(const SweepArgs &a, int grid, hipStream_t s);
 int fwd32_single_blocks_per_cu();
 bool single_supported(int P, int K);
-hipError_t launch_fwd64(const SweepArgs &a, int cls, bool rescaled, int grid, hipStream_t s);
+hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s);
 hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_long64(const SweepArgs &a, bool rescaled, int grid, hipStream_t s);
 int long32_blocks_per_cu(int K);
@@ -289,15 +289,12 @@ hipError_t launch_prep_params(const float *lg, int64_t npos, double *lin, hipStr
 hipError_t launch_validate(const DevProblem &pb, int64_t nread_bases, int64_t nhap_bases,
                            int32_t *bad, hipStream_t s);
 hipError_t launch_reset_keys(int32_t *hist, int nkeys, Book *book, hipStream_t s);
-// chain work lists built at plan creation: the plan's book image (bin ranges,
-// zero cursors) into the book, and the chain code stream of the call's haplotypes
-hipError_t launch_book_copy(Book *book, const Book *image, hipStream_t s);
-hipError_t launch_chain_codes(const int64_t *hap_offset, const uint8_t *hap_bases, int32_t num_haps,
-                              uint8_t *codes, hipStream_t s);
+hipError_t launch_prepare(Book *book, const Book *image, const int64_t *hap_offset, const uint8_t *hap_bases,
+                          int32_t num_haps, uint8_t *codes, hipStream_t s);
 hipError_t launch_na_setup(const int32_t *rb, const int32_t *hb, int32_t nb, int64_t *out_offset,
                            int16_t *m2bin, int32_t *bin_G, const BinTable &t, hipStream_t s);
 int fwd32_blocks_per_cu(int P, int K);
-int fwd64_blocks_per_cu(int cls, bool rescaled);
+int rescue_blocks_per_cu(int group);
 int plain32_blocks_per_cu(int K);
 bool fwd32_supported(int P, int K);
 

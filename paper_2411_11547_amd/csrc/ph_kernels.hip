@@ -1139,19 +1139,14 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         const double lg = log10(acc) - (double)kExp * 0.30102999566398119521;
         const int cls = m < 128 ? 0 : m < 256 ? 1 : m < 512 ? 2 : 3;
         if (A.mode == kModeRescue && sizeof(T) == 8 && HAT) {
-            // rescaled FP64 sweep: inside its range (and no row outside the
-            // rescaled states), or passed on to the plain FP64 sweep
+            // rescaled FP64 sweep (of a long pair): inside its range (and no row
+            // outside the rescaled states), or passed on to the plain FP64 sweep
             if (!gbad && acc >= A.floor64 && acc <= 1.0e300) {
                 A.out_log10[rec.out] = lg;
                 if (A.out_status) A.out_status[rec.out] = 1;
-            } else if (W) {
+            } else {
                 const int slot = atomicAdd(&A.book->long_plain_count, 1);
                 A.long_plain_list[slot] = ridx;
-                atomicAdd(&A.book->rescue_passed, 1);
-            } else {
-                const int q = kRescueClasses + cls;
-                const int slot = atomicAdd(&A.book->rescue_count[q], 1);
-                A.rescue_list[q * A.rescue_stride + slot] = ridx;
                 atomicAdd(&A.book->rescue_passed, 1);
             }
         } else if (A.mode == kModeRescue) {
@@ -1281,21 +1276,46 @@ __global__ __launch_bounds__(64) void k_plain32(SweepArgs A)
     }
 }
 
-// FP64 sweep over one rescue queue (64 lanes per pair, K rows per lane):
-// H = true, the rescaled states over the pairs that left the FP32 range;
-// H = false, the plain states over the second set of queues.
-template <int K, bool V = false, bool H = false>
-__global__ __launch_bounds__(64) void k_fwd64(SweepArgs A)
+// FP64 sweep of one pair by its wave: the rescaled states over a pair that
+// left the FP32 range, the plain states over one with a row outside the
+// rescaled states (or the max-product score) and what the first sweep leaves.
+template <int K, bool V>
+__device__ __forceinline__ void rescue_pair(const SweepArgs &A, const OneRec &one, int need, char *lds)
 {
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, K>::LDS_BYTES];
-    const int q = (H ? 0 : kRescueClasses) + A.rescue_class;
-    const int count = A.book->rescue_count[q];
-    const int32_t *list = A.rescue_list + q * A.rescue_stride;
-    int tile = next_tile(&A.book->rescue_counter[q]);
-    while (tile < count) {
-        sweep_tile<double, 64, K, false, V, H>(A, list, tile, 1, lds);
-        tile = next_tile(&A.book->rescue_counter[q]);
+    if constexpr (!V) {
+        if (need == kPairHat64) need = sweep_tile<double, 64, K, false, V, true, true>(A, nullptr, 0, 1, lds, one);
     }
+    if (need == kPairPlain64) sweep_tile<double, 64, K, false, V, false, true>(A, nullptr, 0, 1, lds, one);
+}
+
+// FP64 sweeps over the rescue queues of the read-length classes C0 .. C1, both
+// queues of a class.  (A launch per class and queue cost 36 us each with the
+// queues empty: 0.19 ms of the mixed batch's call.  Classes of up to 255 bases
+// share the LDS and registers of 4 rows per lane, 12 waves per CU; the longer
+// classes' tables would take that from them.)
+template <int K, bool V>
+__device__ __forceinline__ void rescue_class(const SweepArgs &A, int cls, char *lds)
+{
+    Book *bk = A.book;
+    for (int plain = V ? 1 : 0; plain < 2; ++plain) {
+        const int q = plain * kRescueClasses + cls;
+        const int count = bk->rescue_count[q];
+        const int32_t *list = A.rescue_list + q * A.rescue_stride;
+        if (count == 0) continue;
+        for (int i = next_tile(&bk->rescue_counter[q]); i < count; i = next_tile(&bk->rescue_counter[q])) {
+            const PairRec r = A.recs[list[i]];
+            rescue_pair<K, V>(A, OneRec{r.read, r.hap, r.out, r.n, 0, 64}, plain ? kPairPlain64 : kPairHat64, lds);
+        }
+    }
+}
+
+template <int C0, int C1, bool V>
+__global__ __launch_bounds__(64) void k_rescue(SweepArgs A)
+{
+    constexpr int KHI = 2 << C1;
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES];
+    rescue_class<KHI, V>(A, C1, lds);
+    if constexpr (C0 < C1) rescue_class<(2 << C0), V>(A, C0, lds);
 }
 
 // Windowed sweeps of reads longer than kMaxReadLen, all windows of all pairs
@@ -1408,33 +1428,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3
     // FP64, in the rescue classes' configurations (2, 4, 8 or 16 rows per lane)
     one.lead = 0;
     one.flush = 64;
-    if constexpr (!V) {
-        if (need == kPairHat64) {
-            if constexpr (!LONG) {
-                if (m < 128)
-                    need = sweep_tile<double, 64, 2, false, V, true, true>(A, nullptr, 0, 1, lds, one);
-                else
-                    need = sweep_tile<double, 64, 4, false, V, true, true>(A, nullptr, 0, 1, lds, one);
-            } else {
-                if (m < 512)
-                    need = sweep_tile<double, 64, 8, false, V, true, true>(A, nullptr, 0, 1, lds, one);
-                else
-                    need = sweep_tile<double, 64, 16, false, V, true, true>(A, nullptr, 0, 1, lds, one);
-            }
-        }
-    }
-    if (need == kPairPlain64) {
-        if constexpr (!LONG) {
-            if (m < 128)
-                sweep_tile<double, 64, 2, false, V, false, true>(A, nullptr, 0, 1, lds, one);
-            else
-                sweep_tile<double, 64, 4, false, V, false, true>(A, nullptr, 0, 1, lds, one);
-        } else {
-            if (m < 512)
-                sweep_tile<double, 64, 8, false, V, false, true>(A, nullptr, 0, 1, lds, one);
-            else
-                sweep_tile<double, 64, 16, false, V, false, true>(A, nullptr, 0, 1, lds, one);
-        }
+    if constexpr (!LONG) {
+        if (m < 128)
+            rescue_pair<2, V>(A, one, need, lds);
+        else
+            rescue_pair<4, V>(A, one, need, lds);
+    } else {
+        if (m < 512)
+            rescue_pair<8, V>(A, one, need, lds);
+        else
+            rescue_pair<16, V>(A, one, need, lds);
     }
 }
 
@@ -1600,20 +1603,20 @@ __global__ __launch_bounds__(256) void k_bin_scatter(BinArgs a)
         if (key[j] >= 0) a.recs[base[key[j]] + rank[j]] = rec[j];
 }
 
-// The book of a plan whose work lists were built at plan creation: bin
-// ranges from the plan's image, every cursor and queue length zero.
-__global__ __launch_bounds__(256) void k_book_copy(Book *bk, const Book *img)
+// What a call of a plan whose work lists were built at its creation starts
+// with, one launch.  Block 0: the book, bin ranges from the plan's image, every
+// cursor and queue length zero.  All blocks: the chain code stream (codes not
+// NULL), haplotype h at hap_offset[h] + kChainSep h, its base codes (above 4:
+// N) followed by kChainSep PAD codes, one wave per haplotype.
+__global__ __launch_bounds__(256) void k_prepare(Book *bk, const Book *img, const int64_t *ho, const uint8_t *hb,
+                                                 int32_t nh, uint8_t *codes)
 {
-    int32_t *w = (int32_t *)bk;
-    const int32_t *r = (const int32_t *)img;
-    for (int i = threadIdx.x; i < (int)(sizeof(Book) / 4); i += 256) w[i] = r[i];
-}
-
-// Chain code stream: haplotype h at hap_offset[h] + kChainSep h, its base
-// codes (above 4: N) followed by kChainSep PAD codes.  One wave per haplotype.
-__global__ __launch_bounds__(256) void k_chain_codes(const int64_t *ho, const uint8_t *hb, int32_t nh,
-                                                     uint8_t *codes)
-{
+    if (blockIdx.x == 0) {
+        int32_t *w = (int32_t *)bk;
+        const int32_t *r = (const int32_t *)img;
+        for (int i = threadIdx.x; i < (int)(sizeof(Book) / 4); i += 256) w[i] = r[i];
+    }
+    if (!codes) return;
     const int lane = threadIdx.x & 63;
     for (int h = blockIdx.x * 4 + (threadIdx.x >> 6); h < nh; h += gridDim.x * 4) {
         const int64_t a = ho[h], n = ho[h + 1] - a;
@@ -1700,17 +1703,11 @@ hipError_t launch_reset_keys(int32_t *hist, int nkeys, Book *book, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_book_copy(Book *book, const Book *image, hipStream_t s)
+hipError_t launch_prepare(Book *book, const Book *image, const int64_t *hap_offset, const uint8_t *hap_bases,
+                          int32_t num_haps, uint8_t *codes, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_book_copy, dim3(1), dim3(256), 0, s, book, image);
-    return hipGetLastError();
-}
-
-hipError_t launch_chain_codes(const int64_t *hap_offset, const uint8_t *hap_bases, int32_t num_haps,
-                              uint8_t *codes, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_chain_codes, dim3(grid_for(num_haps, 4, 4096)), dim3(256), 0, s, hap_offset, hap_bases,
-                       num_haps, codes);
+    hipLaunchKernelGGL(k_prepare, dim3(codes ? grid_for(num_haps, 4, 4096) : 1), dim3(256), 0, s, book, image, hap_offset,
+                       hap_bases, num_haps, codes);
     return hipGetLastError();
 }
 
@@ -1755,29 +1752,21 @@ hipError_t launch_plain32(const SweepArgs &a_in, int K, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-static const int kRescueK[kRescueClasses] = {2, 4, 8, 16};
+static const void *rescue_kernel(int group, bool viterbi)
+{
+    if (viterbi)
+        return group == 0 ? (const void *)k_rescue<0, 1, true>
+               : group == 1 ? (const void *)k_rescue<2, 2, true> : (const void *)k_rescue<3, 3, true>;
+    return group == 0 ? (const void *)k_rescue<0, 1, false>
+           : group == 1 ? (const void *)k_rescue<2, 2, false> : (const void *)k_rescue<3, 3, false>;
+}
 
-hipError_t launch_fwd64(const SweepArgs &a, int cls, bool rescaled, int grid, hipStream_t s)
+hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s)
 {
     SweepArgs b = a;
-    b.rescue_class = cls;
     b.mode = kModeRescue;
-    if (b.viterbi && rescaled) return hipSuccess;  // the max-product score uses the plain queues only
-#define PH_L64(k)                                                                            \
-    case k:                                                                                  \
-        if (b.viterbi)                                                                       \
-            hipLaunchKernelGGL((k_fwd64<k, true, false>), dim3(grid), dim3(64), 0, s, b);    \
-        else if (rescaled)                                                                   \
-            hipLaunchKernelGGL((k_fwd64<k, false, true>), dim3(grid), dim3(64), 0, s, b);    \
-        else                                                                                 \
-            hipLaunchKernelGGL((k_fwd64<k, false, false>), dim3(grid), dim3(64), 0, s, b);   \
-        break;
-    switch (kRescueK[cls]) {
-        PH_L64(2) PH_L64(4) PH_L64(8) PH_L64(16)
-    default: return hipErrorInvalidValue;
-    }
-#undef PH_L64
-    return hipGetLastError();
+    void *p[] = {&b};
+    return hipLaunchKernel(rescue_kernel(group, b.viterbi != 0), dim3(grid), dim3(64), p, 0, s);
 }
 
 hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s)
@@ -1878,15 +1867,6 @@ int long32_blocks_per_cu(int K)
 }
 int long64_blocks_per_cu() { return occupancy((const void *)k_long64<false, false>); }
 
-int fwd64_blocks_per_cu(int cls, bool rescaled)
-{
-    switch (kRescueK[cls]) {
-    case 2: return occupancy(rescaled ? (const void *)k_fwd64<2, false, true> : (const void *)k_fwd64<2>);
-    case 4: return occupancy(rescaled ? (const void *)k_fwd64<4, false, true> : (const void *)k_fwd64<4>);
-    case 8: return occupancy(rescaled ? (const void *)k_fwd64<8, false, true> : (const void *)k_fwd64<8>);
-    case 16: return occupancy(rescaled ? (const void *)k_fwd64<16, false, true> : (const void *)k_fwd64<16>);
-    }
-    return 1;
-}
+int rescue_blocks_per_cu(int group) { return occupancy(rescue_kernel(group, false)); }
 
 }  // namespace ph
