@@ -53,6 +53,11 @@ ph_status fail(ph_status st, const char *fmt, ...)
 }  // namespace
 
 namespace ph {
+// ph_plan_create with the longest chain given (0: chosen, and returned), along
+// whose columns the FP32 row sums are grouped; out NULL: the choice alone,
+// without a GPU call
+ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts, int &chain_cols, ph_plan **out);
+
 // the calling thread's message for ph_last_error(), set by other host sources
 void set_last_error(const char *msg) { g_err = msg ? msg : ""; }
 }  // namespace ph
@@ -572,6 +577,63 @@ ph_status build_adjoint(ph_plan *p)
 // of 64,000 reads against 8 haplotypes, gets 2,048.)
 constexpr int64_t kChainMinTiles = 24576;
 
+// Haplotypes hb0 .. hb1 - 1 cut into runs for chains of at most max_cols
+// stream columns: f(first haplotype, haplotypes, columns) for each.
+template <typename F>
+void chain_segments(int32_t hb0, int32_t hb1, const int64_t *ho, int max_cols, F f)
+{
+    int32_t h0 = hb0, H = 0;
+    int64_t len = 0;
+    for (int32_t h = hb0; h < hb1; ++h) {
+        const int64_t n = ho[h + 1] - ho[h];
+        if (H && n >= kChainMinHap && H < kChainMaxHaps && len + kChainSep + n <= max_cols) {
+            H += 1;
+            len += kChainSep + n;
+        } else {
+            if (H) f(h0, H, len);
+            h0 = h;
+            H = 1;
+            len = n;
+        }
+    }
+    if (H) f(h0, H, len);
+}
+
+// Chain tiles of a plan with chains of at most max_cols columns.
+int64_t chain_tile_count(const ph_plan *p, int32_t nb, const int32_t *rb, const int32_t *hb, const int64_t *ro,
+                         const int64_t *ho, const std::vector<int16_t> &m2bin, int max_cols)
+{
+    const int nbins = (int)p->table.size();
+    int64_t tiles = 0;
+    std::vector<int32_t> cnt(nbins, 0);
+    for (int32_t q = 0; q < nb; ++q) {
+        int64_t chains = 0;
+        chain_segments(hb[q], hb[q + 1], ho, max_cols, [&](int32_t, int32_t H, int64_t) { chains += H >= 2; });
+        if (!chains) continue;
+        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) cnt[m2bin[std::min<int64_t>(ro[r + 1] - ro[r], kMaxReadLen + 1)]] += 1;
+        for (int b = 0; b < nbins; ++b) {
+            const int P = p->table[nbins - 1 - b].P;
+            if (b != p->long_bin && P >= 16) tiles += chains * (cnt[b] / (64 / P));
+            cnt[b] = 0;
+        }
+    }
+    return tiles;
+}
+
+// The longest chains that still leave kChainMinTiles chain tiles (or 1,024 columns).
+int choose_chain_cols(const ph_plan *p, int32_t nb, const int32_t *rb, const int32_t *hb, const int64_t *ro,
+                      const int64_t *ho, const std::vector<int16_t> &m2bin)
+{
+    const bool chains_ok = kChains && 2 * p->P < ((int64_t)1 << 31);
+    int cols = kChainMaxCols;
+    while (chains_ok && cols > 1024) {
+        const int64_t n = chain_tile_count(p, nb, rb, hb, ro, ho, m2bin, cols);
+        if (n == 0 || n >= kChainMinTiles) break;
+        cols /= 2;
+    }
+    return cols;
+}
+
 // Which way a call goes: one launch of one-pair tiles (k_one), or the binned
 // launches.  One-pair tiles fill the GPU at 5.7e12 cells a second (rows padded
 // to 64, 64 columns of fill), the binned sweeps compute 7.3e12 cells, but
@@ -590,15 +652,16 @@ double tile_ns(int64_t cols, int P, int K) { return 2.0 * (double)(cols + P + 2)
 // pairs, longest haplotype first.  A chain tile holds G = 64/P reads of one
 // batch and length bin, each against the same run of the batch's
 // haplotypes (at most kChainMaxHaps haplotypes and max_cols stream
-// columns, every haplotype after the first at least kChainMinHap long);
+// columns, every haplotype after the first at least kChainMinHap long), in
+// pieces of at most piece_cols columns, each with the lead that keeps the
+// groups of the row sums where the whole chain has them;
 // bins of fewer than 16 lanes and the reads of a batch's bin that do not
 // fill a tile take single pairs.  A haplotype-length split applies to
 // single pairs only (sending chains whose stream reaches the split length
 // to the split's bin was slower on the mixed batch).
 bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho,
                  const std::vector<int64_t> &out_off, const std::vector<int16_t> &m2bin,
-                 const std::vector<int16_t> &split, int max_cols, std::vector<PairRec> &recs, Book &img,
-                 int64_t &chain_tile_count)
+                 const std::vector<int16_t> &split, int max_cols, int piece_cols, std::vector<PairRec> &recs, Book &img)
 {
     const int nbins = (int)p->table.size();
     auto binP = [&](int b) { return p->table[nbins - 1 - b].P; };
@@ -626,16 +689,8 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
         if (H == 0) continue;
         // runs of haplotypes for chains
         segs.clear();
-        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) {
-            const int64_t n = ho[h + 1] - ho[h];
-            if (!segs.empty() && n >= kChainMinHap && segs.back().H < kChainMaxHaps &&
-                segs.back().len + kChainSep + n <= max_cols) {
-                segs.back().H += 1;
-                segs.back().len += kChainSep + n;
-            } else {
-                segs.push_back(Seg{h, 1, n});
-            }
-        }
+        chain_segments(hb[q], hb[q + 1], ho, max_cols,
+                       [&](int32_t h0, int32_t n, int64_t len) { segs.push_back(Seg{h0, n, len}); });
         by_bin.clear();
         for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
             const int64_t m = ro[r + 1] - ro[r];
@@ -662,12 +717,24 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
             for (const Seg &sg : segs) {
                 const bool chain = chains_ok && b != p->long_bin && sg.H >= 2 && binP(b) >= 16;
                 const int nt = chain ? cnt / G : 0;
-                for (int t = 0; t < nt; ++t) {
-                    chain_tiles[b].push_back(Tile{sg.len, (int64_t)pool.size(), G});
-                    for (int g = 0; g < G; ++g) {
-                        const int32_t r = by_bin[i + (size_t)t * G + g].second;
-                        pool.push_back(PairRec{r, sg.h0, out_of(r, sg.h0), -sg.H});
+                // the chain in pieces of at most piece_cols columns
+                for (int32_t h = sg.h0; nt && h < sg.h0 + sg.H;) {
+                    const int64_t pos = ho[h] - ho[sg.h0] + (int64_t)kChainSep * (h - sg.h0);  // in the chain
+                    int64_t len = ho[h + 1] - ho[h];
+                    int32_t e2 = h + 1;
+                    while (e2 < sg.h0 + sg.H && len + kChainSep + ho[e2 + 1] - ho[e2] <= piece_cols) {
+                        len += kChainSep + ho[e2 + 1] - ho[e2];
+                        ++e2;
                     }
+                    const int32_t n = chain_n(e2 - h, (int)(pos % ring_chunk(binP(b))));
+                    for (int t = 0; t < nt; ++t) {
+                        chain_tiles[b].push_back(Tile{len, (int64_t)pool.size(), G});
+                        for (int g = 0; g < G; ++g) {
+                            const int32_t r = by_bin[i + (size_t)t * G + g].second;
+                            pool.push_back(PairRec{r, h, out_of(r, h), n});
+                        }
+                    }
+                    h = e2;
                 }
                 for (size_t k = i + (size_t)nt * G; k < e; ++k)
                     for (int32_t h = sg.h0; h < sg.h0 + sg.H; ++h) add_single(b, by_bin[k].second, h);
@@ -681,7 +748,6 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     p->bin_tiles.assign(nbins, 0);
     p->bin_cols.assign(nbins, 0);
     p->chain_tiles = false;
-    chain_tile_count = 0;
     int64_t tiles = 0;
     for (int b = 0; b < nbins; ++b) {
         std::stable_sort(chain_tiles[b].begin(), chain_tiles[b].end(), longest_first);
@@ -696,7 +762,6 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
             if (!l->empty()) p->bin_cols[b] = std::max(p->bin_cols[b], l->front().len);
         p->bin_tiles[b] = (int64_t)chain_tiles[b].size() + ((int64_t)singles[b].size() + G - 1) / G;
         p->chain_tiles = p->chain_tiles || !chain_tiles[b].empty();
-        chain_tile_count += (int64_t)chain_tiles[b].size();
         tiles += p->bin_tiles[b];
     }
     img.bin_rec_begin[nbins] = (int32_t)recs.size();
@@ -705,7 +770,7 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     // every pair exactly once
     std::vector<uint8_t> seen((size_t)p->P, 0);
     for (const PairRec &r : recs) {
-        const int32_t cnt = r.n < 0 ? -r.n : 1;
+        const int32_t cnt = r.n < 0 ? chain_haps(r.n) : 1;
         for (int32_t k = 0; k < cnt; ++k) {
             const int64_t o = (int64_t)r.out + k;
             if (o < 0 || o >= p->P || seen[(size_t)o]) return false;
@@ -766,8 +831,8 @@ std::vector<OneRec> one_list(const ph_plan *p, const std::vector<PairRec> &recs,
             const PairRec &r = recs[(size_t)i];
             const int m = (int)(ro[r.read + 1] - ro[r.read]), K = (m + 64) / 64;
             const int shift = m / e.K - m / K;
-            int64_t pos = 0;
-            for (int32_t k = 0; k < (r.n < 0 ? -r.n : 1); ++k) {
+            int64_t pos = r.n < 0 ? chain_lead(r.n) : 0;
+            for (int32_t k = 0; k < (r.n < 0 ? chain_haps(r.n) : 1); ++k) {
                 const int32_t n = (int32_t)(ho[r.hap + k + 1] - ho[r.hap + k]);
                 const int lead = (int)(((pos + shift) % chunk + chunk) % chunk);
                 items.push_back(Item{K * ((int64_t)n + 64), OneRec{r.read, r.hap + k, r.out + k, n, lead, chunk}});
@@ -805,6 +870,16 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
     g_err.clear();
     if (!shape || !out) return fail(PH_ERR_INVALID, "shape or out is NULL");
     *out = nullptr;
+    int chain_cols = 0;
+    return plan_create(shape, opts_in, chain_cols, out);
+}
+
+}  // extern "C"
+
+namespace ph {
+
+ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &chain_cols, ph_plan **out)
+{
     ph_plan_opts opts;
     if (opts_in) opts = *opts_in; else ph_plan_opts_default(&opts);
     const int32_t nb = shape->num_batches, nr = shape->num_reads, nh = shape->num_haps;
@@ -924,14 +999,17 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
     }
     Book img{};
     std::vector<PairRec> recs;
+    if (opts.plain && !out) return PH_OK;
     if (!opts.plain) {
-        // the longest chains that still leave kChainMinTiles chain tiles (or 1,024 columns)
-        for (int cols = kChainMaxCols;; cols /= 2) {
-            int64_t nchain = 0;
-            if (!build_lists(p.get(), rb, hb, ro, ho, out_off, m2bin, split, cols, recs, img, nchain))
-                return fail(PH_ERR_INVALID, "internal: the work lists do not cover every pair once");
-            if (nchain == 0 || nchain >= kChainMinTiles || cols <= 1024) break;
-        }
+        const int own_cols = choose_chain_cols(p.get(), nb, rb, hb, ro, ho, m2bin);
+        if (!chain_cols) chain_cols = own_cols;
+        if (!out) return PH_OK;
+        // chains longer than the plan's own choice are swept in pieces of that
+        // length (a part of 1e10 cells of a batch of 5.2e10, on its own: tiles of
+        // 4,096 columns leave its bins uneven, 10.2 against 9.1 ms for the batch)
+        const int piece = std::min(own_cols, chain_cols);
+        if (!build_lists(p.get(), rb, hb, ro, ho, out_off, m2bin, split, chain_cols, piece, recs, img))
+            return fail(PH_ERR_INVALID, "internal: the work lists do not cover every pair once");
     }
     // small plans (reads of up to 1,023 bases, no option that names a launch)
     std::vector<OneRec> one;
@@ -1051,6 +1129,10 @@ ph_status ph_plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, ph_
     *out = p.release();
     return PH_OK;
 }
+
+}  // namespace ph
+
+extern "C" {
 
 ph_status ph_plan_info(const ph_plan *p, int64_t *num_pairs, int64_t *num_cells, int32_t *max_read_len,
                        int32_t *max_hap_len)

@@ -42,11 +42,14 @@ constexpr int kMaxLongReadLen = 65535;
 
 // One read/haplotype pair: indices into the problem and into the output.
 // In a chain tile of the FP32 sweep (n < 0) a record stands for the read
-// against the -n haplotypes hap, hap + 1, ... of its batch, whose outputs are
-// out, out + 1, ...
+// against the haplotypes hap, hap + 1, ... of its batch (chain_haps of them),
+// whose outputs are out, out + 1, ..., after chain_lead PAD columns.
 struct PairRec {
     int32_t read, hap, out, n;
 };
+constexpr int32_t chain_n(int haps, int lead) { return -(haps | lead << 8); }
+constexpr int chain_haps(int32_t n) { return -n & 255; }
+constexpr int chain_lead(int32_t n) { return -n >> 8; }
 
 // Haplotype chains.  A lane group of 16 or more lanes sweeps its read against
 // several haplotypes of its batch one after the other, so that the wavefront

@@ -607,6 +607,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     // tile sweeps its read against the same NH haplotypes h0, h0 + 1, ... of
     // its batch in turn, along their code stream; lane i holds the length of
     // haplotype h0 + i, Lc is the stream's length up to the last haplotype's end.
+    // A tile that is a later piece of a chain starts with a lead of PAD columns,
+    // which puts its flushes where the whole chain has them.
     constexpr bool CHN = kChains && HAT && !W && !S && sizeof(T) == 4;
     bool chain = false;
     int NH = 1, h0 = 0, nvec = 0, Lc = 0;
@@ -614,7 +616,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         const int r0n = __builtin_amdgcn_readfirstlane(rec.n);
         chain = r0n < 0;
         if (chain) {
-            NH = -r0n;
+            NH = chain_haps(r0n);
+            lead = chain_lead(r0n);
             h0 = __builtin_amdgcn_readfirstlane(rec.hap);
             if (lane < NH) nvec = (int)(pb.hap_offset[h0 + lane + 1] - pb.hap_offset[h0 + lane]);
             int sum = nvec;
@@ -913,7 +916,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     int kc = 0, cpos = 0, nk = 0, bA = 0, rs_next = 0x7fffffff;
     if (chain && NH > 1) {
         nk = __builtin_amdgcn_readlane(nvec, 0);
-        bA = nk + 2;
+        cpos = lead;
+        bA = cpos + nk + 2;
         rs_next = (bA + CW - 1) & ~1;
     }
     auto chain_clear = [&]() {

@@ -11,7 +11,8 @@
 // first bins' sweeps) overlap the tail of subset k (44.3 -> 41.4 ms per call
 // on the mixed batch in 9 subsets).  Subsets of up to 6e10 cells by default:
 // with haplotype chains, whose tiles are longer, the mixed batch runs in 4
-// subsets at 36.4-36.9 ms per call against 39.1-39.4 in 9.  When every subset's inputs and outputs
+// subsets at 36.4-36.9 ms per call against 39.1-39.4 in 9 (35.8 with the first
+// of the 4 in halves, kMinCutCells).  When every subset's inputs and outputs
 // together take at most a
 // quarter of the free device memory (or the caller asks for as many buffer
 // sets as there are subsets), each subset gets its own buffer set and
@@ -25,7 +26,8 @@
 // hardware queues drain, so with two sets the H2D of a subset cannot start
 // before the previous subset's sweeps end.)
 //
-// This file is a client of the public plan API plus the HIP runtime.
+// This file is a client of the public plan API (and of the plan's chain length)
+// plus the HIP runtime.
 #include <hip/hip_runtime.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -38,7 +40,9 @@
 #include "ph.h"
 
 namespace ph {
-void set_last_error(const char *msg);  // ph_api.cpp: the message of ph_last_error()
+// ph_api.cpp: the message of ph_last_error(), and a plan with its longest chain given
+void set_last_error(const char *msg);
+ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts, int &chain_cols, ph_plan **out);
 }
 
 #ifndef PH_PIPE_COMP_STREAMS
@@ -49,6 +53,12 @@ namespace {
 
 constexpr int kCompStreams = PH_PIPE_COMP_STREAMS;  // subsets alternate between these
 constexpr int64_t kDefaultSubsetCells = 60000000000LL;  // cells per subset unless given
+// Unless subsets are given, a first subset of at least that many cells is cut
+// into halves (48,000 regions, 5.2e10 cells, 98 MB, ms per call: whole 10.0,
+// halves 9.1, thirds 9.1, 1 : 2 : 2 9.1, quarters 9.2, sixths 10.3; 2.5e10 cells
+// 5.15 whole, 4.89 in halves; smaller ones lose as much in the ends of their
+// sweeps as they gain).
+constexpr int64_t kMinCutCells = 15000000000LL;
 
 ph_status pfail(ph_status st, const char *fmt, ...)
 {
@@ -76,6 +86,7 @@ struct Subset {
     int64_t hb0, hb1;       // haplotype bases
     int64_t out0, pairs;    // output range
     int64_t cells;
+    int chain_cols;         // longest chain of its plan (0: the plan's own choice)
     std::vector<int32_t> bra, bha;
     std::vector<int64_t> ro, ho;
     int32_t *d_bra = nullptr, *d_bha = nullptr;
@@ -142,6 +153,24 @@ ph_status palloc(T **p, int64_t count)
     return PH_OK;
 }
 
+// The chain length that a plan over the batches b0 .. b1 - 1 of a shape takes.
+ph_status chain_cols_of(const ph_shape *shape, const ph_plan_opts *opts, int32_t b0, int32_t b1, int &cols)
+{
+    const int32_t r0 = shape->batch_read_begin[b0], r1 = shape->batch_read_begin[b1];
+    const int32_t h0 = shape->batch_hap_begin[b0], h1 = shape->batch_hap_begin[b1];
+    std::vector<int32_t> bra(b1 - b0 + 1), bha(b1 - b0 + 1);
+    for (int32_t i = 0; i <= b1 - b0; ++i) {
+        bra[i] = shape->batch_read_begin[b0 + i] - r0;
+        bha[i] = shape->batch_hap_begin[b0 + i] - h0;
+    }
+    std::vector<int64_t> ro(r1 - r0 + 1), ho(h1 - h0 + 1);
+    for (int32_t i = 0; i <= r1 - r0; ++i) ro[i] = shape->read_offset[r0 + i] - shape->read_offset[r0];
+    for (int32_t i = 0; i <= h1 - h0; ++i) ho[i] = shape->hap_offset[h0 + i] - shape->hap_offset[h0];
+    const ph_shape sh{b1 - b0, bra.data(), bha.data(), r1 - r0, ro.data(), h1 - h0, ho.data()};
+    cols = 0;
+    return ph::plan_create(&sh, opts, cols, nullptr);
+}
+
 }  // namespace
 
 extern "C" {
@@ -181,25 +210,49 @@ ph_status ph_pipeline_create(const ph_shape *shape, const ph_pipeline_opts *opts
 
     // stage 1: greedy cut into subsets of whole batches, at most `cap` cells
     // each (a larger batch forms a subset of its own)
+    std::vector<int64_t> batch_cells(nb), batch_pairs(nb);
+    for (int32_t b = 0; b < nb; ++b) {
+        batch_cells[b] = (ro[rb[b + 1]] - ro[rb[b]]) * (ho[hb[b + 1]] - ho[hb[b]]);
+        batch_pairs[b] = (int64_t)(rb[b + 1] - rb[b]) * (hb[b + 1] - hb[b]);
+    }
     int64_t out0 = 0;
-    int32_t b = 0;
-    while (b < nb) {
+    // the next batches from b on, up to `most` cells (one batch at least), before batch `end`
+    auto add_subset = [&](int32_t b, int32_t end, int64_t most) {
         Subset s{};
         s.b0 = b;
         s.out0 = out0;
-        while (b < nb) {
-            int64_t nsum = 0;
-            for (int32_t h = hb[b]; h < hb[b + 1]; ++h) nsum += ho[h + 1] - ho[h];
-            int64_t c = 0, pairs = (int64_t)(rb[b + 1] - rb[b]) * (hb[b + 1] - hb[b]);
-            for (int32_t r = rb[b]; r < rb[b + 1]; ++r) c += (ro[r + 1] - ro[r]) * nsum;
-            if (b > s.b0 && s.cells + c > cap) break;
-            s.cells += c;
-            s.pairs += pairs;
+        while (b < end && (b == s.b0 || s.cells + batch_cells[b] <= most)) {
+            s.cells += batch_cells[b];
+            s.pairs += batch_pairs[b];
             ++b;
         }
         s.b1 = b;
         out0 += s.pairs;
         q->subsets.push_back(std::move(s));
+        return b;
+    };
+    for (int32_t b = 0; b < nb;) b = add_subset(b, nb, cap);
+    if (opts.max_subset_cells <= 0 && !q->subsets.empty() && q->subsets[0].cells >= kMinCutCells) {
+        // The first subset's copies have nothing to overlap with: it is cut into
+        // halves.  They keep the chain length of the whole, so that every score
+        // keeps its rounding.
+        const Subset whole = q->subsets[0];
+        int cols = 0;
+        ph_status cst = chain_cols_of(shape, &opts.plan, whole.b0, whole.b1, cols);
+        if (cst != PH_OK) {  // (a shape that the plans refuse as well)
+            destroy(q);
+            return cst;
+        }
+        std::vector<Subset> rest(q->subsets.begin() + 1, q->subsets.end());
+        q->subsets.clear();
+        out0 = 0;
+        int32_t b = whole.b0;
+        for (int part = 0; b < whole.b1; ++part) {
+            b = add_subset(b, whole.b1, part ? whole.cells : whole.cells / 2);
+            q->subsets.back().chain_cols = cols;
+        }
+        for (Subset &s : rest) q->subsets.push_back(std::move(s));
+        out0 = q->subsets.back().out0 + q->subsets.back().pairs;
     }
     q->P = out0;
 
@@ -226,7 +279,7 @@ ph_status ph_pipeline_create(const ph_shape *shape, const ph_pipeline_opts *opts
         for (int32_t i = 0; i <= snr; ++i) s.ro[i] = ro[s.r0 + i] - s.rb0;
         for (int32_t i = 0; i <= snh; ++i) s.ho[i] = ho[s.h0 + i] - s.hb0;
         ph_shape sh{snb, s.bra.data(), s.bha.data(), snr, s.ro.data(), snh, s.ho.data()};
-        st = ph_plan_create(&sh, &opts.plan, &s.plan);
+        st = ph::plan_create(&sh, &opts.plan, s.chain_cols, &s.plan);
         if (st != PH_OK) {  // the plan's message stays in ph_last_error()
             destroy(q);
             return st;
