@@ -643,7 +643,15 @@ int choose_chain_cols(const ph_plan *p, int32_t nb, const int32_t *rb, const int
 // 100-1,000 bases, 16 bins, 3.1e9 cells 1,020-1,330 / 800, 6.1e9 1,719 / 1,451,
 // 1.04e10 2,252 / 2,384; one bin of 150 x 300 bases, 4.7e8 cells 288 / 164,
 // 1.3e9 396 / 406, 3.6e9 659 / 991.  The estimates are within 10% of these.
+//
+// Pairs with reads of more than 255 bases hold 41 KB of tables each, three a
+// CU: 768 of them run at once, and what is beyond that waits for a second
+// round, of twice the binned sweeps' length (haplotypes of 350 bases, us,
+// binned / one-pair: 300 bases, 512 pairs 96 / 48, 1,024 101 / 87, 4,096
+// 143 / 235; 500 bases, all redone in FP64, 187 / 120, 215 / 223, 421 / 637;
+// 1,000 bases 523 / 429, 855 / 847, 2,336 / 2,520).
 constexpr double kOneCellsPerNs = 5700, kBinnedCellsPerNs = 7300, kOneNs = 20e3, kBinnedNs = 100e3;
+constexpr int64_t kOneLongPairs = 768;
 double tile_ns(int64_t cols, int P, int K) { return 2.0 * (double)(cols + P + 2) * (5.5 * K + 10); }
 
 // The FP32 work lists of a binned plan (Section III-C), built once from the
@@ -782,17 +790,23 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     return true;
 }
 
-// Time of the one-pair launch of a shape.
+// Time of the one-pair launch of a shape (infinite: too many pairs of long reads).
 double one_pair_ns(const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho, int32_t nb)
 {
     double cells = 0;
+    int64_t long_pairs = 0;
     for (int32_t q = 0; q < nb; ++q) {
-        int64_t rows = 0, cols = 0;
-        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) rows += (ro[r + 1] - ro[r] + 64) / 64 * 64;
+        int64_t rows = 0, cols = 0, long_reads = 0;
+        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
+            const int64_t m = ro[r + 1] - ro[r];
+            rows += (m + 64) / 64 * 64;
+            long_reads += m > 255;
+        }
         for (int32_t h = hb[q]; h < hb[q + 1]; ++h) cols += ho[h + 1] - ho[h] + 64;
         cells += (double)rows * (double)cols;
+        long_pairs += long_reads * (hb[q + 1] - hb[q]);
     }
-    return kOneNs + cells / kOneCellsPerNs;
+    return long_pairs > kOneLongPairs ? INFINITY : kOneNs + cells / kOneCellsPerNs;
 }
 
 // Time of a binned plan's launches: the bins run on side streams in turn.

@@ -72,6 +72,9 @@ def equal_length_problem(m, n, pairs, seed=0):
 
 
 def time_config(prob, dev, m, P, K, steps=3):
+    """Median FP32 stage (ms) of the batch in one configuration; None where the
+    batch is so small that its plan takes the one-pair launch instead of bins
+    (whose only stage is the FP32 one)."""
     import torch
     from . import binding
     with tempfile.NamedTemporaryFile("w", suffix=".txt", delete=False) as f:
@@ -85,10 +88,11 @@ def time_config(prob, dev, m, P, K, steps=3):
         for _ in range(steps):
             plan.forward(dev)
             ms.append(plan.stage_ms()[1])
+        binned = plan.stage_ms()[0] > 0
         plan.close()
     finally:
         os.unlink(path)
-    return float(np.median(ms))
+    return float(np.median(ms)) if binned else None
 
 
 def read_table(path):
@@ -218,13 +222,18 @@ def main():
              f"# equal-length batches, haplotype length {args.hap_len}, {args.pairs} pairs, kernel time",
              "# columns after '#' on each line: GCUPS of the chosen and of every tried configuration"]
     for lo, hi in ranges():
-        prob = equal_length_problem(hi, args.hap_len, args.pairs)
-        dev = binding.DeviceProblem(prob)
-        tried = []
-        for P in (4, 8, 16, 32, 64):
-            ks = sorted(k for (p, k) in CONFIGS if p == P and P * k - 1 >= hi)[:args.candidates]
-            for K in ks:
+        pairs, tried = args.pairs, []
+        configs = [(P, K) for P in (4, 8, 16, 32, 64)
+                   for K in sorted(k for (p, k) in CONFIGS if p == P and P * k - 1 >= hi)[:args.candidates]]
+        while len(tried) < len(configs):
+            prob = equal_length_problem(hi, args.hap_len, pairs)
+            dev = binding.DeviceProblem(prob)
+            tried = []
+            for P, K in configs:
                 ms = time_config(prob, dev, hi, P, K)
+                if ms is None:  # again with twice the pairs
+                    pairs *= 2
+                    break
                 tried.append((prob.total_cells / (ms * 1e-3) / 1e9, P, K))
         best = max(tried)
         desc = " ".join(f"{P}x{K}:{g:.0f}" for g, P, K in tried)

@@ -84,3 +84,19 @@ def test_one_pair_plan_free_and_rescued_count():
         assert torch.equal(free[~fp32], out[~fp32])
         assert float((free - out)[fp32].abs().max()) <= 1e-5
         plan.close()
+
+
+@pytest.mark.parametrize("reads,one", [(96, True), (97, False)])
+def test_one_pair_limit_of_long_reads(reads, one):
+    """768 pairs of reads over 255 bases run at once; one read more takes the bins."""
+    rng = np.random.default_rng(4)
+    ref = "".join(rng.choice(list("ACGT"), size=400))
+    prob = wl.from_strings([([ref[q % 50:][:300] for q in range(reads)], [ref[8 * h:][:330] for h in range(8)])])
+    plan = binding.Plan(prob, tune_table="builtin")
+    dev = binding.DeviceProblem(prob)
+    got, st = plan.forward(dev)
+    assert (plan.stage_ms()[0] == 0) == one
+    free, sf = binding.forward_noalloc(prob, dev)
+    same((got.cpu().numpy(), st.cpu().numpy()), gpu_forward(prob, force_p=64), "forward")
+    assert bool((st == sf).all()) and float((free - got).abs().max()) <= 1e-5
+    plan.close()
