@@ -890,15 +890,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K <= 3 ? 3 :
 // rows, reads of 64 (K-1) .. 64 K - 1 bases), one pair at a time per
 // workgroup.  Every wave leaves the loop once the cursor passes the queue
 // length, which the FP32 pass has finished writing before this launch.
+//
+// A plan with reads of several classes drains their queues in one launch, the
+// longest reads first (k_adj64_all): most calls leave them empty, and an empty
+// launch of a grid this size takes 8-10 us.
 // ---------------------------------------------------------------------------
 template <int K>
-__global__ __launch_bounds__(64) void k_adj64(AdjArgs A)
+__device__ void adj64_class(const AdjArgs &A, char *lds, double *ck)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int P = 64;
     const int cls = K - 1;
     const int count = A.q64_count[cls];
-    double *ck = A.ws64 + (int64_t)blockIdx.x * A.ws64_stride;
+    if (!count) return;  // (before the cursor: its atomics, a wave each, come one after the other)
     for (int item = next_tile(&A.q64_next[cls]); item < count; item = next_tile(&A.q64_next[cls])) {
         const int32_t gi = A.q64[(int64_t)cls * A.q64_stride + item];
         const AdjRec rec = A.all_recs[gi];
@@ -915,6 +918,24 @@ __global__ __launch_bounds__(64) void k_adj64(AdjArgs A)
         adj_emit<double, P, K>(A, pr, A.grad_in[rec.out], good ? 1.0 / ldexp(Ls, SB) : (double)NAN, sums);
         __syncthreads();  // LDS tables are rebuilt for the next pair
     }
+}
+
+template <int K>
+__global__ __launch_bounds__(64) void k_adj64(AdjArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    adj64_class<K>(A, lds, A.ws64 + (int64_t)blockIdx.x * A.ws64_stride);
+}
+
+__global__ __launch_bounds__(64) void k_adj64_all(AdjArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    double *ck = A.ws64 + (int64_t)blockIdx.x * A.ws64_stride;
+    adj64_class<5>(A, lds, ck);
+    adj64_class<4>(A, lds, ck);
+    adj64_class<3>(A, lds, ck);
+    adj64_class<2>(A, lds, ck);
+    adj64_class<1>(A, lds, ck);
 }
 
 // Fixed-order sum over the pairs of each read with several pairs:
@@ -995,30 +1016,27 @@ hipError_t launch_adj32(const AdjArgs &a, int P, int K, int lds, int grid, hipSt
 
 int adj32_blocks_per_cu(int P, int K, int lds) { return occupancy(adj32_kernel(P, K), (size_t)lds); }
 
-int adj64_blocks_per_cu(int K)
+// the kernel of one class (only), or of all
+static const void *adj64_kernel(int only)
 {
-    switch (K) {
-    case 1: return occupancy((const void *)k_adj64<1>, 0);
-    case 2: return occupancy((const void *)k_adj64<2>, 0);
-    case 3: return occupancy((const void *)k_adj64<3>, 0);
-    case 4: return occupancy((const void *)k_adj64<4>, 0);
-    case 5: return occupancy((const void *)k_adj64<5>, 0);
+    switch (only) {
+    case 1: return (const void *)k_adj64<1>;
+    case 2: return (const void *)k_adj64<2>;
+    case 3: return (const void *)k_adj64<3>;
+    case 4: return (const void *)k_adj64<4>;
+    case 5: return (const void *)k_adj64<5>;
     }
-    return 1;
+    return (const void *)k_adj64_all;
 }
 
-hipError_t launch_adj64(const AdjArgs &a, int K, int grid, hipStream_t s)
+int adj64_blocks_per_cu(int only) { return occupancy(adj64_kernel(only), 0); }
+
+hipError_t launch_adj64(const AdjArgs &a, int only, int k_max, int grid, hipStream_t s)
 {
-    const size_t lds = (size_t)adj64_e_bytes(K) + (size_t)a.hs_bytes64;
-    switch (K) {
-    case 1: hipLaunchKernelGGL(k_adj64<1>, dim3(grid), dim3(64), lds, s, a); break;
-    case 2: hipLaunchKernelGGL(k_adj64<2>, dim3(grid), dim3(64), lds, s, a); break;
-    case 3: hipLaunchKernelGGL(k_adj64<3>, dim3(grid), dim3(64), lds, s, a); break;
-    case 4: hipLaunchKernelGGL(k_adj64<4>, dim3(grid), dim3(64), lds, s, a); break;
-    case 5: hipLaunchKernelGGL(k_adj64<5>, dim3(grid), dim3(64), lds, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    AdjArgs args = a;
+    void *p[] = {&args};
+    return hipLaunchKernel(adj64_kernel(only), dim3(grid), dim3(64), p,
+                           (size_t)adj64_e_bytes(k_max) + (size_t)a.hs_bytes64, s);
 }
 
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s)

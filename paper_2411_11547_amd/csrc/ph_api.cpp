@@ -300,7 +300,7 @@ struct ph_plan {
     double *d_ws64 = nullptr;
     int64_t q64_stride = 0, ws64_stride = 0;
     int32_t grid64 = 0, hs_bytes64 = 0;
-    bool class64[kAdj64Classes] = {};
+    int k64_max = 1, k64_only = 0;  // the FP64 pass's largest class, and the only one (0: several)
     hipEvent_t ev_adj[2] = {};
     bool adj_recorded = false;
     hipGraph_t adj_graph = nullptr;
@@ -527,14 +527,14 @@ ph_status build_adjoint(ph_plan *p)
     }
     // FP64 pass: sized for the longest haplotype and the largest class of
     // the plan; the grid is bounded by the workspace budget
-    int n_max = 1, k64_max = 1;
+    int n_max = 1, k64_max = 1, k64_min = kAdj64Classes;
     for (const auto &it : items) n_max = std::max(n_max, it.r.n);
     for (int32_t r = 0; r < p->nr; ++r) {
         const int m = (int)(p->h_ro[r + 1] - p->h_ro[r]);
         const int k = (m + 64) / 64;
         if (k >= 1 && k <= kAdj64Classes) {
-            p->class64[k - 1] = true;
             k64_max = std::max(k64_max, k);
+            k64_min = std::min(k64_min, k);
         }
     }
     const int S64 = ((n_max + 63 + kAdjC64 - 1) / kAdjC64) * kAdjC64;
@@ -544,9 +544,11 @@ ph_status build_adjoint(ph_plan *p)
         p->adj_error = "haplotype too long for the FP64 adjoint sweep";
         return p->adj_status;
     }
+    p->k64_max = k64_max;
+    p->k64_only = k64_min == k64_max ? k64_max : 0;
     p->ws64_stride = ((int64_t)(S64 / kAdjC64) * (3 * k64_max + 3) * 64 + 31) / 32 * 32;
     p->grid64 = (int32_t)std::max<int64_t>(
-        1, std::min<int64_t>({(int64_t)p->cus * adj64_blocks_per_cu(k64_max), kAdjWs64Doubles / p->ws64_stride,
+        1, std::min<int64_t>({(int64_t)p->cus * adj64_blocks_per_cu(p->k64_only), kAdjWs64Doubles / p->ws64_stride,
                               (int64_t)items.size()}));
     p->q64_stride = (int64_t)items.size();
     ph_status st;
@@ -1365,10 +1367,8 @@ ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_
         a.ws_stride = L.ws_stride;
         HIPCHK(launch_adj32(a, L.runs.size() == 1 ? L.runs[0].P : 0, L.runs[0].K, L.lds, L.grid, s));
     }
-    // pairs out of the FP32 range, per class (a class whose queue stayed
-    // empty exits at once)
-    for (int k = 1; k <= kAdj64Classes; ++k)
-        if (p->class64[k - 1]) HIPCHK(launch_adj64(a, k, p->grid64, s));
+    // pairs out of the FP32 range
+    HIPCHK(launch_adj64(a, p->k64_only, p->k64_max, p->grid64, s));
     HIPCHK(launch_adj_reduce(p->d_red, p->n_red, p->d_grad_pair, grad_params, s));
     return PH_OK;
 }

@@ -263,13 +263,13 @@ int adj_e_bytes(int P, int K);
 int adj_ck_lds_bytes(int K);  // FP32 pass: LDS checkpoint buffers per workgroup
 hipError_t launch_adj32(const AdjArgs &a, int P, int K, int lds, int grid, hipStream_t s);
 int adj32_blocks_per_cu(int P, int K, int lds);
-int adj64_blocks_per_cu(int K);
+int adj64_blocks_per_cu(int only);  // the class that its reads are all of, or 0
 hipError_t launch_zero_f32(float *p, int64_t n, hipStream_t s);
 hipError_t launch_adj_reduce(const AdjRedRead *reads, int32_t nreads, const float *grad_pair, float *grad_out,
                              hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 int adj64_e_bytes(int K);
-hipError_t launch_adj64(const AdjArgs &a, int K, int grid, hipStream_t s);
+hipError_t launch_adj64(const AdjArgs &a, int only, int k_max, int grid, hipStream_t s);
 
 // Launchers (ph_kernels.hip).  All enqueue on `s` and return the HIP status.
 hipError_t upload_luts();
