@@ -218,7 +218,8 @@ struct ph_plan {
     int rescue_grid[kRescueGroups] = {};
     int plain_K = 0, plain_grid = 0;
     // reads longer than kMaxReadLen: one extra bin swept in windows
-    int long_bin = -1, long_K = 0, windows = 0, windows64 = 0, long_grid = 0, long64_grid = 0;
+    int long_bin = -1, windows = 0, windows64 = 0, long_grid = 0, long64_grid = 0;
+    bool long_few = false;
     int64_t long_pairs = 0, bnd_stride = 0;
     float *d_bnd32 = nullptr;
     double *d_bnd64 = nullptr;
@@ -1004,8 +1005,8 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
     p->cells = cells;
     // 3 waves per SIMD of 4-row windows fill the GPU; more items than that take
     // 16 rows per lane
-    p->long_K = few_items <= 3072 ? kLongK32Few : kLongK32Many;
-    p->windows = max_m / (64 * p->long_K) + 1;
+    p->long_few = few_items <= 3072;
+    p->windows = max_m / (64 * (p->long_few ? kLongK32Few : kLongK32Many)) + 1;
     p->windows64 = max_m / (64 * kLongK64) + 1;
     p->bnd_stride = (p->bnd_stride + 11) / 12 * 12;
     // the split table travels behind the length map in the same device array
@@ -1062,9 +1063,12 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
             if (p->bin_grid[b]) p->launch_order.push_back({b, next++ % kSideStreams});
     }
     if (p->long_pairs) {
-        p->long_grid =
-            (int)std::min<int64_t>(p->long_pairs * p->windows, (int64_t)p->cus * long32_blocks_per_cu(p->long_K));
-        p->long64_grid = (int)std::min<int64_t>(p->long_pairs * p->windows64, (int64_t)p->cus * long64_blocks_per_cu());
+        // work items: a pair's windows, few pairs kLongWaves of them at a time
+        const int wv = p->long_few ? kLongWaves : 1;
+        p->long_grid = (int)std::min<int64_t>(p->long_pairs * ((p->windows + wv - 1) / wv),
+                                              (int64_t)p->cus * long32_blocks_per_cu(p->long_few));
+        p->long64_grid = (int)std::min<int64_t>(p->long_pairs * ((p->windows64 + wv - 1) / wv),
+                                                (int64_t)p->cus * long64_blocks_per_cu(p->long_few));
     }
     if (opts.single_launch && !opts.plain) {
         bool ok = true;
@@ -1268,7 +1272,7 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
                     la.bnd = p->d_bnd32;
                     la.windows = p->windows;
                     la.progress = p->d_progress;
-                    HIPCHK(launch_long32(la, p->long_K, p->long_grid, p->side[k]));
+                    HIPCHK(launch_long32(la, p->long_few, p->long_grid, p->side[k]));
                 } else {
                     HIPCHK(launch_fwd32(sa, sa.bins[b].P, sa.bins[b].K, b, p->bin_grid[b], p->side[k]));
                 }
@@ -1287,9 +1291,9 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
             la.bnd = p->d_bnd64;
             la.windows = p->windows64;
             la.progress = p->d_progress + p->long_pairs * p->windows;
-            HIPCHK(launch_long64(la, true, p->long64_grid, s));
+            HIPCHK(launch_long64(la, p->long_few, true, p->long64_grid, s));
             la.progress += p->long_pairs * p->windows64;
-            HIPCHK(launch_long64(la, false, p->long64_grid, s));
+            HIPCHK(launch_long64(la, p->long_few, false, p->long64_grid, s));
         }
     }
     return PH_OK;

@@ -38,6 +38,7 @@ constexpr int kRescueQueues = 2 * kRescueClasses;
 // (see k_long32).  The FP32 row sums are grouped as in windows of kLongRows rows.
 constexpr int kLongRows = 1024;
 constexpr int kLongK32Few = 4, kLongK32Many = 16, kLongK64 = 4;
+constexpr int kLongWaves = 4;  // few pairs: windows in a workgroup, one a wave
 constexpr int kMaxLongReadLen = 65535;
 
 // One read/haplotype pair: indices into the problem and into the output.
@@ -283,10 +284,10 @@ hipError_t launch_fwd32_single(const SweepArgs &a, int grid, hipStream_t s);
 int fwd32_single_blocks_per_cu();
 bool single_supported(int P, int K);
 hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s);
-hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s);
-hipError_t launch_long64(const SweepArgs &a, bool rescaled, int grid, hipStream_t s);
-int long32_blocks_per_cu(int K);
-int long64_blocks_per_cu();
+hipError_t launch_long32(const SweepArgs &a, bool few, int grid, hipStream_t s);
+hipError_t launch_long64(const SweepArgs &a, bool few, bool rescaled, int grid, hipStream_t s);
+int long32_blocks_per_cu(bool few);
+int long64_blocks_per_cu(bool few);
 hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s);
 hipError_t launch_prep_params(const float *lg, int64_t npos, double *lin, hipStream_t s);
 hipError_t launch_validate(const DevProblem &pb, int64_t nread_bases, int64_t nhap_bases,

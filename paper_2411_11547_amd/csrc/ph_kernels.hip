@@ -416,6 +416,36 @@ struct Boundary {
     }
 };
 
+// NW > 1: NW consecutive windows of a pair in one workgroup, a wave each.  A wave
+// hands its columns to the next one through a ring in LDS, and only the first
+// and the last of them use the boundary row in memory.  done[i]: the columns
+// that wave i has handed on; taken[i]: those that wave i has read (a ring holds
+// kCols, and a wave overwrites only what was read).
+template <typename T, bool H, int NW>
+struct Relay {
+    static constexpr int NV = Boundary<T, H>::NV, kCols = 128;
+    int done[NW], taken[NW];
+    unsigned long long item;
+    T ring[NW > 1 ? NW - 1 : 1][NV][kCols];
+};
+__device__ __forceinline__ int relay_load(const int *p)
+{
+    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+}
+
+// a barrier of the waves that share a tile's LDS: the workgroup, or (NW > 1) the
+// wave alone, whose LDS accesses are carried out in order
+template <int NW>
+__device__ __forceinline__ void tile_sync()
+{
+    if constexpr (NW == 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // One step of the windowed sweep with the plain states (64 lanes): lane 0
 // takes the staged boundary values of its column, the last lane leaves its new
 // ones in `bot`.
@@ -565,18 +595,19 @@ struct RangeHat<double> {
 // Only the window that holds the absorbing row m+1 produces the result; its
 // FP32 sum is grouped as in windows of 1,024 rows with 16 rows per lane (a
 // lead, as in one-pair mode), so that it does not depend on K.
-template <typename T, int P, int K, bool W = false, bool V = false, bool H = sizeof(T) == 4, bool S = false>
+template <typename T, int P, int K, bool W = false, bool V = false, bool H = sizeof(T) == 4, bool S = false, int NW = 1>
 __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int rec_first,
                           int nvalid, char *lds, OneRec one = OneRec(), WinRec win = WinRec())
 {
     using C = Cfg<T, P, K>;
     static_assert(!S || (P == 64 && !W), "one-pair mode: 64 lanes, no windows");
     static_assert(!W || P == 64, "windowed sweep: 64 lanes");
+    static_assert(W || NW == 1, "several waves: windows only");
     constexpr int WR = P * K;  // rows of a window
     static_assert(sizeof(T) == 4 || !H || !V, "FP64 rescaled states: the sum-product sweep only");
     constexpr bool HAT = H;  // rescaled states (M, It, Dh)
     constexpr int kExp = HAT ? RangeHat<T>::kExp : Range<T>::kExp;
-    const int lane = threadIdx.x;
+    const int lane = NW > 1 ? threadIdx.x & 63 : threadIdx.x;
     const int g = lane / P;
     const int t = lane % P;
     const int r0 = W ? win.w * WR : 0;  // first row of the window (0-based)
@@ -641,6 +672,9 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         bnd.open((T *)A.bnd + (int64_t)win.slot * A.bnd_stride, A.bnd_stride);
         prog = A.progress + (int64_t)win.slot * A.windows + win.w;
     }
+    // several windows in a workgroup: this one is its wave wi
+    const int wi = NW > 1 ? win.w % NW : 0;
+    Relay<T, HAT, NW> *relay = (Relay<T, HAT, NW> *)(lds + (NW - wi) * (C::LDS_BYTES + Boundary<T, HAT>::LDS_BYTES));
 
     // the longest haplotype (chain) of the wave sets the number of steps
     int nmax = nring + lead;
@@ -855,7 +889,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     }
     // haplotype ring: PAD everywhere (negative columns read slot 3), then chunks 0 and 1
     for (int x = t; x < ring_alloc(P); x += P) ring[x] = (uint16_t)(kPad * C::CODE_BYTES);
-    __syncthreads();
+    tile_sync<NW>();
     {
         uint32_t c0[RingPer<P>::N], c1[RingPer<P>::N];
         ring_load<P>(c0, 0, hap, nring, t, lead);
@@ -863,7 +897,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         ring_store<P>(ring, 0, c0, t, C::CODE_BYTES, chain);
         ring_store<P>(ring, 1, c1, t, C::CODE_BYTES, chain);
     }
-    __syncthreads();
+    tile_sync<NW>();
 
     // ---- sweep ----------------------------------------------------------------
     T M[K], I[K], D[K];
@@ -984,6 +1018,19 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     auto take_columns = [&](int s) {
         if (r0 == 0) {
             bnd.none(HAT ? first_edge : (T)0);
+        } else if (wi > 0) {
+            // (ends: the wave above, if it waits for room, does so with more
+            // columns handed on than this one needs)
+            const int need = __builtin_amdgcn_readfirstlane(min(n, s + CH - lead)), j = s + 1 + t - lead;
+            while (relay_load(&relay->done[wi - 1]) < need) __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            bnd.none(0);
+            if (j >= 1 && j <= n)
+#pragma unroll
+                for (int v = 0; v < Boundary<T, HAT>::NV; ++v)
+                    bnd.next[v] = relay->ring[wi - 1][v][j & (Relay<T, HAT, NW>::kCols - 1)];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (t == 0) __hip_atomic_store(&relay->taken[wi], need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else if (!early) {
             const int need = __builtin_amdgcn_readfirstlane(min(n, s + CH - lead)), j = s + 1 + t - lead;
             // (ends: the window above was handed out before this one, to a
@@ -998,7 +1045,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
         }
         bnd.stage(wlds, t);
         early = false;
-        if (r0 > 0) {
+        if (r0 > 0 && wi == 0) {
             if (seen >= __builtin_amdgcn_readfirstlane(min(n, s + 2 * CH - lead))) {
                 const int j = s + CH + 1 + t - lead;
                 early = true;
@@ -1007,12 +1054,27 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             }
             ahead_prog = __hip_atomic_load(prog - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        __syncthreads();
+        tile_sync<NW>();
     };
     // after them, the columns handed on in these steps, and once they have
     // arrived the count of columns that the window below may read
     auto give_columns = [&](int s, int steps) {
         const int j = s + t - (Boundary<T, HAT>::kBehind);
+        if (NW > 1 && wi < NW - 1) {
+            const int room = __builtin_amdgcn_readfirstlane(min(n, s + CH - 1 - (Boundary<T, HAT>::kBehind))) -
+                             Relay<T, HAT, NW>::kCols;
+            while (relay_load(&relay->taken[wi + 1]) < room) __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (t < steps && j >= 1 && j <= n)
+#pragma unroll
+                for (int v = 0; v < Boundary<T, HAT>::NV; ++v)
+                    relay->ring[wi][v][j & (Relay<T, HAT, NW>::kCols - 1)] =
+                        ((const T *)wlds)[(Boundary<T, HAT>::NV + v) * 64 + t];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            const int columns = s + CH < total ? s + CH - 1 - (Boundary<T, HAT>::kBehind) : 0x7fffffff;
+            if (t == 0) __hip_atomic_store(&relay->done[wi], columns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            return;
+        }
         if (t < steps && j >= 1 && j <= n) bnd.write(wlds, t, j);
         wait_vm0();
         const int columns = s + CH < total ? s + CH - 1 - (Boundary<T, HAT>::kBehind) : 0x7fffffff;
@@ -1076,7 +1138,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                 acc += (double)part;
         }
         ring_store<P>(ring, s0 / CH + 2, ahead, t, C::CODE_BYTES, chain);
-        __syncthreads();
+        tile_sync<NW>();
         if constexpr (W) {
             if (!fin) give_columns(s0, cnt);
         }
@@ -1136,7 +1198,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                 if (A.out_status) A.out_status[rec.out] = st;
             }
         }
-        __syncthreads();  // the tables in LDS are rebuilt by the pair's next sweep
+        tile_sync<NW>();  // the tables in LDS are rebuilt by the pair's next sweep
         return __builtin_amdgcn_readlane(need, HAT ? __builtin_amdgcn_readfirstlane(m / K) : P - 1);
     }
     if (gvalid && owner && fin) {
@@ -1327,49 +1389,70 @@ __global__ __launch_bounds__(64) void k_rescue(SweepArgs A)
 // boundary row, so the windows of a pair run as a pipeline.  (One launch per
 // window of 1,024 rows kept one wave per pair busy: 53 pairs of 1,100-8,000 x
 // 3,000-9,000 bases took 19.7 ms in FP32 and 39 ms in FP64.)  What bounds it with few pairs
-// is the length of one pair's pipeline, n steps plus about 250 for each window,
+// is the length of one pair's pipeline, n steps plus about 150 for each window,
 // at the 5 clocks a wave takes for an instruction: few rows per lane make short
-// steps and more waves.  Plans with many long pairs take 16 rows per lane, which
-// costs fewer instructions per cell.
+// steps and more waves, and kLongWaves windows of a pair in one workgroup, a
+// wave each, hand their columns on in LDS (53 pairs as above: 3.66 ms with every
+// boundary in memory, 3.34 with one in four).  Plans with many long pairs take 16
+// rows per lane, which costs fewer instructions per cell, and a window per
+// workgroup.
 //
-// Work items are (pair, window), a pair's windows in a row and the first window first,
+// Work items are (pair, NW windows), a pair's windows in a row and the first window first,
 // handed out in that order by one counter: the window above an item was handed
 // out before it, to a wave that is running and itself waits only for windows
 // further up, so every wait ends, whatever part of the grid is resident.
 // FP32: the pairs of the long bin (slot = position in the bin); FP64: the
 // long-pair queues (slot = queue position).
-template <int K, bool V>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K > 8 ? 2 : 4))) void k_long32(SweepArgs A)
+template <typename T, int K, bool V, bool H, int NW>
+__device__ __forceinline__ void long_items(const SweepArgs &A, const int32_t *list, int first, int64_t pairs,
+                                           unsigned long long *cursor)
 {
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<float, 64, K>::LDS_BYTES + Boundary<float, true>::LDS_BYTES];
+    constexpr int PER = Cfg<T, 64, K>::LDS_BYTES + Boundary<T, H>::LDS_BYTES;
+    static_assert(PER % 16 == 0, "");
+    __shared__ __attribute__((aligned(16))) char lds[NW * PER + (NW > 1 ? sizeof(Relay<T, H, NW>) : 0)];
+    const int wi = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : 0;
+    const uint32_t groups = (uint32_t)(A.windows + NW - 1) / NW;  // of NW windows
+    const uint64_t items = (uint64_t)pairs * groups;
+    for (;;) {
+        uint64_t item;
+        if constexpr (NW == 1) {
+            item = next_item(cursor);
+        } else {
+            Relay<T, H, NW> *relay = (Relay<T, H, NW> *)(lds + NW * PER);
+            __syncthreads();  // every wave has left the last item
+            if (threadIdx.x < NW) relay->done[threadIdx.x] = relay->taken[threadIdx.x] = 0;
+            if (threadIdx.x == 0) relay->item = atomicAdd(cursor, 1ull);
+            __syncthreads();
+            item = relay->item;
+            item = (uint64_t)__builtin_amdgcn_readfirstlane((int)(item >> 32)) << 32 |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)item);
+        }
+        if (item >= items) return;
+        WinRec win;
+        win.slot = (int)(item / groups);
+        win.w = (int)(item % groups) * NW + wi;
+        sweep_tile<T, 64, K, true, V, H, false, NW>(A, list, first + win.slot, 1, lds + wi * PER, OneRec(), win);
+    }
+}
+
+template <int K, bool V, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(K > 8 ? 2 : 4))) void k_long32(SweepArgs A)
+{
     Book *bk = A.book;
     const int rb = bk->bin_rec_begin[A.long_bin];
-    const uint64_t items = (uint64_t)(bk->bin_rec_begin[A.long_bin + 1] - rb) * A.windows;
-    for (uint64_t item = next_item(&bk->long_next); item < items; item = next_item(&bk->long_next)) {
-        WinRec win;
-        win.slot = (int)(item / (uint32_t)A.windows);
-        win.w = (int)(item % (uint32_t)A.windows);
-        sweep_tile<float, 64, K, true, V>(A, nullptr, rb + win.slot, 1, lds, OneRec(), win);
-    }
+    long_items<float, K, V, true, NW>(A, nullptr, rb, bk->bin_rec_begin[A.long_bin + 1] - rb, &bk->long_next);
 }
 
 // H: the rescaled states over the long pairs that left the FP32 range, then the
 // plain ones over those with a row outside the rescaled states and what the
 // first pass leaves.
-template <bool V, bool H>
-__global__ __launch_bounds__(64) void k_long64(SweepArgs A)
+template <bool V, bool H, int NW>
+__global__ __launch_bounds__(64 * NW) void k_long64(SweepArgs A)
 {
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, kLongK64>::LDS_BYTES + Boundary<double, H>::LDS_BYTES];
     Book *bk = A.book;
-    const uint64_t items = (uint64_t)(H ? bk->long_rescue_count : bk->long_plain_count) * A.windows;
-    unsigned long long *next = H ? &bk->long64_next : &bk->long_plain_next;
-    for (uint64_t item = next_item(next); item < items; item = next_item(next)) {
-        WinRec win;
-        win.slot = (int)(item / (uint32_t)A.windows);
-        win.w = (int)(item % (uint32_t)A.windows);
-        sweep_tile<double, 64, kLongK64, true, V, H>(A, H ? A.long_rescue_list : A.long_plain_list, win.slot, 1, lds,
-                                                     OneRec(), win);
-    }
+    long_items<double, kLongK64, V, H, NW>(A, H ? A.long_rescue_list : A.long_plain_list, 0,
+                                           H ? bk->long_rescue_count : bk->long_plain_count,
+                                           H ? &bk->long64_next : &bk->long_plain_next);
 }
 
 // Small calls: one launch, one pair per wave, 64 lanes x ceil((m + 1) / 64)
@@ -1666,7 +1749,7 @@ __global__ __launch_bounds__(256) void k_validate(const uint8_t *rb, int64_t nr,
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-static int occupancy(const void *fn);
+static int occupancy(const void *fn, int threads = 64);
 
 static int grid_for(int64_t items, int per_block, int cap)
 {
@@ -1773,35 +1856,37 @@ hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s)
     return hipLaunchKernel(rescue_kernel(group, b.viterbi != 0), dim3(grid), dim3(64), p, 0, s);
 }
 
-hipError_t launch_long32(const SweepArgs &a, int K, int grid, hipStream_t s)
+// few (4 rows per lane in FP32) or many long pairs: the kernels and their waves per workgroup
+static const void *long32_kernel(bool few, bool viterbi)
+{
+    if (few)
+        return viterbi ? (const void *)k_long32<kLongK32Few, true, kLongWaves>
+                       : (const void *)k_long32<kLongK32Few, false, kLongWaves>;
+    return viterbi ? (const void *)k_long32<kLongK32Many, true, 1> : (const void *)k_long32<kLongK32Many, false, 1>;
+}
+static const void *long64_kernel(bool few, bool viterbi, bool rescaled)
+{
+    if (viterbi) return few ? (const void *)k_long64<true, false, kLongWaves> : (const void *)k_long64<true, false, 1>;
+    if (rescaled) return few ? (const void *)k_long64<false, true, kLongWaves> : (const void *)k_long64<false, true, 1>;
+    return few ? (const void *)k_long64<false, false, kLongWaves> : (const void *)k_long64<false, false, 1>;
+}
+
+hipError_t launch_long32(const SweepArgs &a, bool few, int grid, hipStream_t s)
 {
     SweepArgs b = a;
     b.mode = kModeBinned;
-#define PH_LL(k)                                                                       \
-    if (K == k) {                                                                      \
-        if (b.viterbi)                                                                 \
-            hipLaunchKernelGGL((k_long32<k, true>), dim3(grid), dim3(64), 0, s, b);    \
-        else                                                                           \
-            hipLaunchKernelGGL((k_long32<k, false>), dim3(grid), dim3(64), 0, s, b);   \
-        return hipGetLastError();                                                      \
-    }
-    PH_LL(kLongK32Few) PH_LL(kLongK32Many)
-#undef PH_LL
-    return hipErrorInvalidValue;
+    void *p[] = {&b};
+    return hipLaunchKernel(long32_kernel(few, b.viterbi != 0), dim3(grid), dim3(few ? 64 * kLongWaves : 64), p, 0, s);
 }
 
-hipError_t launch_long64(const SweepArgs &a, bool rescaled, int grid, hipStream_t s)
+hipError_t launch_long64(const SweepArgs &a, bool few, bool rescaled, int grid, hipStream_t s)
 {
     SweepArgs b = a;
     b.mode = kModeRescue;
     if (b.viterbi && rescaled) return hipSuccess;  // the max-product score uses the plain queue only
-    if (b.viterbi)
-        hipLaunchKernelGGL((k_long64<true, false>), dim3(grid), dim3(64), 0, s, b);
-    else if (rescaled)
-        hipLaunchKernelGGL((k_long64<false, true>), dim3(grid), dim3(64), 0, s, b);
-    else
-        hipLaunchKernelGGL((k_long64<false, false>), dim3(grid), dim3(64), 0, s, b);
-    return hipGetLastError();
+    void *p[] = {&b};
+    return hipLaunchKernel(long64_kernel(few, b.viterbi != 0, rescaled), dim3(grid),
+                           dim3(few ? 64 * kLongWaves : 64), p, 0, s);
 }
 
 hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s)
@@ -1838,10 +1923,10 @@ hipError_t launch_validate(const DevProblem &pb, int64_t nrb, int64_t nhb, int32
     return hipGetLastError();
 }
 
-static int occupancy(const void *fn)
+static int occupancy(const void *fn, int threads)
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 64, 0) != hipSuccess || nb < 1) nb = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
 
@@ -1864,12 +1949,8 @@ int plain32_blocks_per_cu(int K)
     return 1;
 }
 
-int long32_blocks_per_cu(int K)
-{
-    return K == kLongK32Few ? occupancy((const void *)k_long32<kLongK32Few, false>)
-                            : occupancy((const void *)k_long32<kLongK32Many, false>);
-}
-int long64_blocks_per_cu() { return occupancy((const void *)k_long64<false, false>); }
+int long32_blocks_per_cu(bool few) { return occupancy(long32_kernel(few, false), few ? 64 * kLongWaves : 64); }
+int long64_blocks_per_cu(bool few) { return occupancy(long64_kernel(few, false, false), few ? 64 * kLongWaves : 64); }
 
 int rescue_blocks_per_cu(int group) { return occupancy(rescue_kernel(group, false)); }
 

@@ -4,7 +4,7 @@ against the FP64 oracle."""
 import numpy as np
 import pytest
 
-from gpu_util import binding, check_against_oracle, gpu_forward, oracle, say, wl
+from gpu_util import binding, check_against_oracle, gpu_forward, gpu_viterbi, oracle, say, wl
 
 pytestmark = pytest.mark.gpu
 
@@ -208,3 +208,22 @@ def test_many_long_pairs_equal_few():
     assert np.array_equal(gf[fp32], gm[:k][fp32])
     ok = sf == binding.PAIR_FP64
     assert np.abs(gf[ok] - gm[:k][ok]).max() <= 1e-9
+
+
+@pytest.mark.parametrize("m", [1024, 1300, 1791, 1792, 2303])
+def test_windows_of_a_workgroup(m):
+    """Four windows of 256 rows in a workgroup, handing on through rings of 128
+    columns: haplotypes around one and two rings, FP32, FP64 and Viterbi; the last window
+    is a workgroup's first, second, third, fourth or the next one's first."""
+    rng = np.random.default_rng(m)
+    ref = rng.choice(list("ACGT"), size=2400)
+    reads = ["".join(ref[10:10 + m])]
+    haps = ["".join(ref[:n]) for n in (2, 62, 127, 128, 129, 191, 192, 193, 255, 256, 257, 385, 2400)]
+    prob = wl.from_strings([(reads, haps)], base_q=37)
+    got, st = gpu_forward(prob)
+    check_against_oracle(prob, got, st)
+    got, st = gpu_forward(prob, rescue_threshold=float("inf"))
+    assert np.all(st != binding.PAIR_FP32)
+    check_against_oracle(prob, got, st)
+    got, st = gpu_viterbi(prob)
+    check_against_oracle(prob, got, st, ref=oracle.viterbi(prob))
