@@ -467,19 +467,19 @@ __device__ __forceinline__ void window_step(T (&M)[K], T (&I)[K], T (&D)[K], T &
     }
 }
 
-// The same with the rescaled states.
+// The same with the rescaled states: lane 0 takes tX and tY, read from LDS a step
+// before, and the last lane leaves its X and Y in bot[0] and bot[64].
 template <typename T, int K, bool V>
 __device__ __forceinline__ void window_step_hx(T (&M)[K], T (&I)[K], T (&D)[K], T &Xd, const T *lam,
                                                const T (&ci)[K], const T (&cd)[K], const T (&ke)[K],
-                                               const T (&ep)[K], T cib, T cdb, T keb, char *win, int u, int t)
+                                               const T (&ep)[K], T cib, T cdb, T keb, T tX, T tY,
+                                               __attribute__((address_space(3))) T *bot, int t)
 {
-    T *top = (T *)win, *bot = top + 128;
     T X, Y;
-    cell_step_hx<T, 64, K, V, true>(M, I, D, Xd, lam, ci, cd, ke, ep, cib, cdb, keb, (T)0, ~0u, X, Y, top[u],
-                                    top[64 + u]);
+    cell_step_hx<T, 64, K, V, true>(M, I, D, Xd, lam, ci, cd, ke, ep, cib, cdb, keb, (T)0, ~0u, X, Y, tX, tY);
     if (t == 63) {
-        bot[u] = X;
-        bot[64 + u] = Y;
+        bot[0] = X;
+        bot[64] = Y;
     }
 }
 
@@ -1096,19 +1096,41 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             const volatile __attribute__((address_space(3))) uint16_t *hv =
                 (const volatile __attribute__((address_space(3))) uint16_t *)hp;
             int u = 0;
+            // Where a wave has its SIMD to itself (windows, one-pair mode)
+            // every read from LDS is issued a step before its value is needed:
+            // the codes two steps ahead, the emissions and the window's
+            // columns one (at the end of a chunk one code and column too many):
+            // 53 long pairs 3.34 -> 2.92 ms, 360 pairs without a plan 36.8 ->
+            // 31.6 us.
+            constexpr bool EARLY = W || S;
+            uint32_t code = EARLY ? hv[1] : 0;
+            __attribute__((address_space(3))) T *wp = (__attribute__((address_space(3))) T *)wlds;
+            T tX = 0, tY = 0;
+            if constexpr (W) {
+                asm volatile("" : "+v"(wp));  // a vector register: no move of a scalar address for each access
+                tX = wp[0];
+                tY = wp[64];
+            }
             for (;;) {
                 const int stop = (CHN && rs_next - s0 < cnt) ? rs_next - s0
                                  : (S && u == 0 && one.flush < cnt) ? one.flush : cnt;
                 for (; u < stop; u += 2) {
-                    load_lam<T, P, K>(lb, ebase_lane + hv[u + 1]);
+                    load_lam<T, P, K>(lb, ebase_lane + (EARLY ? code : hv[u + 1]));
+                    if constexpr (EARLY) code = hv[u + 2];
                     if constexpr (W) {
-                        window_step_hx<T, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, wlds, u, t);
-                        load_lam<T, P, K>(la, ebase_lane + hv[u + 2]);
-                        window_step_hx<T, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, wlds, u + 1, t);
+                        T nX = wp[1], nY = wp[65];
+                        window_step_hx<T, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, tX, tY, wp + 128, t);
+                        load_lam<T, P, K>(la, ebase_lane + code);
+                        code = hv[u + 3];
+                        tX = wp[2];
+                        tY = wp[66];
+                        window_step_hx<T, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, nX, nY, wp + 129, t);
+                        wp += 2;
                     } else {
                         T X, Y;
                         cell_step_hx<T, P, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
-                        load_lam<T, P, K>(la, ebase_lane + hv[u + 2]);
+                        load_lam<T, P, K>(la, ebase_lane + (EARLY ? code : hv[u + 2]));
+                        if constexpr (EARLY) code = hv[u + 3];
                         cell_step_hx<T, P, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
                     }
                 }
@@ -1379,7 +1401,7 @@ template <int C0, int C1, bool V>
 __global__ __launch_bounds__(64) void k_rescue(SweepArgs A)
 {
     constexpr int KHI = 2 << C1;
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (a code past the ring is read)
     rescue_class<KHI, V>(A, C1, lds);
     if constexpr (C0 < C1) rescue_class<(2 << C0), V>(A, C0, lds);
 }
@@ -1473,7 +1495,7 @@ template <bool LONG, bool V, bool FREE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3))) void k_one(SweepArgs A, OneArgs L)
 {
     constexpr int KHI = LONG ? 16 : 4;
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (a code past the ring is read)
     OneRec one;
     if constexpr (FREE) {
         const int k = blockIdx.x;
