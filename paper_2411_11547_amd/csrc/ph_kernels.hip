@@ -1099,11 +1099,16 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             // Where a wave has its SIMD to itself (windows, one-pair mode)
             // every read from LDS is issued a step before its value is needed:
             // the codes two steps ahead, the emissions and the window's
-            // columns one (at the end of a chunk one code and column too many):
-            // 53 long pairs 3.34 -> 2.92 ms, 360 pairs without a plan 36.8 ->
-            // 31.6 us.
+            // columns one (at the end of a chunk a code or two and a column too
+            // many): 53 long pairs 3.34 -> 2.92 ms, 360 pairs without a plan
+            // 36.8 -> 31.6 us.  Steps of one or two rows are shorter than a read
+            // takes: codes three steps ahead there (32 pairs of 2 rows 22.3 ->
+            // 21.0 us; with 3 or 4 rows 31.7 -> 33.2).
             constexpr bool EARLY = W || S;
-            uint32_t code = EARLY ? hv[1] : 0;
+            constexpr int AHEAD = S && sizeof(T) == 4 && K <= 2 ? 3 : 2;
+            uint32_t code = EARLY ? hv[1] : 0;  // of the next step
+            uint32_t code2 = AHEAD == 3 ? hv[2] : 0;  // and of the one after it
+            (void)code2;
             __attribute__((address_space(3))) T *wp = (__attribute__((address_space(3))) T *)wlds;
             T tX = 0, tY = 0;
             if constexpr (W) {
@@ -1116,7 +1121,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                                  : (S && u == 0 && one.flush < cnt) ? one.flush : cnt;
                 for (; u < stop; u += 2) {
                     load_lam<T, P, K>(lb, ebase_lane + (EARLY ? code : hv[u + 1]));
-                    if constexpr (EARLY) code = hv[u + 2];
+                    if constexpr (EARLY) code = hv[u + AHEAD];
                     if constexpr (W) {
                         T nX = wp[1], nY = wp[65];
                         window_step_hx<T, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, tX, tY, wp + 128, t);
@@ -1129,8 +1134,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                     } else {
                         T X, Y;
                         cell_step_hx<T, P, K, V>(M, I, D, Xd, la, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
-                        load_lam<T, P, K>(la, ebase_lane + (EARLY ? code : hv[u + 2]));
-                        if constexpr (EARLY) code = hv[u + 3];
+                        load_lam<T, P, K>(la, ebase_lane + (!EARLY ? hv[u + 2] : AHEAD == 3 ? code2 : code));
+                        if constexpr (EARLY) (AHEAD == 3 ? code2 : code) = hv[u + AHEAD + 1];
                         cell_step_hx<T, P, K, V>(M, I, D, Xd, lb, ci, cd, ke, ep, cib, cdb, keb, edge, keep, X, Y);
                     }
                 }
@@ -1401,7 +1406,7 @@ template <int C0, int C1, bool V>
 __global__ __launch_bounds__(64) void k_rescue(SweepArgs A)
 {
     constexpr int KHI = 2 << C1;
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (a code past the ring is read)
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (two codes past the ring are read)
     rescue_class<KHI, V>(A, C1, lds);
     if constexpr (C0 < C1) rescue_class<(2 << C0), V>(A, C0, lds);
 }
@@ -1495,7 +1500,7 @@ template <bool LONG, bool V, bool FREE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3))) void k_one(SweepArgs A, OneArgs L)
 {
     constexpr int KHI = LONG ? 16 : 4;
-    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (a code past the ring is read)
+    __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (two codes past the ring are read)
     OneRec one;
     if constexpr (FREE) {
         const int k = blockIdx.x;
