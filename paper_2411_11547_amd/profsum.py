@@ -11,7 +11,7 @@ kept with the repository.
         run and a WRITE_SIZE run of the same command, each scaled by what the
         counter reads for a device copy of COPY_MIB MiB (bench.py
         --copy-probe-mib) in the same run; with KERNEL (a name prefix such as
-        k_adj32 or k_fwd64), the same scaled bytes per dispatch of every
+        k_adj32 or k_rescue), the same scaled bytes per dispatch of every
         kernel of that name instead
 
 Reads the databases only; runs nothing.
@@ -70,8 +70,8 @@ def kernels(db):
     fwd = [r for r in rows if not any(k in r[0] for k in SWEEP) or _is_sweep(r[0])]
     vit = [r for r in rows if not any(k in r[0] for k in SWEEP) or not _is_sweep(r[0])]
     # a forward call starts with its binning (k_reset) or, with work lists
-    # built at plan creation, with the copy of the plan's book (k_book_copy)
-    first = ("k_reset", "k_book_copy")
+    # built at plan creation, with the copy of the plan's book (k_prepare)
+    first = ("k_reset", "k_prepare")
     for title, rs, marker, members in (("FP32 sweep stage of the forward calls", fwd, first, SWEEP),
                                        ("FP32 sweep stage of the Viterbi calls", vit, first, SWEEP),
                                        ("adjoint kernels", rows, ("k_zero_i32",), ADJ)):
