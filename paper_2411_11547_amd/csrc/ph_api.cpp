@@ -240,6 +240,7 @@ struct ph_plan {
     // small plans: one launch, one pair per wave (k_one)
     bool one = false;
     bool one_reads[2] = {};            // some read of up to 255 bases, some longer one
+    int one_max_m = 0;
     OneRec *d_one = nullptr;
     uint8_t *d_one_rescued = nullptr;  // per output of the last call: 1 if the pair went to FP64
 
@@ -825,6 +826,26 @@ double binned_ns(const ph_plan *p)
     return kBinnedNs + (double)p->cells / kBinnedCellsPerNs + *std::max_element(stream, stream + kSideStreams);
 }
 
+// The one-pair launches of a call with reads of up to 255 bases and longer ones.
+// Two launches, one after the other, each take at least one pair's sweep; in one,
+// every pair holds the longer reads' tables (25 KB up to 511 bases, 6 a CU; 41 KB
+// beyond, 3 a CU).  One launch wins up to three rounds of 1,536 pairs (reads of
+// 60-300 bases, us, two / one: 200 pairs 93 / 51, 1,900 119 / 80, 4,000 152 /
+// 119), with reads over 511 bases up to the one round of 768 that kOneLongPairs
+// allows (60-600 bases, 100 pairs 345 / 300, 700 pairs 350 / 300).
+constexpr int kOneUpTo511Pairs = 4096;
+hipError_t launch_one_pairs(const SweepArgs &sa, const OneArgs &oa, const bool *reads, int max_m, int pairs,
+                            hipStream_t s)
+{
+    if (reads[0] && reads[1]) {
+        if (max_m <= 511 && pairs <= kOneUpTo511Pairs) return launch_one(sa, oa, kOneUpTo511, pairs, s);
+        if (pairs <= kOneLongPairs) return launch_one(sa, oa, kOneUpTo1023, pairs, s);
+    }
+    hipError_t e = reads[1] ? launch_one(sa, oa, kOneLong, pairs, s) : hipSuccess;
+    if (e == hipSuccess && reads[0]) e = launch_one(sa, oa, kOneShort, pairs, s);
+    return e;
+}
+
 // The pairs of a small plan in the one-pair list, longest sweep first.  The
 // lead of a pair puts the groups of its FP32 row sum where its tile in the
 // work lists has them: that tile flushes the sum after the columns j with
@@ -1035,6 +1056,7 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
         p->one = true;
         one = one_list(p.get(), recs, img, ro, ho);
         for (const OneRec &r : one) p->one_reads[ro[r.read + 1] - ro[r.read] > 255] = true;
+        p->one_max_m = max_m;
     }
     // the first HIP calls (everything above is host work)
     HIPCHK(hipGetDevice(&p->device));
@@ -1412,8 +1434,7 @@ ph_status run_forward(ph_plan *p, const ph_problem *pb, const float *log10_param
         oa.rescued = p->d_one_rescued;
         HIPCHK(hipEventRecord(p->ev[0], s));
         if (log10_params) HIPCHK(launch_prep_params(log10_params, p->nread_bases, p->d_lin, s));
-        for (int lg = 1; lg >= 0; --lg)
-            if (p->one_reads[lg]) HIPCHK(launch_one(sa, oa, lg != 0, (int)p->P, s));
+        HIPCHK(launch_one_pairs(sa, oa, p->one_reads, p->one_max_m, (int)p->P, s));
         HIPCHK(hipEventRecord(p->ev[3], s));
         p->last_stream = s;
         p->stages_recorded = true;
@@ -1746,6 +1767,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     // pairs per bin and per FP64 class, from the host shape
     int64_t bin_pairs[kMaxBins] = {}, class_pairs[kRescueClasses] = {}, bin_cols[kMaxBins] = {};
     bool one_reads[2] = {};  // some read of up to 255 bases, some longer one
+    int one_max_m = 0;
     double cells = 0;
     for (int32_t q = 0; q < nb; ++q) {
         const int64_t H = hb[q + 1] - hb[q];
@@ -1762,6 +1784,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
             bin_cols[b] = std::max(bin_cols[b], nmax);
             class_pairs[rescue_class_of(m)] += H;
             one_reads[m > 255] = true;
+            one_max_m = std::max(one_max_m, m);
             cells += m * cols;
         }
     }
@@ -1829,8 +1852,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
             HIPCHK(launch_na_setup(pb->batch_read_begin, pb->batch_hap_begin, nb, out_off, m2bin, binG, tab, s));
             oa.out_offset = out_off;
         }
-        for (int lg = 1; lg >= 0; --lg)
-            if (one_reads[lg]) HIPCHK(launch_one(sa, oa, lg != 0, (int)P, s));
+        HIPCHK(launch_one_pairs(sa, oa, one_reads, one_max_m, (int)P, s));
         return PH_OK;
     }
     // binning (the set-up kernel writes what a plan uploads at creation;

@@ -173,6 +173,8 @@ struct OneRec {
     int32_t read, hap, out, n;
     int32_t lead, flush;
 };
+// Reads that a launch takes: up to 255 bases, 256 to 1,023, or all of a call's.
+constexpr int kOneShort = 0, kOneLong = 1, kOneUpTo511 = 2, kOneUpTo1023 = 3;
 constexpr int kOneBatches = 256;  // batches whose first pairs travel in the kernel's arguments
 struct OneArgs {
     const OneRec *recs;          // a plan's list, else NULL:
@@ -288,7 +290,7 @@ hipError_t launch_long32(const SweepArgs &a, bool few, int grid, hipStream_t s);
 hipError_t launch_long64(const SweepArgs &a, bool few, bool rescaled, int grid, hipStream_t s);
 int long32_blocks_per_cu(bool few);
 int long64_blocks_per_cu(bool few);
-hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s);
+hipError_t launch_one(const SweepArgs &a, const OneArgs &l, int reads, int pairs, hipStream_t s);
 hipError_t launch_prep_params(const float *lg, int64_t npos, double *lin, hipStream_t s);
 hipError_t launch_validate(const DevProblem &pb, int64_t nread_bases, int64_t nhap_bases,
                            int32_t *bad, hipStream_t s);

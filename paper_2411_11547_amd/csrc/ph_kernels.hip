@@ -1487,19 +1487,21 @@ __global__ __launch_bounds__(64 * NW) void k_long64(SweepArgs A)
 // What bounds a small call is not the GPU's rate but the chain of launches and
 // the length of one tile: a wave issues at most one vector instruction per 5
 // clocks, so a step of 16 rows takes 0.2 us and one tile of 350 columns 77 us,
-// a step of 4 rows 0.06 us.  Reads of up to 255 bases (LONG = false) and of
+// a step of 4 rows 0.06 us.  Reads of up to 255 bases and of
 // 256 to 1023 are two launches, each present only if the shape has such reads:
 // the first keeps the tables (12.9 KB in FP64) and registers of 4 rows per
-// lane, 12 waves per CU.
+// lane, 12 waves per CU.  Smaller calls with both take one launch (C: which
+// reads a launch takes; a pair of others returns at once).
 //
 // The pair of a wave: record blockIdx.x of the plan's list, or (no plan) pair
 // blockIdx.x in output order, found in the first pair of every batch, with
 // the lead of the built-in table's tile (16 lanes x ceil((m + 1) / 16) rows up to
 // 255 bases).
-template <bool LONG, bool V, bool FREE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3))) void k_one(SweepArgs A, OneArgs L)
+template <int C, bool V, bool FREE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == kOneShort ? 3 : C == kOneUpTo511 ? 2 : 1))) void
+k_one(SweepArgs A, OneArgs L)
 {
-    constexpr int KHI = LONG ? 16 : 4;
+    constexpr int KLO = C == kOneLong ? 5 : 1, KHI = C == kOneShort ? 4 : C == kOneUpTo511 ? 8 : 16;
     __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (two codes past the ring are read)
     OneRec one;
     if constexpr (FREE) {
@@ -1520,17 +1522,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3
         one = L.recs[blockIdx.x];
     }
     const int m = (int)(A.pb.read_offset[one.read + 1] - A.pb.read_offset[one.read]);
-    if ((m > 255) != LONG) return;
     const int K = (m + 64) / 64;
+    if (K < KLO || K > KHI) return;
     if constexpr (FREE) {
-        one.lead = LONG ? 0 : (m / ((m + 16) / 16) - m / K) & 31;
-        one.flush = LONG ? 64 : 32;
+        one.lead = m > 255 ? 0 : (m / ((m + 16) / 16) - m / K) & 31;
+        one.flush = m > 255 ? 64 : 32;
     }
     int need = kPairDone;
     switch (K) {
 #define PH_ONE(k) \
     case k: \
-        if constexpr (LONG == (k > 4)) need = sweep_tile<float, 64, k, false, V, true, true>(A, nullptr, 0, 1, lds, one); \
+        if constexpr (k >= KLO && k <= KHI) need = sweep_tile<float, 64, k, false, V, true, true>(A, nullptr, 0, 1, lds, one); \
         break;
         PH_ONE(1) PH_ONE(2) PH_ONE(3) PH_ONE(4) PH_ONE(5) PH_ONE(6) PH_ONE(7) PH_ONE(8)
         PH_ONE(9) PH_ONE(10) PH_ONE(11) PH_ONE(12) PH_ONE(13) PH_ONE(14) PH_ONE(15) PH_ONE(16)
@@ -1542,16 +1544,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONG ? 1 : 3
     // FP64, in the rescue classes' configurations (2, 4, 8 or 16 rows per lane)
     one.lead = 0;
     one.flush = 64;
-    if constexpr (!LONG) {
-        if (m < 128)
-            rescue_pair<2, V>(A, one, need, lds);
-        else
-            rescue_pair<4, V>(A, one, need, lds);
+    if (m < 128) {
+        if constexpr (KLO == 1) rescue_pair<2, V>(A, one, need, lds);
+    } else if (m < 256) {
+        if constexpr (KLO == 1) rescue_pair<4, V>(A, one, need, lds);
+    } else if (m < 512) {
+        if constexpr (KHI >= 8) rescue_pair<8, V>(A, one, need, lds);
     } else {
-        if (m < 512)
-            rescue_pair<8, V>(A, one, need, lds);
-        else
-            rescue_pair<16, V>(A, one, need, lds);
+        if constexpr (KHI == 16) rescue_pair<16, V>(A, one, need, lds);
     }
 }
 
@@ -1916,15 +1916,16 @@ hipError_t launch_long64(const SweepArgs &a, bool few, bool rescaled, int grid, 
                            dim3(few ? 64 * kLongWaves : 64), p, 0, s);
 }
 
-hipError_t launch_one(const SweepArgs &a, const OneArgs &l, bool long_reads, int pairs, hipStream_t s)
+hipError_t launch_one(const SweepArgs &a, const OneArgs &l, int reads, int pairs, hipStream_t s)
 {
-#define PH_LONE(lg, v, f)                                                                    \
-    if (long_reads == lg && (a.viterbi != 0) == v && (l.recs == nullptr) == f) {               \
-        hipLaunchKernelGGL((k_one<lg, v, f>), dim3(pairs), dim3(64), 0, s, a, l);              \
+#define PH_LONE(c, v, f)                                                                     \
+    if (reads == c && (a.viterbi != 0) == v && (l.recs == nullptr) == f) {                     \
+        hipLaunchKernelGGL((k_one<c, v, f>), dim3(pairs), dim3(64), 0, s, a, l);               \
         return hipGetLastError();                                                            \
     }
-    PH_LONE(false, false, false) PH_LONE(true, false, false) PH_LONE(false, true, false) PH_LONE(true, true, false)
-    PH_LONE(false, false, true) PH_LONE(true, false, true)
+#define PH_LONE3(c) PH_LONE(c, false, false) PH_LONE(c, true, false) PH_LONE(c, false, true)
+    PH_LONE3(kOneShort) PH_LONE3(kOneLong) PH_LONE3(kOneUpTo511) PH_LONE3(kOneUpTo1023)
+#undef PH_LONE3
 #undef PH_LONE
     return hipErrorInvalidValue;
 }

@@ -100,3 +100,20 @@ def test_one_pair_limit_of_long_reads(reads, one):
     same((got.cpu().numpy(), st.cpu().numpy()), gpu_forward(prob, force_p=64), "forward")
     assert bool((st == sf).all()) and float((free - got).abs().max()) <= 1e-5
     plan.close()
+
+
+@pytest.mark.parametrize("lens,repeat", [(SHORT + LONG[:5], 2), (SHORT + LONG, 1)])
+def test_one_pair_short_and_long_in_one_launch(lens, repeat):
+    """Reads up to 255 bases beside reads of up to 511, and of up to 1,023, in one
+    launch: the binned launches' results with the same table, FP32 and FP64."""
+    prob = problem(lens, seed=21, repeat=repeat)
+    assert prob.num_pairs <= 768
+    table = dict(tune_table=binding.TUNED_TABLE)
+    bins = dict(table, single_launch=True)  # never the one-pair launch; the same (lanes, rows)
+    one = gpu_forward(prob, **table)
+    check_against_oracle(prob, *one, ref=oracle.forward(prob))
+    same(one, gpu_forward(prob, **bins), "forward")
+    same(gpu_viterbi(prob, **table), gpu_viterbi(prob, **bins), "viterbi")
+    got, st = gpu_forward(prob, rescue_threshold=float("inf"))
+    assert np.all(st != binding.PAIR_FP32)
+    check_against_oracle(prob, got, st)
