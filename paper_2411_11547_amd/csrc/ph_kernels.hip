@@ -362,6 +362,18 @@ __device__ __forceinline__ double get_shared(const double *p)
     return __builtin_bit_cast(double, __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Between a window's progress count and the columns it covers.  Both are read
+// with relaxed device-scope loads, which meet at the point where the caches agree;
+// the count's value is waited for before it is compared, and a wave issues its
+// loads in order, so what is left to rule out is that the compiler moves the
+// columns' loads up: a barrier for the compiler alone.  The writer has its columns
+// arrive (wait_vm0, the same kind of barrier) before it stores its count.  (Acquire
+// and release fences would write back and invalidate whole caches for values that
+// are in none: an acquire fence costs up to 10% with many long pairs and 4% of the
+// Viterbi score, 400 pairs of 4,000-8,000 bases 10.5 -> 11.7 ms, a release fence as
+// well 23.5 ms.)
+__device__ __forceinline__ void after_progress() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
+
 // The boundary row between two windows of a long read.  Rescaled states: the
 // sums X and Y of the next window's first row (FP32: a float2 per column; FP64:
 // two rows of doubles); plain states (FP64): M, I and D, three rows.  A
@@ -1038,6 +1050,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             while ((seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(prog - 1, __ATOMIC_RELAXED,
                                                                             __HIP_MEMORY_SCOPE_AGENT))) < need)
                 __builtin_amdgcn_s_sleep(1);
+            after_progress();
             bnd.none(0);
             if (j >= 1 && j <= n) bnd.fetch(j);
         } else {
@@ -1049,6 +1062,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             if (seen >= __builtin_amdgcn_readfirstlane(min(n, s + 2 * CH - lead))) {
                 const int j = s + CH + 1 + t - lead;
                 early = true;
+                after_progress();
                 bnd.none(0);
                 if (j >= 1 && j <= n) bnd.fetch(j);
             }
