@@ -13,8 +13,8 @@
 //      parallel branches (Section III-C runs one kernel per index list on its
 //      own stream);
 //   4. the FP64 sweep over the pairs whose FP32 sum fell below the rescue
-//      threshold, one persistent launch for reads of up to 255 bases and one per
-//      longer class.
+//      threshold, one persistent launch for reads of up to 255 bases, one for
+//      those of up to 511 and two for longer ones.
 // The FP32 launches are captured once into a HIP graph and replayed while the
 // problem and output pointers stay the same.  Small calls are one launch (k_one).
 #include <stdarg.h>
@@ -104,7 +104,7 @@ int rescue_class_of(int m) { return m < 128 ? 0 : m < 256 ? 1 : m < 512 ? 2 : 3;
 // pairs of the classes that a rescue launch sweeps
 int64_t rescue_pairs(const int64_t *class_pairs, int group)
 {
-    return group == 0 ? class_pairs[0] + class_pairs[1] : class_pairs[group + 1];
+    return group == 0 ? class_pairs[0] + class_pairs[1] : class_pairs[std::min(group + 1, 3)];
 }
 
 // The library's own bin table, shortest reads first: 16 lanes x K rows
@@ -1616,8 +1616,8 @@ ph_status ph_plan_rescued(ph_plan *p, int64_t *count)
     HIPCHK(hipMemcpy(&lc, &p->d_book->long_rescue_count, sizeof(lc), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&lp, &p->d_book->long_plain_count, sizeof(lp), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(&passed, &p->d_book->rescue_passed, sizeof(passed), hipMemcpyDeviceToHost));
-    // pairs of reads longer than 1023 bases (windowed FP64 sweeps), less those
-    // the rescaled sweep passed on (counted twice), plus both sets of queues
+    // pairs of reads longer than 1023 bases (windowed FP64 sweeps) and both sets of
+    // queues, less those that a rescaled sweep passed on (counted twice)
     *count = (int64_t)lc + lp - passed;
     for (int i = 0; i < kRescueQueues; ++i) *count += c[i];
     return PH_OK;

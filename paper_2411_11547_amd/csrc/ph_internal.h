@@ -27,11 +27,13 @@ constexpr int kBuckets = 128;            // haplotype-length buckets per bin
 constexpr int kMaxKeys = kMaxBins * kBuckets;
 constexpr int kMaxReadLen = 1023;        // 64 lanes x 16 rows minus the absorbing row
 constexpr int kRescueClasses = 4;        // FP64 sweep: 64 lanes x {2, 4, 8, 16} rows
-constexpr int kRescueGroups = 3;         // its launches: classes 0 and 1, class 2, class 3
+// its launches: classes 0 and 1, class 2, class 3 with rescaled states, then plain
+constexpr int kRescueGroups = 4, kRescueRescaled = 2;
 // FP64 queues: [rescaled-state FP64 sweep | plain-state FP64 sweep] x class.
 // The FP32 sweep queues a pair that leaves the FP32 range into the first
 // set, one with a row outside the rescaled states into the second; what leaves
-// the rescaled FP64 sweep's own range is redone in plain states by its wave.
+// the rescaled FP64 sweep's own range is redone in plain states by its wave, with 16
+// rows per lane passed on to the second set.
 constexpr int kRescueQueues = 2 * kRescueClasses;
 // Longer reads run in windows of 64 K rows (64 lanes x K rows): the window's
 // top boundary row comes from memory, its bottom row goes back there.  K by the number of long pairs
@@ -106,7 +108,7 @@ struct Book {
     int32_t bin_counter[kMaxBins];         // FP32 sweep work cursor of every bin
     int32_t rescue_count[kRescueQueues];   // FP64 queue lengths
     int32_t rescue_counter[kRescueQueues]; // FP64 sweep work cursors
-    int32_t rescue_passed;                 // long pairs the rescaled FP64 sweep passed on
+    int32_t rescue_passed;                 // pairs that a rescaled FP64 sweep passed on to a plain queue
     int32_t long_rescue_count;             // FP64 queues of long pairs: rescaled states,
     int32_t long_plain_count;              // plain states
     unsigned long long long_next;          // work cursors of the windowed sweeps: FP32,

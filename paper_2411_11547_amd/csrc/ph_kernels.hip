@@ -1117,8 +1117,11 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             // many): 53 long pairs 3.34 -> 2.92 ms, 360 pairs without a plan
             // 36.8 -> 31.6 us.  Steps of one or two rows are shorter than a read
             // takes: codes three steps ahead there (32 pairs of 2 rows 22.3 ->
-            // 21.0 us; with 3 or 4 rows 31.7 -> 33.2).
-            constexpr bool EARLY = W || S;
+            // 21.0 us; with 3 or 4 rows 31.7 -> 33.2).  FP64 with 16 rows has no
+            // registers for it, nor for a second place that flushes (FP64 sums
+            // need no grouping).
+            constexpr bool EARLY = W || (S && (sizeof(T) == 4 || K <= 8));
+            constexpr bool GROUPED = S && sizeof(T) == 4;
             constexpr int AHEAD = S && sizeof(T) == 4 && K <= 2 ? 3 : 2;
             uint32_t code = EARLY ? hv[1] : 0;  // of the next step
             uint32_t code2 = AHEAD == 3 ? hv[2] : 0;  // and of the one after it
@@ -1132,7 +1135,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
             }
             for (;;) {
                 const int stop = (CHN && rs_next - s0 < cnt) ? rs_next - s0
-                                 : (S && u == 0 && one.flush < cnt) ? one.flush : cnt;
+                                 : (GROUPED && u == 0 && one.flush < cnt) ? one.flush : cnt;
                 for (; u < stop; u += 2) {
                     load_lam<T, P, K>(lb, ebase_lane + (EARLY ? code : hv[u + 1]));
                     if constexpr (EARLY) code = hv[u + AHEAD];
@@ -1155,7 +1158,7 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
                 }
                 if (u >= cnt) break;
                 if constexpr (CHN) chain_clear();
-                if constexpr (S) flush_row();
+                if constexpr (GROUPED) flush_row();
             }
             flush_row();
         } else {
@@ -1395,34 +1398,49 @@ __device__ __forceinline__ void rescue_pair(const SweepArgs &A, const OneRec &on
     if (need == kPairPlain64) sweep_tile<double, 64, K, false, V, false, true>(A, nullptr, 0, 1, lds, one);
 }
 
-// FP64 sweeps over the rescue queues of the read-length classes C0 .. C1, both
-// queues of a class.  (A launch per class and queue cost 36 us each with the
-// queues empty: 0.19 ms of the mixed batch's call.  Classes of up to 255 bases
-// share the LDS and registers of 4 rows per lane, 12 waves per CU; the longer
-// classes' tables would take that from them.)
-template <int K, bool V>
+// FP64 sweeps over the rescue queues Q0 .. Q1 (0: rescaled states, 1: plain) of
+// the read-length classes C0 .. C1.  (A launch per class and queue cost 36 us each
+// with the queues empty: 0.19 ms of the mixed batch's call.  Classes of up to 255
+// bases share the LDS and registers of 4 rows per lane, 12 waves per CU; the longer
+// classes' tables would take that from them.)  With 16 rows per lane the two sweeps
+// in one kernel spill: each has its own there, and a pair that the first leaves
+// goes to the second's queue (20,000 pairs of 600 bases, all redone: 7.11 -> 5.63
+// ms, of 700-1,000 bases 11.96 -> 9.64).
+template <int K, bool V, int Q0, int Q1>
 __device__ __forceinline__ void rescue_class(const SweepArgs &A, int cls, char *lds)
 {
     Book *bk = A.book;
-    for (int plain = V ? 1 : 0; plain < 2; ++plain) {
+    for (int plain = V ? 1 : Q0; plain <= Q1; ++plain) {
         const int q = plain * kRescueClasses + cls;
         const int count = bk->rescue_count[q];
         const int32_t *list = A.rescue_list + q * A.rescue_stride;
         if (count == 0) continue;
         for (int i = next_tile(&bk->rescue_counter[q]); i < count; i = next_tile(&bk->rescue_counter[q])) {
             const PairRec r = A.recs[list[i]];
-            rescue_pair<K, V>(A, OneRec{r.read, r.hap, r.out, r.n, 0, 64}, plain ? kPairPlain64 : kPairHat64, lds);
+            const OneRec one{r.read, r.hap, r.out, r.n, 0, 64};
+            if constexpr (Q1 == 0) {
+                const int need = sweep_tile<double, 64, K, false, V, true, true>(A, nullptr, 0, 1, lds, one);
+                if (need == kPairPlain64 && threadIdx.x == 0) {
+                    const int slot = atomicAdd(&bk->rescue_count[kRescueClasses + cls], 1);
+                    A.rescue_list[(kRescueClasses + cls) * A.rescue_stride + slot] = list[i];
+                    atomicAdd(&bk->rescue_passed, 1);
+                }
+            } else if constexpr (Q0 == 1) {
+                sweep_tile<double, 64, K, false, V, false, true>(A, nullptr, 0, 1, lds, one);
+            } else {
+                rescue_pair<K, V>(A, one, plain ? kPairPlain64 : kPairHat64, lds);
+            }
         }
     }
 }
 
-template <int C0, int C1, bool V>
+template <int C0, int C1, bool V, int Q0 = 0, int Q1 = 1>
 __global__ __launch_bounds__(64) void k_rescue(SweepArgs A)
 {
     constexpr int KHI = 2 << C1;
     __shared__ __attribute__((aligned(16))) char lds[Cfg<double, 64, KHI>::LDS_BYTES + 16];  // (two codes past the ring are read)
-    rescue_class<KHI, V>(A, C1, lds);
-    if constexpr (C0 < C1) rescue_class<(2 << C0), V>(A, C0, lds);
+    rescue_class<KHI, V, Q0, Q1>(A, C1, lds);
+    if constexpr (C0 < C1) rescue_class<(2 << C0), V, Q0, Q1>(A, C0, lds);
 }
 
 // Windowed sweeps of reads longer than kMaxReadLen, all windows of all pairs
@@ -1882,17 +1900,19 @@ hipError_t launch_plain32(const SweepArgs &a_in, int K, int grid, hipStream_t s)
 
 static const void *rescue_kernel(int group, bool viterbi)
 {
-    if (viterbi)
-        return group == 0 ? (const void *)k_rescue<0, 1, true>
-               : group == 1 ? (const void *)k_rescue<2, 2, true> : (const void *)k_rescue<3, 3, true>;
-    return group == 0 ? (const void *)k_rescue<0, 1, false>
-           : group == 1 ? (const void *)k_rescue<2, 2, false> : (const void *)k_rescue<3, 3, false>;
+    switch (group) {
+    case 0: return viterbi ? (const void *)k_rescue<0, 1, true> : (const void *)k_rescue<0, 1, false>;
+    case 1: return viterbi ? (const void *)k_rescue<2, 2, true> : (const void *)k_rescue<2, 2, false>;
+    case 2: return (const void *)k_rescue<3, 3, false, 0, 0>;
+    }
+    return viterbi ? (const void *)k_rescue<3, 3, true, 1, 1> : (const void *)k_rescue<3, 3, false, 1, 1>;
 }
 
 hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s)
 {
     SweepArgs b = a;
     b.mode = kModeRescue;
+    if (b.viterbi && group == kRescueRescaled) return hipSuccess;  // the max-product score uses the plain queues only
     void *p[] = {&b};
     return hipLaunchKernel(rescue_kernel(group, b.viterbi != 0), dim3(grid), dim3(64), p, 0, s);
 }
