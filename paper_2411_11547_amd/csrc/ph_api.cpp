@@ -1107,7 +1107,8 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
         }
     }
     for (int g = 0; g < kRescueGroups; ++g)
-        p->rescue_grid[g] = (int)std::min<int64_t>(rescue_pairs(p->class_pairs, g), (int64_t)p->cus * rescue_blocks_per_cu(g));
+        p->rescue_grid[g] = (int)std::min<int64_t>(rescue_pairs(p->class_pairs, g),
+                                                   (int64_t)p->cus * rescue_blocks_per_cu(g, !p->class_pairs[1]));
     p->plain_K = (max_m + 1 + 63) / 64;
     if (p->plain_K < 1) p->plain_K = 1;
     p->plain_grid = (int)std::min<int64_t>(std::max<int64_t>(P, 1), (int64_t)p->cus * plain32_blocks_per_cu(p->plain_K));
@@ -1307,7 +1308,7 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
         }
     } else if (!p->opts.plain) {
         for (int g = 0; g < kRescueGroups; ++g)
-            if (p->rescue_grid[g]) HIPCHK(launch_rescue(sa, g, p->rescue_grid[g], s));
+            if (p->rescue_grid[g]) HIPCHK(launch_rescue(sa, g, !p->class_pairs[1], p->rescue_grid[g], s));
         if (p->long_pairs) {
             SweepArgs la = sa;
             la.bnd = p->d_bnd64;
@@ -1668,7 +1669,7 @@ struct NaDevice {
     unsigned char *base = nullptr;  // device address of `scratch` on this device
     int cus = 0;
     int fwd32_cap[kMaxBins] = {};   // persistent grid cap of each built-in bin (bin order)
-    int rescue_cap[kRescueGroups] = {};
+    int rescue_cap[kRescueGroups][2] = {};  // [1: no read of 128 to 255 bases]
 };
 
 std::mutex g_na_mu;
@@ -1692,7 +1693,8 @@ ph_status na_device_setup(int dev, NaDevice *&out)
             const TuneEntry &e = g_na_table[g_na_bins - 1 - b];
             d.fwd32_cap[b] = d.cus * std::max(1, fwd32_blocks_per_cu(e.P, e.K));
         }
-        for (int g = 0; g < kRescueGroups; ++g) d.rescue_cap[g] = d.cus * std::max(1, rescue_blocks_per_cu(g));
+        for (int g = 0; g < kRescueGroups; ++g)
+            for (int u = 0; u < 2; ++u) d.rescue_cap[g][u] = d.cus * std::max(1, rescue_blocks_per_cu(g, u));
         d.base = (unsigned char *)ptr;
         d.ready = true;
     }
@@ -1887,7 +1889,9 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     }
     for (int g = 0; g < kRescueGroups; ++g) {
         const int64_t pairs = rescue_pairs(class_pairs, g);
-        if (pairs) HIPCHK(launch_rescue(sa, g, (int)std::min<int64_t>(pairs, d->rescue_cap[g]), s));
+        const bool upto127 = !class_pairs[1];
+        if (pairs)
+            HIPCHK(launch_rescue(sa, g, upto127, (int)std::min<int64_t>(pairs, d->rescue_cap[g][upto127]), s));
     }
     return PH_OK;
 }

@@ -287,7 +287,8 @@ hipError_t launch_plain32(const SweepArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_fwd32_single(const SweepArgs &a, int grid, hipStream_t s);
 int fwd32_single_blocks_per_cu();
 bool single_supported(int P, int K);
-hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s);
+// upto127: no read of 128 to 255 bases (group 0)
+hipError_t launch_rescue(const SweepArgs &a, int group, bool upto127, int grid, hipStream_t s);
 hipError_t launch_long32(const SweepArgs &a, bool few, int grid, hipStream_t s);
 hipError_t launch_long64(const SweepArgs &a, bool few, bool rescaled, int grid, hipStream_t s);
 int long32_blocks_per_cu(bool few);
@@ -302,7 +303,7 @@ hipError_t launch_prepare(Book *book, const Book *image, const int64_t *hap_offs
 hipError_t launch_na_setup(const int32_t *rb, const int32_t *hb, int32_t nb, int64_t *out_offset,
                            int16_t *m2bin, int32_t *bin_G, const BinTable &t, hipStream_t s);
 int fwd32_blocks_per_cu(int P, int K);
-int rescue_blocks_per_cu(int group);
+int rescue_blocks_per_cu(int group, bool upto127);
 int plain32_blocks_per_cu(int K);
 bool fwd32_supported(int P, int K);
 

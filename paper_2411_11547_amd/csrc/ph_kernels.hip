@@ -1401,9 +1401,11 @@ __device__ __forceinline__ void rescue_pair(const SweepArgs &A, const OneRec &on
 // FP64 sweeps over the rescue queues Q0 .. Q1 (0: rescaled states, 1: plain) of
 // the read-length classes C0 .. C1.  (A launch per class and queue cost 36 us each
 // with the queues empty: 0.19 ms of the mixed batch's call.  Classes of up to 255
-// bases share the LDS and registers of 4 rows per lane, 12 waves per CU; the longer
-// classes' tables would take that from them.)  With 16 rows per lane the two sweeps
-// in one kernel spill: each has its own there, and a pair that the first leaves
+// bases share the LDS and registers of 4 rows per lane, 12 waves per CU, unless a
+// call has none of 128 to 255: 2 rows leave room for 16 (150,000 pairs of 127
+// bases, all redone: 4.05 -> 3.95 ms, Viterbi of 60-120 bases 5.17 -> 4.97; a launch
+// for each class would cost calls with both 8 us); the longer classes' tables would take
+// that from them.)  With 16 rows per lane the two sweeps in one kernel spill: each has its own there, and a pair that the first leaves
 // goes to the second's queue (20,000 pairs of 600 bases, all redone: 7.11 -> 5.63
 // ms, of 700-1,000 bases 11.96 -> 9.64).
 template <int K, bool V, int Q0, int Q1>
@@ -1898,23 +1900,25 @@ hipError_t launch_plain32(const SweepArgs &a_in, int K, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-static const void *rescue_kernel(int group, bool viterbi)
+static const void *rescue_kernel(int group, bool upto127, bool viterbi)
 {
     switch (group) {
-    case 0: return viterbi ? (const void *)k_rescue<0, 1, true> : (const void *)k_rescue<0, 1, false>;
+    case 0:
+        if (upto127) return viterbi ? (const void *)k_rescue<0, 0, true> : (const void *)k_rescue<0, 0, false>;
+        return viterbi ? (const void *)k_rescue<0, 1, true> : (const void *)k_rescue<0, 1, false>;
     case 1: return viterbi ? (const void *)k_rescue<2, 2, true> : (const void *)k_rescue<2, 2, false>;
     case 2: return (const void *)k_rescue<3, 3, false, 0, 0>;
     }
     return viterbi ? (const void *)k_rescue<3, 3, true, 1, 1> : (const void *)k_rescue<3, 3, false, 1, 1>;
 }
 
-hipError_t launch_rescue(const SweepArgs &a, int group, int grid, hipStream_t s)
+hipError_t launch_rescue(const SweepArgs &a, int group, bool upto127, int grid, hipStream_t s)
 {
     SweepArgs b = a;
     b.mode = kModeRescue;
     if (b.viterbi && group == kRescueRescaled) return hipSuccess;  // the max-product score uses the plain queues only
     void *p[] = {&b};
-    return hipLaunchKernel(rescue_kernel(group, b.viterbi != 0), dim3(grid), dim3(64), p, 0, s);
+    return hipLaunchKernel(rescue_kernel(group, upto127, b.viterbi != 0), dim3(grid), dim3(64), p, 0, s);
 }
 
 // few (4 rows per lane in FP32) or many long pairs: the kernels and their waves per workgroup
@@ -2014,6 +2018,6 @@ int plain32_blocks_per_cu(int K)
 int long32_blocks_per_cu(bool few) { return occupancy(long32_kernel(few, false), few ? 64 * kLongWaves : 64); }
 int long64_blocks_per_cu(bool few) { return occupancy(long64_kernel(few, false, false), few ? 64 * kLongWaves : 64); }
 
-int rescue_blocks_per_cu(int group) { return occupancy(rescue_kernel(group, false)); }
+int rescue_blocks_per_cu(int group, bool upto127) { return occupancy(rescue_kernel(group, upto127, false)); }
 
 }  // namespace ph

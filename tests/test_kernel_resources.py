@@ -55,3 +55,14 @@ def test_rescaled_fp64_sweeps_do_not_spill():
     plain16 = "k_rescueILi3ELi3ELb0ELi1ELi1E"
     spilled = {n: m[".vgpr_spill_count"] for n, m in found.items() if m[".vgpr_spill_count"] and plain16 not in n}
     assert not spilled, spilled
+
+
+def test_fp64_sweep_of_short_reads_has_its_own_tables():
+    """Reads of up to 127 bases alone: 2 rows per lane, 16 waves per CU, of 160 KB of
+    LDS and 512 registers in each of four SIMDs."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    found = {n: m for n, m in kernels(LIB).items() if "k_rescueILi0ELi0E" in n}
+    assert len(found) == 2
+    for n, m in found.items():
+        assert 16 * m[".group_segment_fixed_size"] <= 160 * 1024 and 4 * m[".vgpr_count"] <= 512, n
