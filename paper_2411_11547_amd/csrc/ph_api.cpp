@@ -312,15 +312,39 @@ struct ph_plan {
 
 namespace {
 
+// (a graph that may still run is waited for before it goes)
+void drop_stage_graph(ph_plan *p, int v)
+{
+    if (p->exec[v]) {
+        if (p->stages_recorded) (void)hipEventSynchronize(p->ev[3]);
+        (void)hipGraphExecDestroy(p->exec[v]);
+        p->exec[v] = nullptr;
+    }
+    if (p->graph[v]) { (void)hipGraphDestroy(p->graph[v]); p->graph[v] = nullptr; }
+    p->graph_key[v].clear();
+}
+
+void drop_adjoint_graph(ph_plan *p)
+{
+    if (p->adj_exec) {
+        if (p->adj_recorded) (void)hipEventSynchronize(p->ev_adj[1]);
+        (void)hipGraphExecDestroy(p->adj_exec);
+        p->adj_exec = nullptr;
+    }
+    if (p->adj_graph) { (void)hipGraphDestroy(p->adj_graph); p->adj_graph = nullptr; }
+    p->adj_graph_key.clear();
+}
+
+void drop_graphs(ph_plan *p)
+{
+    for (int v = 0; v < 2; ++v) drop_stage_graph(p, v);
+    drop_adjoint_graph(p);
+}
+
 void free_plan(ph_plan *p)
 {
     if (!p) return;
-    for (int v = 0; v < 2; ++v) {
-        if (p->exec[v]) (void)hipGraphExecDestroy(p->exec[v]);
-        if (p->graph[v]) (void)hipGraphDestroy(p->graph[v]);
-    }
-    if (p->adj_exec) (void)hipGraphExecDestroy(p->adj_exec);
-    if (p->adj_graph) (void)hipGraphDestroy(p->adj_graph);
+    drop_graphs(p);
     void *bufs[] = {p->d_out_offset, p->d_m2bin, p->d_bin_G, p->d_hist, p->d_recs, p->d_book, p->d_bad, p->d_rescue, p->d_lin,
                     p->d_book_img, p->d_chain_codes, p->d_one, p->d_one_rescued,
                     p->d_bnd32, p->d_bnd64, p->d_long_rescue, p->d_progress,
@@ -1320,35 +1344,6 @@ ph_status enqueue_stage(ph_plan *p, int stage, const ph_problem *pb, const float
         }
     }
     return PH_OK;
-}
-
-// (a graph that may still run is waited for before it goes)
-void drop_stage_graph(ph_plan *p, int v)
-{
-    if (p->exec[v]) {
-        if (p->stages_recorded) (void)hipEventSynchronize(p->ev[3]);
-        (void)hipGraphExecDestroy(p->exec[v]);
-        p->exec[v] = nullptr;
-    }
-    if (p->graph[v]) { (void)hipGraphDestroy(p->graph[v]); p->graph[v] = nullptr; }
-    p->graph_key[v].clear();
-}
-
-void drop_adjoint_graph(ph_plan *p)
-{
-    if (p->adj_exec) {
-        if (p->adj_recorded) (void)hipEventSynchronize(p->ev_adj[1]);
-        (void)hipGraphExecDestroy(p->adj_exec);
-        p->adj_exec = nullptr;
-    }
-    if (p->adj_graph) { (void)hipGraphDestroy(p->adj_graph); p->adj_graph = nullptr; }
-    p->adj_graph_key.clear();
-}
-
-void drop_graphs(ph_plan *p)
-{
-    for (int v = 0; v < 2; ++v) drop_stage_graph(p, v);
-    drop_adjoint_graph(p);
 }
 
 // The adjoint's launch sequence: parameter preparation, zeroing of the
