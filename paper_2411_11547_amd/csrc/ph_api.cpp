@@ -15,8 +15,8 @@
 //   4. the FP64 sweep over the pairs whose FP32 sum fell below the rescue
 //      threshold, one persistent launch for reads of up to 255 bases, one for
 //      those of up to 511 and two for longer ones.
-// The FP32 launches are captured once into a HIP graph and replayed while the
-// problem and output pointers stay the same.  Small calls are one launch (k_one).
+// The FP32 launches are captured into a HIP graph when the problem and output
+// pointers come again and replayed while they stay.  Small calls are one launch (k_one).
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -261,10 +261,15 @@ struct ph_plan {
     hipEvent_t ev[kStageEvents] = {};
     bool stages_recorded = false;
 
-    // FP32 stage graphs of the forward ([0]) and of the Viterbi score ([1])
-    hipGraph_t graph[2] = {};
-    hipGraphExec_t exec[2] = {};
-    std::vector<const void *> graph_key[2];
+    // Captured launches: they hold for the pointers that they were captured with.
+    struct Captured {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+        std::vector<const void *> key, last;  // pointers of the graph, of the last call
+        hipEvent_t ran = nullptr;             // after the graph's last launch, once marked
+        bool marked = false;
+    };
+    Captured fwd[2];  // the FP32 stage of the forward ([0]) and of the Viterbi score ([1])
 
     hipStream_t last_stream = nullptr;
     bool forward_done = false;
@@ -305,40 +310,27 @@ struct ph_plan {
     int k64_max = 1, k64_only = 0;  // the FP64 pass's largest class, and the only one (0: several)
     hipEvent_t ev_adj[2] = {};
     bool adj_recorded = false;
-    hipGraph_t adj_graph = nullptr;
-    hipGraphExec_t adj_exec = nullptr;
-    std::vector<const void *> adj_graph_key;
+    Captured adj;
 };
 
 namespace {
 
+void drop_captured(ph_plan::Captured &c)
+{
+    if (c.exec) (void)hipGraphExecDestroy(c.exec);
+    if (c.graph) (void)hipGraphDestroy(c.graph);
+    c.exec = nullptr;
+    c.graph = nullptr;
+    c.key.clear();
+    c.marked = false;
+}
+
 // (a graph that may still run is waited for before it goes)
-void drop_stage_graph(ph_plan *p, int v)
-{
-    if (p->exec[v]) {
-        if (p->stages_recorded) (void)hipEventSynchronize(p->ev[3]);
-        (void)hipGraphExecDestroy(p->exec[v]);
-        p->exec[v] = nullptr;
-    }
-    if (p->graph[v]) { (void)hipGraphDestroy(p->graph[v]); p->graph[v] = nullptr; }
-    p->graph_key[v].clear();
-}
-
-void drop_adjoint_graph(ph_plan *p)
-{
-    if (p->adj_exec) {
-        if (p->adj_recorded) (void)hipEventSynchronize(p->ev_adj[1]);
-        (void)hipGraphExecDestroy(p->adj_exec);
-        p->adj_exec = nullptr;
-    }
-    if (p->adj_graph) { (void)hipGraphDestroy(p->adj_graph); p->adj_graph = nullptr; }
-    p->adj_graph_key.clear();
-}
-
 void drop_graphs(ph_plan *p)
 {
-    for (int v = 0; v < 2; ++v) drop_stage_graph(p, v);
-    drop_adjoint_graph(p);
+    if (p->stages_recorded && (p->fwd[0].exec || p->fwd[1].exec)) (void)hipEventSynchronize(p->ev[3]);
+    if (p->adj_recorded && p->adj.exec) (void)hipEventSynchronize(p->ev_adj[1]);
+    for (auto *c : {&p->fwd[0], &p->fwd[1], &p->adj}) drop_captured(*c);
 }
 
 void free_plan(ph_plan *p)
@@ -351,6 +343,8 @@ void free_plan(ph_plan *p)
                     p->d_adj_recs, p->d_adj_tiles, p->d_ws, p->d_adj_ctr, p->d_q64, p->d_ws64, p->d_grad_pair, p->d_red};
     for (auto &e : p->ev_adj)
         if (e) (void)hipEventDestroy(e);
+    for (auto *c : {&p->fwd[0], &p->fwd[1], &p->adj})
+        if (c->ran) (void)hipEventDestroy(c->ran);
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     for (auto &e : p->ev)
@@ -1180,6 +1174,7 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
     for (auto &e : p->join) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     for (auto &e : p->ev) HIPCHK(hipEventCreate(&e));
     for (auto &e : p->ev_adj) HIPCHK(hipEventCreate(&e));
+    for (auto *c : {&p->fwd[0], &p->fwd[1], &p->adj}) HIPCHK(hipEventCreateWithFlags(&c->ran, hipEventDisableTiming));
     if (nb > 0) {
         p->h_rb.assign(rb, rb + nb + 1);
         p->h_hb.assign(hb, hb + nb + 1);
@@ -1395,6 +1390,60 @@ ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_
     return PH_OK;
 }
 
+// Whether a call on stream s replays captured launches (graph) or enqueues them
+// itself.  A set of pointers is captured when it comes twice in a row: calls whose
+// buffers alternate, as autograd's do, would capture and instantiate a graph each
+// (0.3 ms and more) and wait for the one that it takes the place of.  That one is
+// let go only after its last launch has run, which no call waits for: until then
+// calls enqueue their launches themselves.
+template <typename F>
+ph_status use_captured(ph_plan *p, ph_plan::Captured &c, std::vector<const void *> key, hipStream_t s, bool &graph,
+                       F enqueue)
+{
+    graph = false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (!p->opts.use_graph) return PH_OK;
+    HIPCHK(hipStreamIsCapturing(s, &cs));
+    if (cs != hipStreamCaptureStatusNone) return PH_OK;  // the caller's own graph takes the launches
+    const bool again = key == c.last;
+    c.last = key;
+    if (c.exec && key == c.key) {
+        c.marked = false;
+        graph = true;
+        return PH_OK;
+    }
+    if (c.exec) {
+        if (!c.marked) HIPCHK(hipEventRecord(c.ran, s));
+        c.marked = true;
+        if (!again) return PH_OK;
+        if (hipEventQuery(c.ran) != hipSuccess) {
+            (void)hipGetLastError();  // (not ready: no error)
+            return PH_OK;
+        }
+        drop_captured(c);
+    }
+    if (!again) return PH_OK;
+    HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
+    const ph_status st = enqueue(p->cap);
+    hipGraph_t g = nullptr;
+    const hipError_t e = hipStreamEndCapture(p->cap, &g);
+    if (st != PH_OK) {
+        if (g) (void)hipGraphDestroy(g);
+        return st;
+    }
+    if (e != hipSuccess) return fail(PH_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+    c.graph = g;
+    const hipError_t ei = hipGraphInstantiate(&c.exec, g, nullptr, nullptr, 0);
+    if (ei != hipSuccess) {
+        c.exec = nullptr;
+        drop_captured(c);
+        return fail(PH_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(ei));
+    }
+    c.key = std::move(key);
+    graph = true;
+    return PH_OK;
+}
+
 // The forward call and the Viterbi call: the same three stages, with the
 // sum (forward) or the maximum (Viterbi) in the sweeps, each mode with its
 // own stage graphs.
@@ -1441,34 +1490,19 @@ ph_status run_forward(ph_plan *p, const ph_problem *pb, const float *log10_param
     // The FP32 stage (one launch per bin, on side streams) is captured into a
     // graph; the stages before and after it are a launch or two.  HIP events
     // recorded on the caller's stream around the stages time them.
-    const bool graph = p->opts.use_graph != 0;
-    if (graph) {
-        std::vector<const void *> key = {pb->batch_read_begin, pb->batch_hap_begin, pb->read_offset,
-                                         pb->read_bases, pb->base_qual, pb->ins_qual, pb->del_qual,
-                                         pb->gcp_qual, pb->hap_offset, pb->hap_bases, log10_params,
-                                         out_log10L, out_status};
-        if (!p->exec[v] || key != p->graph_key[v]) {
-            drop_stage_graph(p, v);
-            HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
-            st = enqueue_stage(p, 1, pb, log10_params, out_log10L, out_status, p->cap, viterbi);
-            hipGraph_t g = nullptr;
-            hipError_t e = hipStreamEndCapture(p->cap, &g);
-            if (st != PH_OK) { if (g) (void)hipGraphDestroy(g); return st; }
-            if (e != hipSuccess) return fail(PH_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-            p->graph[v] = g;
-            e = hipGraphInstantiate(&p->exec[v], g, nullptr, nullptr, 0);
-            if (e != hipSuccess) {
-                p->exec[v] = nullptr;
-                drop_stage_graph(p, v);
-                return fail(PH_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-            }
-            p->graph_key[v] = key;
-        }
-    }
+    bool graph = false;
+    st = use_captured(p, p->fwd[v],
+                      {pb->batch_read_begin, pb->batch_hap_begin, pb->read_offset, pb->read_bases, pb->base_qual,
+                       pb->ins_qual, pb->del_qual, pb->gcp_qual, pb->hap_offset, pb->hap_bases, log10_params,
+                       out_log10L, out_status},
+                      s, graph, [&](hipStream_t cs) {
+                          return enqueue_stage(p, 1, pb, log10_params, out_log10L, out_status, cs, viterbi);
+                      });
+    if (st != PH_OK) return st;
     for (int stage = 0; stage < 3; ++stage) {
         HIPCHK(hipEventRecord(p->ev[stage], s));
         if (stage == 1 && graph) {
-            HIPCHK(hipGraphLaunch(p->exec[v], s));
+            HIPCHK(hipGraphLaunch(p->fwd[v].exec, s));
         } else {
             st = enqueue_stage(p, stage, pb, log10_params, out_log10L, out_status, s, viterbi);
             if (st != PH_OK) return st;
@@ -1518,32 +1552,18 @@ ph_status ph_backward_batch(ph_plan *p, const ph_problem *pb, const float *log10
         p->lin_cap = p->nread_bases;
         drop_graphs(p);
     }
-    if (p->opts.use_graph) {
-        std::vector<const void *> key = {pb->read_offset, pb->read_bases, pb->base_qual, pb->ins_qual,
-                                         pb->del_qual, pb->gcp_qual, pb->hap_offset, pb->hap_bases,
-                                         log10_params, grad_log10L, grad_params};
-        if (!p->adj_exec || key != p->adj_graph_key) {
-            drop_adjoint_graph(p);
-            HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
-            st = enqueue_backward(p, pb, log10_params, grad_log10L, grad_params, p->cap);
-            hipGraph_t g = nullptr;
-            hipError_t e = hipStreamEndCapture(p->cap, &g);
-            if (st != PH_OK) { if (g) (void)hipGraphDestroy(g); return st; }
-            if (e != hipSuccess) return fail(PH_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-            p->adj_graph = g;
-            e = hipGraphInstantiate(&p->adj_exec, g, nullptr, nullptr, 0);
-            if (e != hipSuccess) {
-                (void)hipGraphDestroy(g);
-                p->adj_graph = nullptr;
-                p->adj_exec = nullptr;
-                return fail(PH_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-            }
-            p->adj_graph_key = key;
-        }
-        HIPCHK(hipEventRecord(p->ev_adj[0], s));
-        HIPCHK(hipGraphLaunch(p->adj_exec, s));
+    bool graph = false;
+    st = use_captured(p, p->adj,
+                      {pb->read_offset, pb->read_bases, pb->base_qual, pb->ins_qual, pb->del_qual, pb->gcp_qual,
+                       pb->hap_offset, pb->hap_bases, log10_params, grad_log10L, grad_params},
+                      s, graph, [&](hipStream_t cs) {
+                          return enqueue_backward(p, pb, log10_params, grad_log10L, grad_params, cs);
+                      });
+    if (st != PH_OK) return st;
+    HIPCHK(hipEventRecord(p->ev_adj[0], s));
+    if (graph) {
+        HIPCHK(hipGraphLaunch(p->adj.exec, s));
     } else {
-        HIPCHK(hipEventRecord(p->ev_adj[0], s));
         st = enqueue_backward(p, pb, log10_params, grad_log10L, grad_params, s);
         if (st != PH_OK) return st;
     }
