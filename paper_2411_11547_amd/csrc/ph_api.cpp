@@ -119,6 +119,9 @@ int builtin_table(TuneEntry *t)
     return n;
 }
 
+// its entry for reads of m bases (1 to 1,023)
+int builtin_entry(int m) { return m < 256 ? m >> 4 : 12 + (m >> 6); }
+
 std::vector<TuneEntry> default_table(int force_p)
 {
     std::vector<TuneEntry> t;
@@ -233,6 +236,7 @@ struct ph_plan {
     // chain tiles; the call copies the book image and writes the chain codes
     std::vector<int64_t> bin_tiles;    // tiles per bin
     std::vector<int64_t> bin_cols;     // columns of each bin's longest tile
+    double binned_ns = 0;              // time that all tiles take a full GPU
     int32_t chain_rec_base = 0;        // records of the lists; FP64 records of chain pairs follow
     bool chain_tiles = false;
     Book *d_book_img = nullptr;
@@ -657,24 +661,54 @@ int choose_chain_cols(const ph_plan *p, int32_t nb, const int32_t *rb, const int
 }
 
 // Which way a call goes: one launch of one-pair tiles (k_one), or the binned
-// launches.  One-pair tiles fill the GPU at 5.7e12 cells a second (rows padded
-// to 64, 64 columns of fill), the binned sweeps compute 7.3e12 cells, but
-// their launches take 0.1 ms and every bin's kernel ends with its longest tile,
-// a single wave that takes 2 ns per vector instruction, about 5.5 K + 10 of them
-// per step.  Measured (forward, us, binned / one-pair): regions of 50-250 x
-// 100-1,000 bases, 16 bins, 3.1e9 cells 1,020-1,330 / 800, 6.1e9 1,719 / 1,451,
-// 1.04e10 2,252 / 2,384; one bin of 150 x 300 bases, 4.7e8 cells 288 / 164,
-// 1.3e9 396 / 406, 3.6e9 659 / 991.  The estimates are within 10% of these.
+// launches.  Both are priced by their tiles, in ns: a step of K rows takes a SIMD
+// 19 + 13 K clocks where the GPU is full (step_ns, of the whole GPU; measured with
+// 150,000 pairs of 10 to 250 bases), a tile alone 2 ns per vector instruction, about
+// 5.5 K + 10 of them per step (tile_ns).
 //
-// Pairs with reads of more than 255 bases hold 41 KB of tables each, three a
+// One-pair tiles take 64 lanes each and 130 steps beside their columns; half of the
+// longest tile adds to their sum.  Binned tiles pad fewer rows and lanes, but their
+// launches take 55 us and 9 more for every further bin (without a plan 45 us, 9 per
+// bin, 4.9 ns a pair, beyond 15,000 pairs 1.5, 6 a batch), single pairs 2.5 ns beside their
+// steps (0.6 in 4 lanes, 1.3 in 8), and every bin's kernel ends with its longest tile: a plan's bins on side
+// streams in turn, otherwise one after the other; the tiles' sum and those ends
+// overlap in part.  13 to 16 rows in 16 lanes run at 2 waves per SIMD.  Measured on
+// 1,001 shapes of 1 to 60 reads and 1 to 20 haplotypes a region, us, binned / one-pair
+// (of a plan; the estimates choose the lesser but where 2 or 3 are given):
+//   10 x 300 bases: 4,500 pairs 62 / 47, 15,000 79 / 113
+//   60 x 300: 15,000 130 / 111, 45,000 227 / 302; 60 x 4,000: 4,500 388 / 362, 15,000
+//   653 / 995; 60 x 150, two haplotypes: 24,800 133 / 109 (binned)
+//   150 x 300: 15,000 204 / 181, 45,000 352 / 500; 150 x 1,000: 4,500 205 / 177,
+//   15,000 384 / 470
+//   100-150 x 1,010, four bins: 12,000 376 / 328; 60-250 x 350, 14 bins: 60,000 738 /
+//   804 (one-pair); 50-250 x 1,000: 15,000 782 / 453, 150,000 3,298 / 4,079
+//   without a plan: 10 x 1,000, 4,500 118 / 99, 15,000 200 / 272; 100 x 1,000, 4,500
+//   183 / 126, 15,000 306 / 351; 50-250 x 1,000, 45,000 2,090 / 1,311
+// 23 of the choices take 5 to 14% longer than the other way, one 22%.
+//
+// Pairs with reads of more than 255 bases hold 50 KB of tables each, three a
 // CU: 768 of them run at once, and what is beyond that waits for a second
 // round, of twice the binned sweeps' length (haplotypes of 350 bases, us,
 // binned / one-pair: 300 bases, 512 pairs 96 / 48, 1,024 101 / 87, 4,096
 // 143 / 235; 500 bases, all redone in FP64, 187 / 120, 215 / 223, 421 / 637;
 // 1,000 bases 523 / 429, 855 / 847, 2,336 / 2,520).
-constexpr double kOneCellsPerNs = 5700, kBinnedCellsPerNs = 7300, kOneNs = 20e3, kBinnedNs = 100e3;
+constexpr double kOneNs = 12e3, kBinnedNs = 55e3, kNextBinNs = 9e3, kSingleNs = 0.16;
+constexpr double kFreeNs = 45e3, kFreePairNs = 4.9, kFreeFurtherNs = 1.5, kFreeBatchNs = 6;  // without a plan
+constexpr int64_t kFreeFurther = 15000;
+constexpr int64_t kOneSteps = 130, kBinnedSteps = 60;  // beside the columns of a tile
 constexpr int64_t kOneLongPairs = 768;
+constexpr double kStepNs = 0.0081, kRowNs = 0.00557;
+double step_ns(int K) { return kStepNs + kRowNs * K; }
 double tile_ns(int64_t cols, int P, int K) { return 2.0 * (double)(cols + P + 2) * (5.5 * K + 10); }
+// the sum of a bin's tiles, which take that many steps
+double bin_ns(double steps, int P, int K) { return steps * step_ns(K) * (P == 16 && K > 12 ? 1.2 : 1.0); }
+// ns is no more than the binned launches take, their tiles' sum and their ends overlapping
+bool within_binned(double ns, double launches, double sum, double ends)
+{
+    const double left = ns - launches;
+    if (left <= std::max(sum, ends)) return true;
+    return left <= sum + ends && left <= std::pow(std::pow(sum, 1.6) + std::pow(ends, 1.6), 1 / 1.6);
+}
 
 // The FP32 work lists of a binned plan (Section III-C), built once from the
 // shape: records of every bin, bin b's range and tiles in the book image.
@@ -777,6 +811,7 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     recs.reserve(pool.size());
     p->bin_tiles.assign(nbins, 0);
     p->bin_cols.assign(nbins, 0);
+    p->binned_ns = 0;
     p->chain_tiles = false;
     int64_t tiles = 0;
     for (int b = 0; b < nbins; ++b) {
@@ -791,6 +826,11 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
         for (const auto *l : {&chain_tiles[b], &singles[b]})
             if (!l->empty()) p->bin_cols[b] = std::max(p->bin_cols[b], l->front().len);
         p->bin_tiles[b] = (int64_t)chain_tiles[b].size() + ((int64_t)singles[b].size() + G - 1) / G;
+        int64_t steps = 0;
+        for (const Tile &t : chain_tiles[b]) steps += t.len + kBinnedSteps;
+        for (size_t k = 0; k < singles[b].size(); k += G) steps += singles[b][k].len + kBinnedSteps;
+        p->binned_ns += bin_ns((double)steps, binP(b), p->table[nbins - 1 - b].K);
+        p->binned_ns += kSingleNs * std::min(binP(b), 16) * (double)singles[b].size();
         p->chain_tiles = p->chain_tiles || !chain_tiles[b].empty();
         tiles += p->bin_tiles[b];
     }
@@ -812,28 +852,33 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     return true;
 }
 
-// Time of the one-pair launch of a shape (infinite: too many pairs of long reads).
-double one_pair_ns(const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho, int32_t nb)
+// Time of the one-pair launch (infinite: too many pairs of long reads): the steps of
+// all tiles, and times their rows per lane; the longest haplotype and read.
+double one_pair_ns(double steps, double row_steps, int64_t n_max, int m_max, int64_t long_pairs)
 {
-    double cells = 0;
-    int64_t long_pairs = 0;
-    for (int32_t q = 0; q < nb; ++q) {
-        int64_t rows = 0, cols = 0, long_reads = 0;
-        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
-            const int64_t m = ro[r + 1] - ro[r];
-            rows += (m + 64) / 64 * 64;
-            long_reads += m > 255;
-        }
-        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) cols += ho[h + 1] - ho[h] + 64;
-        cells += (double)rows * (double)cols;
-        long_pairs += long_reads * (hb[q + 1] - hb[q]);
-    }
-    return long_pairs > kOneLongPairs ? INFINITY : kOneNs + cells / kOneCellsPerNs;
+    if (long_pairs > kOneLongPairs) return INFINITY;
+    return kOneNs + kStepNs * steps + kRowNs * row_steps + 0.5 * tile_ns(n_max, 64, (m_max + 64) >> 6);
 }
 
-// Time of a binned plan's launches: the bins run on side streams in turn.
-double binned_ns(const ph_plan *p)
+// A plan takes the one-pair launch (its bins would run on side streams in turn).
+bool one_pair_plan(const ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho)
 {
+    double steps = 0, row_steps = 0;
+    int64_t long_pairs = 0;
+    for (int32_t q = 0; q < p->nb; ++q) {
+        const int64_t R = rb[q + 1] - rb[q], H = hb[q + 1] - hb[q];
+        int64_t K_sum = 0, long_reads = 0;
+        for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
+            const int m = (int)(ro[r + 1] - ro[r]);
+            K_sum += (m + 64) >> 6;
+            long_reads += m > 255;
+        }
+        const double tile = (double)(ho[hb[q + 1]] - ho[hb[q]] + kOneSteps * H);
+        steps += (double)R * tile;
+        row_steps += (double)K_sum * tile;
+        long_pairs += long_reads * H;
+    }
+    const double one = one_pair_ns(steps, row_steps, p->max_n, p->max_m, long_pairs);
     double stream[kSideStreams] = {};
     const int nbins = (int)p->table.size();
     int next = 0;
@@ -841,12 +886,13 @@ double binned_ns(const ph_plan *p)
         const TuneEntry &e = p->table[nbins - 1 - b];
         if (p->bin_cols[b]) stream[next++ % kSideStreams] += tile_ns(p->bin_cols[b], e.P, e.K);
     }
-    return kBinnedNs + (double)p->cells / kBinnedCellsPerNs + *std::max_element(stream, stream + kSideStreams);
+    return within_binned(one, kBinnedNs + kNextBinNs * (next - 1), p->binned_ns,
+                         *std::max_element(stream, stream + kSideStreams));
 }
 
 // The one-pair launches of a call with reads of up to 255 bases and longer ones.
 // Two launches, one after the other, each take at least one pair's sweep; in one,
-// every pair holds the longer reads' tables (25 KB up to 511 bases, 6 a CU; 41 KB
+// every pair holds the longer reads' tables (25 KB up to 511 bases, 6 a CU; 50 KB
 // beyond, 3 a CU).  One launch wins up to three rounds of 1,536 pairs (reads of
 // 60-300 bases, us, two / one: 200 pairs 93 / 51, 1,900 119 / 80, 4,000 152 /
 // 119), with reads over 511 bases up to the one round of 768 that kOneLongPairs
@@ -1070,7 +1116,7 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
     // small plans (reads of up to 1,023 bases, no option that names a launch)
     std::vector<OneRec> one;
     if (!opts.plain && !opts.force_p && !opts.single_launch && P > 0 && max_m <= kMaxReadLen &&
-        one_pair_ns(rb, hb, ro, ho, nb) <= binned_ns(p.get())) {
+        one_pair_plan(p.get(), rb, hb, ro, ho)) {
         p->one = true;
         one = one_list(p.get(), recs, img, ro, ho);
         for (const OneRec &r : one) p->one_reads[ro[r.read + 1] - ro[r.read] > 255] = true;
@@ -1783,32 +1829,42 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
 
     // pairs per bin and per FP64 class, from the host shape
     int64_t bin_pairs[kMaxBins] = {}, class_pairs[kRescueClasses] = {}, bin_cols[kMaxBins] = {};
-    bool one_reads[2] = {};  // some read of up to 255 bases, some longer one
-    int one_max_m = 0;
-    double cells = 0;
+    int64_t bin_steps[kMaxBins] = {};  // of every pair
+    int64_t steps = 0, row_steps = 0, n_max = 0, long_pairs = 0;  // of one-pair tiles
+    int m_max = 0;
     for (int32_t q = 0; q < nb; ++q) {
-        const int64_t H = hb[q + 1] - hb[q];
-        if (H == 0) continue;
-        int64_t nmax = 0;
-        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) nmax = std::max(nmax, ho[h + 1] - ho[h]);
-        const double cols = (double)(ho[hb[q + 1]] - ho[hb[q]]);
+        const int64_t R = rb[q + 1] - rb[q], H = hb[q + 1] - hb[q], cols = ho[hb[q + 1]] - ho[hb[q]];
+        if (R == 0 || H == 0) continue;
+        int64_t n_longest = 0, K_sum = 0, long_reads = 0;
+        for (int32_t h = hb[q]; h < hb[q + 1]; ++h) n_longest = std::max(n_longest, ho[h + 1] - ho[h]);
         for (int32_t r = rb[q]; r < rb[q + 1]; ++r) {
-            const int m = (int)(ro[r + 1] - ro[r]);
-            int e = 0;
-            while (e < nbins - 1 && g_na_table[e].max_m < m) ++e;
-            const int b = nbins - 1 - e;
+            const int m = (int)(ro[r + 1] - ro[r]), b = nbins - 1 - builtin_entry(m);
             bin_pairs[b] += H;
-            bin_cols[b] = std::max(bin_cols[b], nmax);
+            bin_steps[b] += cols + kBinnedSteps * H;
+            bin_cols[b] = std::max(bin_cols[b], n_longest);
             class_pairs[rescue_class_of(m)] += H;
-            one_reads[m > 255] = true;
-            one_max_m = std::max(one_max_m, m);
-            cells += m * cols;
+            K_sum += (m + 64) >> 6;
+            long_reads += m > 255;
+            m_max = std::max(m_max, m);
         }
+        steps += R * (cols + kOneSteps * H);
+        row_steps += K_sum * (cols + kOneSteps * H);
+        n_max = std::max(n_max, n_longest);
+        long_pairs += long_reads * H;
     }
+    const double one = one_pair_ns((double)steps, (double)row_steps, n_max, m_max, long_pairs);
+    const bool one_reads[2] = {long_pairs < P, long_pairs > 0};  // some read of up to 255 bases, some longer one
     // the binned launches run one after the other here
-    double binned = kBinnedNs + cells / kBinnedCellsPerNs;
-    for (int b = 0; b < nbins; ++b)
-        if (bin_pairs[b]) binned += tile_ns(bin_cols[b], g_na_table[nbins - 1 - b].P, g_na_table[nbins - 1 - b].K);
+    const double few = (double)std::min<int64_t>(P, kFreeFurther);
+    double launches = kFreeNs - kNextBinNs + kFreePairNs * few + kFreeFurtherNs * ((double)P - few) + kFreeBatchNs * nb;
+    double sum = 0, ends = 0;
+    for (int b = 0; b < nbins; ++b) {
+        const TuneEntry &e = g_na_table[nbins - 1 - b];
+        if (!bin_pairs[b]) continue;
+        launches += kNextBinNs;
+        sum += bin_ns((double)bin_steps[b] * e.P / 64, e.P, e.K);
+        ends += tile_ns(bin_cols[b], e.P, e.K);
+    }
 
     unsigned char *base = d->base;
     Book *book = (Book *)(base + kNaBook);
@@ -1850,7 +1906,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
     sa.plain_count = (int32_t)P;
     sa.long_bin = -1;
 
-    if (one_pair_ns(rb, hb, ro, ho, nb) <= binned) {
+    if (within_binned(one, launches, sum, ends)) {
         // a small call: no binning, one pair per wave; the first pair of every
         // batch travels in the kernel's arguments, or is summed up on the
         // device where there are too many batches for that
@@ -1869,7 +1925,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
             HIPCHK(launch_na_setup(pb->batch_read_begin, pb->batch_hap_begin, nb, out_off, m2bin, binG, tab, s));
             oa.out_offset = out_off;
         }
-        HIPCHK(launch_one_pairs(sa, oa, one_reads, one_max_m, (int)P, s));
+        HIPCHK(launch_one_pairs(sa, oa, one_reads, m_max, (int)P, s));
         return PH_OK;
     }
     // binning (the set-up kernel writes what a plan uploads at creation;
