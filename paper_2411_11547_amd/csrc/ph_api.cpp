@@ -32,6 +32,7 @@
 
 #include "../../include/ph.h"
 #include "ph_internal.h"
+#include "ph_rules.h"
 
 using namespace ph;
 
@@ -70,16 +71,6 @@ namespace {
         if (e_ != hipSuccess) return fail(PH_ERR_HIP, "%s: %s", #x, hipGetErrorString(e_)); \
     } while (0)
 
-// One bin of the FP32 sweep: reads up to max_m bases in groups of P lanes x
-// K rows.  A table line may add a haplotype-length split "n_split P2 K2":
-// pairs of that read range whose haplotype has at least n_split bases go to
-// a second bin of P2 x K2 (a table entry that follows its parent, with the
-// same max_m, so that the read-length map never selects it).
-struct TuneEntry {
-    int max_m, P, K;
-    int n_split = 0, P2 = 0, K2 = 0;
-};
-
 // haplotype-length bucket of the binning key (16-column buckets below 1024,
 // 128-column buckets above; the kernels' pair_key uses the same)
 int hap_bucket(int64_t n) { return n < 1024 ? (int)(n >> 4) : 64 + (int)std::min<int64_t>((n - 1024) >> 7, 63); }
@@ -106,21 +97,6 @@ int64_t rescue_pairs(const int64_t *class_pairs, int group)
 {
     return group == 0 ? class_pairs[0] + class_pairs[1] : class_pairs[std::min(group + 1, 3)];
 }
-
-// The library's own bin table, shortest reads first: 16 lanes x K rows
-// (K = 1..16) up to 255 bases, then 64 lanes x K rows (K = 5..16).  Written
-// into a fixed array (the allocation-free forward uses it too); returns the
-// number of entries.
-int builtin_table(TuneEntry *t)
-{
-    int n = 0;
-    for (int K = 1; K <= 16; ++K) t[n++] = {16 * K - 1, 16, K};
-    for (int K = 5; K <= 16; ++K) t[n++] = {64 * K - 1, 64, K};
-    return n;
-}
-
-// its entry for reads of m bases (1 to 1,023)
-int builtin_entry(int m) { return m < 256 ? m >> 4 : 12 + (m >> 6); }
 
 std::vector<TuneEntry> default_table(int force_p)
 {
@@ -660,56 +636,6 @@ int choose_chain_cols(const ph_plan *p, int32_t nb, const int32_t *rb, const int
     return cols;
 }
 
-// Which way a call goes: one launch of one-pair tiles (k_one), or the binned
-// launches.  Both are priced by their tiles, in ns: a step of K rows takes a SIMD
-// 19 + 13 K clocks where the GPU is full (step_ns, of the whole GPU; measured with
-// 150,000 pairs of 10 to 250 bases), a tile alone 2 ns per vector instruction, about
-// 5.5 K + 10 of them per step (tile_ns).
-//
-// One-pair tiles take 64 lanes each and 130 steps beside their columns; half of the
-// longest tile adds to their sum.  Binned tiles pad fewer rows and lanes, but their
-// launches take 55 us and 9 more for every further bin (without a plan 45 us, 9 per
-// bin, 4.9 ns a pair, beyond 15,000 pairs 1.5, 6 a batch), single pairs 2.5 ns beside their
-// steps (0.6 in 4 lanes, 1.3 in 8), and every bin's kernel ends with its longest tile: a plan's bins on side
-// streams in turn, otherwise one after the other; the tiles' sum and those ends
-// overlap in part.  13 to 16 rows in 16 lanes run at 2 waves per SIMD.  Measured on
-// 1,001 shapes of 1 to 60 reads and 1 to 20 haplotypes a region, us, binned / one-pair
-// (of a plan; the estimates choose the lesser but where 2 or 3 are given):
-//   10 x 300 bases: 4,500 pairs 62 / 47, 15,000 79 / 113
-//   60 x 300: 15,000 130 / 111, 45,000 227 / 302; 60 x 4,000: 4,500 388 / 362, 15,000
-//   653 / 995; 60 x 150, two haplotypes: 24,800 133 / 109 (binned)
-//   150 x 300: 15,000 204 / 181, 45,000 352 / 500; 150 x 1,000: 4,500 205 / 177,
-//   15,000 384 / 470
-//   100-150 x 1,010, four bins: 12,000 376 / 328; 60-250 x 350, 14 bins: 60,000 738 /
-//   804 (one-pair); 50-250 x 1,000: 15,000 782 / 453, 150,000 3,298 / 4,079
-//   without a plan: 10 x 1,000, 4,500 118 / 99, 15,000 200 / 272; 100 x 1,000, 4,500
-//   183 / 126, 15,000 306 / 351; 50-250 x 1,000, 45,000 2,090 / 1,311
-// 23 of the choices take 5 to 14% longer than the other way, one 22%.
-//
-// Pairs with reads of more than 255 bases hold 50 KB of tables each, three a
-// CU: 768 of them run at once, and what is beyond that waits for a second
-// round, of twice the binned sweeps' length (haplotypes of 350 bases, us,
-// binned / one-pair: 300 bases, 512 pairs 96 / 48, 1,024 101 / 87, 4,096
-// 143 / 235; 500 bases, all redone in FP64, 187 / 120, 215 / 223, 421 / 637;
-// 1,000 bases 523 / 429, 855 / 847, 2,336 / 2,520).
-constexpr double kOneNs = 12e3, kBinnedNs = 55e3, kNextBinNs = 9e3, kSingleNs = 0.16;
-constexpr double kFreeNs = 45e3, kFreePairNs = 4.9, kFreeFurtherNs = 1.5, kFreeBatchNs = 6;  // without a plan
-constexpr int64_t kFreeFurther = 15000;
-constexpr int64_t kOneSteps = 130, kBinnedSteps = 60;  // beside the columns of a tile
-constexpr int64_t kOneLongPairs = 768;
-constexpr double kStepNs = 0.0081, kRowNs = 0.00557;
-double step_ns(int K) { return kStepNs + kRowNs * K; }
-double tile_ns(int64_t cols, int P, int K) { return 2.0 * (double)(cols + P + 2) * (5.5 * K + 10); }
-// the sum of a bin's tiles, which take that many steps
-double bin_ns(double steps, int P, int K) { return steps * step_ns(K) * (P == 16 && K > 12 ? 1.2 : 1.0); }
-// ns is no more than the binned launches take, their tiles' sum and their ends overlapping
-bool within_binned(double ns, double launches, double sum, double ends)
-{
-    const double left = ns - launches;
-    if (left <= std::max(sum, ends)) return true;
-    return left <= sum + ends && left <= std::pow(std::pow(sum, 1.6) + std::pow(ends, 1.6), 1 / 1.6);
-}
-
 // The FP32 work lists of a binned plan (Section III-C), built once from the
 // shape: records of every bin, bin b's range and tiles in the book image.
 // A bin's records are its chain tiles, longest chain first, then single
@@ -852,14 +778,6 @@ bool build_lists(ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t
     return true;
 }
 
-// Time of the one-pair launch (infinite: too many pairs of long reads): the steps of
-// all tiles, and times their rows per lane; the longest haplotype and read.
-double one_pair_ns(double steps, double row_steps, int64_t n_max, int m_max, int64_t long_pairs)
-{
-    if (long_pairs > kOneLongPairs) return INFINITY;
-    return kOneNs + kStepNs * steps + kRowNs * row_steps + 0.5 * tile_ns(n_max, 64, (m_max + 64) >> 6);
-}
-
 // A plan takes the one-pair launch (its bins would run on side streams in turn).
 bool one_pair_plan(const ph_plan *p, const int32_t *rb, const int32_t *hb, const int64_t *ro, const int64_t *ho)
 {
@@ -878,7 +796,7 @@ bool one_pair_plan(const ph_plan *p, const int32_t *rb, const int32_t *hb, const
         row_steps += (double)K_sum * tile;
         long_pairs += long_reads * H;
     }
-    const double one = one_pair_ns(steps, row_steps, p->max_n, p->max_m, long_pairs);
+    const double one = one_pair_ns(p->P, steps, row_steps, p->max_n, p->max_m, long_pairs);
     double stream[kSideStreams] = {};
     const int nbins = (int)p->table.size();
     int next = 0;
@@ -1852,7 +1770,7 @@ ph_status ph_forward_batch_noalloc(const ph_shape *shape, const ph_problem *pb, 
         n_max = std::max(n_max, n_longest);
         long_pairs += long_reads * H;
     }
-    const double one = one_pair_ns((double)steps, (double)row_steps, n_max, m_max, long_pairs);
+    const double one = one_pair_ns(P, (double)steps, (double)row_steps, n_max, m_max, long_pairs);
     const bool one_reads[2] = {long_pairs < P, long_pairs > 0};  // some read of up to 255 bases, some longer one
     // the binned launches run one after the other here
     const double few = (double)std::min<int64_t>(P, kFreeFurther);

@@ -1,0 +1,49 @@
+"""The host runtime's rules (csrc/ph_rules.h) in a program of their own, without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2411_11547_amd", "csrc")
+
+
+def run(tmp_path, body):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <cstdio>\n#include <vector>\n#include "ph_rules.h"\nusing namespace ph;\nint main()\n{\n' + body + "}\n")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-I", CSRC, "-o", str(exe), str(src)], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
+
+
+def test_builtin_entry_is_the_tables(tmp_path):
+    out = run(tmp_path, """
+    TuneEntry t[64];
+    const int n = builtin_table(t);
+    for (int m = 1; m <= 1023; ++m) {
+        int e = 0;
+        while (e < n - 1 && t[e].max_m < m) ++e;
+        if (e != builtin_entry(m)) printf("%d\\n", m);
+    }
+    printf("%d\\n", t[n - 1].max_m);
+""")
+    assert out == ["1023"]
+
+
+def test_one_pair_launch_holds_its_pairs(tmp_path):
+    """Threads of a launch are counted in 32 bits: 2^26 - 1 pairs at most, whatever the
+    other way would take (one haplotype of 10^7 bases beside pairs of one base)."""
+    out = run(tmp_path, """
+    const int64_t far = 10000000;
+    const double ends = tile_ns(far, 16, 1);
+    for (int64_t pairs : {(int64_t)1 << 25, ((int64_t)1 << 26) - 1, (int64_t)1 << 26, (int64_t)1 << 30}) {
+        const double steps = (double)pairs * (1 + kOneSteps);
+        printf("%d\\n", (int)within_binned(one_pair_ns(pairs, steps, steps, 1, 1, 0), 55e3, steps * step_ns(1) / 4, ends));
+    }
+    printf("%d %d\\n", (int)std::isinf(one_pair_ns(2000, 1e6, 1e6, 300, 300, 768)),
+           (int)std::isinf(one_pair_ns(2000, 1e6, 1e6, 300, 300, 769)));
+""")
+    assert out == ["1", "1", "0", "0", "0 1"]
