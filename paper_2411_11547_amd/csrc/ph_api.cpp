@@ -360,27 +360,25 @@ ph_status check_problem(const ph_plan *p, const ph_problem *pb)
     return PH_OK;
 }
 
-// Adjoint configuration of a read length: 32 lanes x K <= 5 rows, then 64 x K;
-// wide: 64 lanes x K for every read.
-bool adj_config(int m, bool wide, int &P, int &K)
+// Whether the plan's adjoint takes 64 lanes for every pair (adj_wide).
+bool adjoint_wide(const ph_plan *p)
 {
-    if (!wide && m + 1 <= 32 * 5) {
-        P = 32;
-        K = (m + 1 + 31) / 32;
-    } else if (m + 1 <= 64 * 5) {
-        P = 64;
-        K = (m + 1 + 63) / 64;
-        if (!wide) K = std::max(3, K);
-    } else {
-        return false;
-    }
-    return adj_supported(P, K);
+    if (p->P > kAdjWidePairs) return false;
+    int only = -1;
+    std::vector<int64_t> n;  // haplotypes of all pairs
+    for (int32_t q = 0; q < p->nb; ++q)
+        for (int32_t r = p->h_rb[q]; r < p->h_rb[q + 1] && p->h_hb[q] < p->h_hb[q + 1]; ++r) {
+            int P = 0, K = 0;
+            if (!adj_config((int)(p->h_ro[r + 1] - p->h_ro[r]), false, P, K)) return false;
+            if (P == 64 || (only >= 0 && only != K)) return true;
+            only = K;
+            for (int32_t h = p->h_hb[q]; h < p->h_hb[q + 1]; ++h) n.push_back(p->h_ho[h + 1] - p->h_ho[h]);
+        }
+    if (n.empty()) return false;
+    std::sort(n.begin(), n.end(), [](int64_t a, int64_t b) { return a > b; });
+    return adj_wide(p->P, only, n[0], (int64_t)n.size() > kAdjAlone ? n[kAdjAlone] : 0);
 }
 
-// Calls of no more pairs than that take 64 lanes for each: every tile is under
-// way at once and shorter (1,923 pairs with reads of 60-300 bases: 0.65 ms
-// against 0.67; 23,734 pairs 2.16 against 1.83, 10,000 of 150 bases 1.00 against 0.74).
-constexpr int64_t kAdjWidePairs = 2048;
 // From this many tiles on the ends of the launches count less than what a
 // kernel for every configuration gains.
 constexpr int64_t kAdjApartTiles = 32768;
@@ -395,7 +393,7 @@ ph_status build_adjoint(ph_plan *p)
     };
     std::vector<Item> items;
     items.reserve((size_t)p->P);
-    const bool wide = p->P <= kAdjWidePairs;
+    const bool wide = adjoint_wide(p);
     std::vector<AdjRedRead> red;
     int64_t grow = 0;  // per-pair gradient rows handed out so far
     std::vector<char> has_pair(p->nr, 0);
@@ -404,7 +402,7 @@ ph_status build_adjoint(ph_plan *p)
         for (int32_t r = p->h_rb[q]; r < p->h_rb[q + 1]; ++r) {
             const int m = (int)(p->h_ro[r + 1] - p->h_ro[r]);
             int P = 0, K = 0;
-            if (!adj_config(m, wide, P, K)) {
+            if (!adj_config(m, wide, P, K) || !adj_supported(P, K)) {
                 p->adj_status = PH_ERR_UNSUPPORTED;
                 p->adj_error = "adjoint supports reads up to 319 bases";
                 return p->adj_status;

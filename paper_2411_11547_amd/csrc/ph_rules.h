@@ -97,4 +97,52 @@ inline double one_pair_ns(int64_t pairs, double steps, double row_steps, int64_t
     return kOneNs + kStepNs * steps + kRowNs * row_steps + 0.5 * tile_ns(n_max, 64, (m_max + 64) >> 6);
 }
 
+// Adjoint configuration of reads of m bases (up to 319): 32 lanes x K <= 5 rows, then
+// 64 x K; wide: 64 lanes x K, but for reads that 32 lanes hold with one row each, whose
+// steps would be no shorter and more (160 to 2,000 pairs of 20-31 bases: 4 to 33% longer).
+inline bool adj_config(int m, bool wide, int &P, int &K)
+{
+    if (m + 1 <= 32 * (wide ? 1 : 5)) {
+        P = 32;
+        K = (m + 1 + 31) / 32;
+    } else if (m + 1 <= 64 * 5) {
+        P = 64;
+        K = (m + 1 + 63) / 64;
+        if (!wide) K = std::max(3, K);
+    } else {
+        return false;
+    }
+    return true;
+}
+
+// Calls of no more pairs than that may take 64 lanes for each: every tile is under
+// way at once and shorter.
+constexpr int64_t kAdjWidePairs = 2048;
+// 1,024 tiles have a SIMD each; a wave that shares its SIMD with another of its length
+// takes 1.58 times as long.
+constexpr int64_t kAdjAlone = 1024;
+constexpr double kAdjShared = 0.58;
+// instructions of a tile's step
+inline int adj_step(int K) { return 40 * K + 25; }
+
+// Whether a plan takes 64 lanes for each pair.  K: the rows per lane of its only
+// configuration of 32 lanes, or 0 where its reads take several or 64 lanes; n1, n1025:
+// its longest haplotype and the 1,025th of its pairs' (0: no more than 1,024 pairs).
+// With several configurations the lengths of the tiles even out (us, 32 and 64 lanes /
+// 64 lanes: reads of 60-300 x 200-600 bases, 1,200 pairs 336 / 360, 1,800 457 / 407,
+// 2,300 461 / 425, 4,000 747 / 754; 50-150 x 400-600, 800 315 / 244, 2,040 330 / 301,
+// 3,000 371 / 399).  With one, a tile of 64 lanes is shorter but shares its SIMD
+// beyond 1,024 pairs (32 / 64 lanes: 60 x 300, 800 pairs 111 / 102, 1,500 117 / 133;
+// 100 x 1,000, 800 420 / 297, 1,500 429 / 401, 4,000 687 / 697; 150 x 2,000, 800 939 /
+// 674, 1,500 971 / 1,010; 150 x 200-600, 1,500 319 / 296, 2,300 367 / 390).
+inline bool adj_wide(int64_t pairs, int K, int64_t n1, int64_t n1025)
+{
+    if (pairs > kAdjWidePairs) return false;
+    if (K == 0) return true;
+    const double narrow = (double)(n1 + 33) * adj_step(K);
+    double wide = (double)(n1 + 65) * adj_step((K + 1) / 2);
+    if (pairs > kAdjAlone) wide += kAdjShared * (double)(n1025 + 65) * adj_step((K + 1) / 2);
+    return wide < narrow;
+}
+
 }  // namespace ph

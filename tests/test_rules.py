@@ -47,3 +47,24 @@ def test_one_pair_launch_holds_its_pairs(tmp_path):
            (int)std::isinf(one_pair_ns(2000, 1e6, 1e6, 300, 300, 769)));
 """)
     assert out == ["1", "1", "0", "0", "0 1"]
+
+
+def test_adjoint_lanes(tmp_path):
+    """32 or 64 lanes: reads with one row per lane stay in 32, no read takes fewer rows
+    than it has, and plans of one configuration take 64 where that measured shorter."""
+    out = run(tmp_path, """
+    for (int m = 1; m <= 320; ++m)
+        for (int wide = 0; wide < 2; ++wide) {
+            int P = 0, K = 0;
+            const bool ok = adj_config(m, wide, P, K);
+            if (ok != (m <= 319) || (ok && (P * K < m + 1 || K > 5 || (m < 32) != (wide ? P == 32 : P == 32 && K == 1))))
+                printf("%d %d: %d %d\\n", m, wide, P, K);
+        }
+    // K of 32 lanes, haplotypes, pairs, 64 lanes
+    const int t[][4] = {{1, 40, 160, 0}, {1, 300, 2000, 0}, {2, 300, 800, 1}, {2, 300, 1500, 0}, {4, 1000, 800, 1},
+                        {4, 1000, 1500, 1}, {5, 2000, 800, 1}, {5, 2000, 1500, 0}, {5, 600, 2049, 0}, {0, 600, 2048, 1}};
+    for (auto &r : t)
+        if (adj_wide(r[2], r[0], r[1], r[2] > 1024 ? r[1] : 0) != (r[3] == 1)) printf("%d %d %d\\n", r[0], r[1], r[2]);
+    printf("done\\n");
+""")
+    assert out == ["done"]
