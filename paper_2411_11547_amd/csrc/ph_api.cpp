@@ -87,9 +87,6 @@ hipError_t g_lut_adj_status = hipSuccess;
 constexpr int64_t kAdjWsFloats = (int64_t)1 << 30;    // 4 GiB, FP32 pass
 constexpr int64_t kAdjWs64Doubles = (int64_t)1 << 28;  // 2 GiB, FP64 pass
 
-// adjoint tiles of more steps are launched apart: up to here the LDS of 8
-// workgroups fits a CU
-constexpr int kAdjLongSteps = 1280;
 
 int rescue_class_of(int m) { return m < 128 ? 0 : m < 256 ? 1 : m < 512 ? 2 : 3; }
 // pairs of the classes that a rescue launch sweeps
@@ -266,6 +263,7 @@ struct ph_plan {
         int64_t tile_begin = 0;
         int32_t ntiles = 0, lds = 0, grid = 0;
         int64_t ws_stride = 0;  // floats per workgroup
+        double time = 0;        // as adj_launch_time
     };
     bool adj_built = false;
     ph_status adj_status = PH_OK;
@@ -379,6 +377,9 @@ bool adjoint_wide(const ph_plan *p)
     return adj_wide(p->P, only, n[0], (int64_t)n.size() > kAdjAlone ? n[kAdjAlone] : 0);
 }
 
+// LDS bytes of a lane group's haplotype codes, one byte per column
+int adj_hs_bytes(int S, int P) { return (S + P + 2 + 15) / 16 * 16; }
+
 // From this many tiles on the ends of the launches count less than what a
 // kernel for every configuration gains.
 constexpr int64_t kAdjApartTiles = 32768;
@@ -438,90 +439,130 @@ ph_status build_adjoint(ph_plan *p)
         if (a.r.n != b.r.n) return a.r.n > b.r.n;
         return a.r.out < b.r.out;
     });
-    std::vector<AdjRec> recs(items.size());
-    struct Timed {
-        int64_t time;
-        AdjTile tile;
+    // the tiles of every configuration, G records each, longest first
+    struct Config {
+        int P, K;
+        size_t begin, end;             // items
+        std::vector<int> S;            // steps of each tile
+        size_t group[kAdjGroups + 1];  // first tile of each group (adj_group), the longest tiles' group first
     };
-    // the configurations of tiles of up to kAdjLongSteps steps, and of longer
-    // ones, which need more LDS and longer slices
-    std::vector<Timed> tiles[2];
-    std::vector<AdjRun> runs[2];
-    std::vector<int> run_steps[2];  // most steps of each
-    size_t i = 0;
-    while (i < items.size()) {
-        const int P = items[i].P, K = items[i].K, G = 64 / P;
-        // steps of the tile that starts at record a, whose haplotype is its
-        // longest: every lane reaches column n + 2 (the absorbing row of the
-        // rescaled states sums column n into column n + 2), rounded up to whole
-        // checkpoint intervals
-        auto steps = [&](size_t a) {
+    std::vector<AdjRec> recs(items.size());
+    std::vector<Config> configs;
+    for (size_t i = 0; i < items.size();) {
+        Config c{items[i].P, items[i].K, i, i, {}, {}};
+        while (c.end < items.size() && items[c.end].P == c.P && items[c.end].K == c.K) ++c.end;
+        const size_t G = 64 / c.P;
+        for (size_t a = i; a < c.end; a += G) {
+            // every lane reaches column n + 2 (the absorbing row of the rescaled
+            // states sums column n into column n + 2), rounded up to whole
+            // checkpoint intervals; the tile's first record has its longest haplotype
             constexpr int CK = kAdjC * kAdjR;  // steps per checkpoint
-            return ((items[a].r.n + P + 1 + CK - 1) / CK) * CK;
-        };
-        const int S_max = steps(i);
-        const int group = S_max > kAdjLongSteps ? 1 : 0;
-        AdjRun run{P, K, 0, ((S_max + P + 2 + 15) / 16) * 16, (int64_t)i};  // one code byte per column
-        size_t a = i;
-        const size_t before = tiles[group].size();
-        while (a < items.size() && items[a].P == P && items[a].K == K && (steps(a) > kAdjLongSteps) == (group == 1)) {
-            size_t b = a;
-            const int S = steps(a);
-            for (; b < items.size() && b < a + G && items[b].P == P && items[b].K == K; ++b) {
+            c.S.push_back((items[a].r.n + c.P + 1 + CK - 1) / CK * CK);
+            for (size_t b = a; b < std::min(a + G, c.end); ++b) {
                 recs[b] = items[b].r;
-                recs[b].S = S;
+                recs[b].S = c.S.back();
             }
-            // about 40 instructions per row and step, 25 for the step itself
-            tiles[group].push_back(
-                Timed{(int64_t)S * (40 * K + 25), {(int32_t)runs[group].size(), (int32_t)((a - i) / G)}});
-            a = b;
         }
-        run.nrec = (int32_t)(a - i);
-        // (each configuration's tiles come longest first)
-        std::inplace_merge(tiles[group].begin(), tiles[group].begin() + before, tiles[group].end(),
-                           [](const Timed &x, const Timed &y) { return x.time > y.time; });
-        if ((int64_t)adj_e_bytes(P, K) + (int64_t)G * run.hs_bytes + adj_ck_lds_bytes(K) > 64 * 1024) {
+        for (int g = 0, t = 0; g <= kAdjGroups; ++g) {
+            while (t < (int)c.S.size() && (g == kAdjGroups || adj_group(c.S[t]) > kAdjGroups - 1 - g)) ++t;
+            c.group[g] = t;
+        }
+        if ((int64_t)adj_e_bytes(c.P, c.K) + (int64_t)G * adj_hs_bytes(c.S[0], c.P) + adj_ck_lds_bytes(c.K) > 64 * 1024) {
             p->adj_status = PH_ERR_UNSUPPORTED;
             p->adj_error = "haplotype too long for the adjoint sweep";
             return p->adj_status;
         }
-        runs[group].push_back(run);
-        run_steps[group].push_back(S_max);
-        i = a;
+        i = c.end;
+        configs.push_back(std::move(c));
     }
-    std::vector<AdjTile> order;
-    int64_t ws_total = 0;
-    // one launch over the runs first .. last of a group
-    auto add_launch = [&](int group, size_t first, size_t last, int64_t ntiles) {
+    // a launch over the tiles of the groups g0 .. g1 - 1 (as in Config::group) of
+    // configuration only, or (-1) of all
+    auto launch_of = [&](int g0, int g1, int only) {
         ph_plan::AdjLaunch L;
-        for (size_t k = first; k <= last; ++k) {
-            const AdjRun &r = runs[group][k];
+        double longest = 0, total = 0;
+        for (size_t k = 0; k < configs.size(); ++k) {
+            const Config &c = configs[k];
+            const size_t t0 = c.group[g0], t1 = c.group[g1], G = 64 / c.P;
+            if (t0 == t1 || (only >= 0 && (int)k != only)) continue;
+            const size_t first = c.begin + t0 * G;
+            const AdjRun r{c.P, c.K, (int32_t)(std::min(c.begin + t1 * G, c.end) - first), adj_hs_bytes(c.S[t0], c.P),
+                           (int64_t)first};
             L.runs.push_back(r);
-            L.lds = std::max(L.lds, adj_e_bytes(r.P, r.K) + 64 / r.P * r.hs_bytes + adj_ck_lds_bytes(r.K));
+            L.lds = std::max(L.lds, adj_e_bytes(r.P, r.K) + (int)G * r.hs_bytes + adj_ck_lds_bytes(r.K));
             L.ws_stride = std::max<int64_t>(
-                L.ws_stride, ((int64_t)(run_steps[group][k] / (kAdjC * kAdjR)) * (3 * r.K + 3) * 64 + 63) / 64 * 64);
+                L.ws_stride, ((int64_t)(c.S[t0] / (kAdjC * kAdjR)) * (3 * r.K + 3) * 64 + 63) / 64 * 64);
+            L.ntiles += (int32_t)(t1 - t0);
+            longest = std::max(longest, (double)c.S[t0] * adj_step(c.K));
+            for (size_t t = t0; t < t1; ++t) total += (double)c.S[t] * adj_step(c.K);
         }
-        L.tile_begin = (int64_t)order.size();
-        L.ntiles = (int32_t)ntiles;
+        if (L.runs.empty()) return L;
         const bool one = L.runs.size() == 1;
         L.grid = (int32_t)std::max<int64_t>(
-            1, std::min<int64_t>(
-                   {ntiles, (int64_t)p->cus * adj32_blocks_per_cu(one ? L.runs[0].P : 0, L.runs[0].K, L.lds),
-                    kAdjWsFloats / L.ws_stride}));
-        ws_total = std::max(ws_total, (int64_t)L.grid * L.ws_stride);
-        p->adj_launches.push_back(L);
+            1, std::min<int64_t>({L.ntiles, (int64_t)p->cus * adj32_blocks_per_cu(one ? L.runs[0].P : 0, L.runs[0].K, L.lds),
+                                  kAdjWsFloats / L.ws_stride}));
+        L.time = adj_launch_time(longest, total, L.grid);
+        return L;
     };
-    for (int g = 1; g >= 0; --g) {
-        if (tiles[g].empty()) continue;
-        if (runs[g].size() == 1 || (int64_t)tiles[g].size() >= kAdjApartTiles) {
-            for (size_t k = 0; k < runs[g].size(); ++k) {
-                const int G = 64 / runs[g][k].P;
-                add_launch(g, k, k, ((int64_t)runs[g][k].nrec + G - 1) / G);
+    // the launches over the groups g0 .. g1 - 1, and which launches the groups make:
+    // the cut with the least time
+    auto launches_of = [&](int g0, int g1) {
+        std::vector<ph_plan::AdjLaunch> l = {launch_of(g0, g1, -1)};
+        if (l[0].ntiles >= kAdjApartTiles && l[0].runs.size() > 1) {
+            l.clear();
+            for (size_t k = 0; k < configs.size(); ++k) {
+                l.push_back(launch_of(g0, g1, (int)k));
+                if (l.back().runs.empty()) l.pop_back();
             }
-        } else {
-            add_launch(g, 0, runs[g].size() - 1, (int64_t)tiles[g].size());
-            for (const Timed &x : tiles[g]) order.push_back(x.tile);
         }
+        if (l[0].runs.empty()) l.clear();
+        return l;
+    };
+    std::vector<ph_plan::AdjLaunch> best[kAdjGroups + 1];  // of the groups before g
+    std::vector<int> begin[kAdjGroups + 1], end[kAdjGroups + 1];  // their groups
+    double best_time[kAdjGroups + 1] = {};
+    for (int g1 = 1; g1 <= kAdjGroups; ++g1) {
+        best_time[g1] = INFINITY;
+        for (int g0 = 0; g0 < g1; ++g0) {
+            const auto l = launches_of(g0, g1);
+            double time = best_time[g0];
+            for (const auto &x : l) time += x.time;
+            if (time >= best_time[g1]) continue;
+            best_time[g1] = time;
+            best[g1] = best[g0];
+            begin[g1] = begin[g0];
+            end[g1] = end[g0];
+            for (const auto &x : l) {
+                best[g1].push_back(x);
+                begin[g1].push_back(g0);
+                end[g1].push_back(g1);
+            }
+        }
+    }
+    p->adj_launches = best[kAdjGroups];
+    // the order of the tiles of launches over several configurations: longest first
+    std::vector<AdjTile> order;
+    int64_t ws_total = 0;
+    for (size_t l = 0; l < p->adj_launches.size(); ++l) {
+        ph_plan::AdjLaunch &L = p->adj_launches[l];
+        L.tile_begin = (int64_t)order.size();
+        ws_total = std::max(ws_total, (int64_t)L.grid * L.ws_stride);
+        if (L.runs.size() == 1) continue;
+        struct Timed {
+            int64_t time;
+            AdjTile tile;
+        };
+        std::vector<Timed> tiles;
+        int32_t run = 0;
+        for (const Config &c : configs) {
+            const size_t t0 = c.group[begin[kAdjGroups][l]], t1 = c.group[end[kAdjGroups][l]], before = tiles.size();
+            if (t0 == t1) continue;
+            for (size_t t = t0; t < t1; ++t)
+                tiles.push_back(Timed{(int64_t)c.S[t] * adj_step(c.K), {run, (int32_t)(t - t0)}});
+            std::inplace_merge(tiles.begin(), tiles.begin() + before, tiles.end(),
+                               [](const Timed &x, const Timed &y) { return x.time > y.time; });
+            ++run;
+        }
+        for (const Timed &x : tiles) order.push_back(x.tile);
     }
     // FP64 pass: sized for the longest haplotype and the largest class of
     // the plan; the grid is bounded by the workspace budget

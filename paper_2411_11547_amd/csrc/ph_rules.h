@@ -145,4 +145,29 @@ inline bool adj_wide(int64_t pairs, int K, int64_t n1, int64_t n1025)
     return wide < narrow;
 }
 
+// Adjoint tiles by their steps: up to 1,280, where the LDS of 8 workgroups fits a CU,
+// and twice that again and again.  Groups share a launch or are launched apart,
+// whichever takes less time by adj_launch_time: a launch's LDS and checkpoint slices
+// are its longest tile's, which leaves fewer workgroups for the shorter ones, while
+// launches apart each end with their longest tile.  (Reads of 50-300 x 1,300-2,000 bases
+// and one pair of 100 x 20,000, ms, together / apart: 3,600 pairs 7.3 / 9.0, 27,000
+// 30.0 / 19.3; 150 x 1,000-3,000, 3,600 pairs 2.0 / 2.4; 50-300 x 2,000-10,000, 600
+// pairs 2.6 / 4.7, 27,000 51 / 45.)
+constexpr int kAdjGroups = 6;
+inline int adj_group(int steps)
+{
+    int g = 0;
+    while (g < kAdjGroups - 1 && steps > 1280 << g) ++g;
+    return g;
+}
+// Time of a launch (2 ns) with that many workgroups resident: 1,024 SIMDs run a wave
+// each at its own rate, two at 1 / 1.58 of it, and one and a half on average gain as much
+// as two; a launch costs 5 us beside that.
+inline double adj_launch_time(double longest, double total, int64_t grid)
+{
+    const double waves = (double)grid / kAdjAlone;
+    const double rate = waves <= 1 ? waves : std::min(1 + 0.54 * (waves - 1), 1.27);
+    return 2500 + std::max(longest * (waves > 1 ? 1 + kAdjShared : 1), total / (kAdjAlone * rate));
+}
+
 }  // namespace ph

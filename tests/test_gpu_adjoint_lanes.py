@@ -32,3 +32,27 @@ def test_small_plans(lens, haps, copies):
     compare(got[:ref_grad.shape[0]], ref_grad, "small plan")
     rows = got.reshape(copies, -1, 7)
     assert np.array_equal(rows, np.broadcast_to(rows[:1], rows.shape))
+
+
+@pytest.mark.parametrize("copies", [1, 260])
+def test_long_haplotypes_beside_short_ones(copies):
+    """Haplotypes around the steps that part the groups of tiles (1,280, 2,560, 5,120) and
+    a very long one, in one launch (few pairs) and, where its LDS and its slice would
+    leave few workgroups for many other pairs, in launches of their own."""
+    rng = np.random.default_rng(11)
+    ref = rng.choice(list("ACGT"), size=20000)
+    cut = lambda m, s: "".join(ref[s:s + m])
+    base = [([cut(100, 30)], [cut(20000, 0)]),
+            ([cut(m, 5) for m in (150, 140, 90, 31)], [cut(n, 0) for n in (1247, 1248, 2527, 2528)]),
+            ([cut(200, 9), cut(319, 9)], [cut(n, 0) for n in (1215, 1216, 5055, 5056)])]
+    fill = [([cut(m, 7) for m in (40, 60, 90, 100, 130, 150, 159, 160, 200, 230, 250, 300, 310, 70, 80, 110, 120, 155, 170, 190)],
+             [cut(n, 0) for n in (420, 440, 460, 480, 500)])]
+    prob, one = wl.from_strings(base + fill * copies, base_q=30), wl.from_strings(base + fill, base_q=30)
+    say(f"adjoint: {prob.num_pairs} pairs, haplotypes of 420 to 20,000 bases")
+    u = rng.normal(size=one.num_pairs)
+    of_fill = u[-100:]
+    want, _ = oracle_grad(one, u)
+    got, _ = gpu_grad(prob, np.concatenate([u, np.tile(of_fill, copies - 1)]))
+    compare(got[:want.shape[0]], want, "long haplotypes")
+    rows = got[-copies * sum(len(r) for r in fill[0][0]):].reshape(copies, -1, 7)
+    assert np.array_equal(rows, np.broadcast_to(rows[:1], rows.shape))

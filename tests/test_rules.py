@@ -68,3 +68,18 @@ def test_adjoint_lanes(tmp_path):
     printf("done\\n");
 """)
     assert out == ["done"]
+
+
+def test_adjoint_launch_groups(tmp_path):
+    """Tiles of 1,280 steps and twice that again and again; a launch apart for one long
+    tile pays with many other tiles, not with few (27,000 and 3,600 pairs of 50-300 x
+    1,300-2,000 bases beside one of 100 x 20,000, which leaves 447 workgroups)."""
+    out = run(tmp_path, """
+    for (int s : {8, 1280, 1288, 2560, 2568, 5120, 5128, 10240, 20480, 20488, 40960, 50000}) printf("%d ", adj_group(s));
+    printf("\\n");
+    const double far = 20033.0 * adj_step(4), near = 2033.0 * adj_step(5), mean = 0.8 * near;
+    for (int tiles : {2900, 21800})
+        printf("%d\\n", (int)(adj_launch_time(far, far + tiles * mean, 447) >
+                             adj_launch_time(far, far, 1) + adj_launch_time(near, tiles * mean, 1792)));
+""")
+    assert out == ["0 0 1 1 2 2 3 3 4 5 5 5 ", "0", "1"]
