@@ -377,8 +377,20 @@ bool adjoint_wide(const ph_plan *p)
     return adj_wide(p->P, only, n[0], (int64_t)n.size() > kAdjAlone ? n[kAdjAlone] : 0);
 }
 
-// LDS bytes of a lane group's haplotype codes, one byte per column
+// Steps of a tile of P lanes per pair: every lane reaches column n + 2 (the absorbing
+// row of the rescaled states sums column n into column n + 2), rounded up to whole
+// checkpoint intervals.
+int adj_steps(int n, int P)
+{
+    constexpr int CK = kAdjC * kAdjR;  // steps per checkpoint
+    return (n + P + 1 + CK - 1) / CK * CK;
+}
+// LDS bytes of a lane group's haplotype codes, one byte per column, and of a workgroup
 int adj_hs_bytes(int S, int P) { return (S + P + 2 + 15) / 16 * 16; }
+int64_t adj32_lds_bytes(int P, int K, int S)
+{
+    return (int64_t)adj_e_bytes(P, K) + 64 / P * (int64_t)adj_hs_bytes(S, P) + adj_ck_lds_bytes(K);
+}
 
 // From this many tiles on the ends of the launches count less than what a
 // kernel for every configuration gains.
@@ -400,6 +412,9 @@ ph_status build_adjoint(ph_plan *p)
     std::vector<char> has_pair(p->nr, 0);
     for (int32_t q = 0; q < p->nb; ++q) {
         const int32_t H = p->h_hb[q + 1] - p->h_hb[q];
+        int n_longest = 0;
+        for (int32_t h = p->h_hb[q]; h < p->h_hb[q + 1]; ++h)
+            n_longest = std::max(n_longest, (int)(p->h_ho[h + 1] - p->h_ho[h]));
         for (int32_t r = p->h_rb[q]; r < p->h_rb[q + 1]; ++r) {
             const int m = (int)(p->h_ro[r + 1] - p->h_ro[r]);
             int P = 0, K = 0;
@@ -409,6 +424,15 @@ ph_status build_adjoint(ph_plan *p)
                 return p->adj_status;
             }
             if (H > 0) has_pair[r] = 1;
+            // the longest haplotype that is accepted does not depend on the plan's
+            // other pairs: what the LDS holds with the lanes of a large plan
+            int Pn = 0, Kn = 0;
+            adj_config(m, false, Pn, Kn);
+            if (H > 0 && adj32_lds_bytes(Pn, Kn, adj_steps(n_longest, Pn)) > 64 * 1024) {
+                p->adj_status = PH_ERR_UNSUPPORTED;
+                p->adj_error = "haplotype too long for the adjoint sweep";
+                return p->adj_status;
+            }
             // a read with several pairs: pair h's rows at grow + h m
             if (H > 1) red.push_back(AdjRedRead{grow, p->h_ro[r], m, H});
             for (int32_t h = p->h_hb[q]; h < p->h_hb[q + 1]; ++h) {
@@ -453,11 +477,8 @@ ph_status build_adjoint(ph_plan *p)
         while (c.end < items.size() && items[c.end].P == c.P && items[c.end].K == c.K) ++c.end;
         const size_t G = 64 / c.P;
         for (size_t a = i; a < c.end; a += G) {
-            // every lane reaches column n + 2 (the absorbing row of the rescaled
-            // states sums column n into column n + 2), rounded up to whole
-            // checkpoint intervals; the tile's first record has its longest haplotype
-            constexpr int CK = kAdjC * kAdjR;  // steps per checkpoint
-            c.S.push_back((items[a].r.n + c.P + 1 + CK - 1) / CK * CK);
+            // (the tile's first record has its longest haplotype)
+            c.S.push_back(adj_steps(items[a].r.n, c.P));
             for (size_t b = a; b < std::min(a + G, c.end); ++b) {
                 recs[b] = items[b].r;
                 recs[b].S = c.S.back();
@@ -466,11 +487,6 @@ ph_status build_adjoint(ph_plan *p)
         for (int g = 0, t = 0; g <= kAdjGroups; ++g) {
             while (t < (int)c.S.size() && (g == kAdjGroups || adj_group(c.S[t]) > kAdjGroups - 1 - g)) ++t;
             c.group[g] = t;
-        }
-        if ((int64_t)adj_e_bytes(c.P, c.K) + (int64_t)G * adj_hs_bytes(c.S[0], c.P) + adj_ck_lds_bytes(c.K) > 64 * 1024) {
-            p->adj_status = PH_ERR_UNSUPPORTED;
-            p->adj_error = "haplotype too long for the adjoint sweep";
-            return p->adj_status;
         }
         i = c.end;
         configs.push_back(std::move(c));
@@ -488,7 +504,7 @@ ph_status build_adjoint(ph_plan *p)
             const AdjRun r{c.P, c.K, (int32_t)(std::min(c.begin + t1 * G, c.end) - first), adj_hs_bytes(c.S[t0], c.P),
                            (int64_t)first};
             L.runs.push_back(r);
-            L.lds = std::max(L.lds, adj_e_bytes(r.P, r.K) + (int)G * r.hs_bytes + adj_ck_lds_bytes(r.K));
+            L.lds = std::max(L.lds, (int)adj32_lds_bytes(c.P, c.K, c.S[t0]));
             L.ws_stride = std::max<int64_t>(
                 L.ws_stride, ((int64_t)(c.S[t0] / (kAdjC * kAdjR)) * (3 * r.K + 3) * 64 + 63) / 64 * 64);
             L.ntiles += (int32_t)(t1 - t0);

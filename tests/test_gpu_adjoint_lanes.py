@@ -56,3 +56,23 @@ def test_long_haplotypes_beside_short_ones(copies):
     compare(got[:want.shape[0]], want, "long haplotypes")
     rows = got[-copies * sum(len(r) for r in fill[0][0]):].reshape(copies, -1, 7)
     assert np.array_equal(rows, np.broadcast_to(rows[:1], rows.shape))
+
+
+@pytest.mark.parametrize("n,ok", [(25600, True), (25984, False), (40000, False)])
+@pytest.mark.parametrize("copies", [1, 3000])
+def test_longest_haplotype_of_the_adjoint(n, ok, copies):
+    """The longest haplotype that is accepted is the same for few pairs and for many."""
+    import torch
+    read, hap = "ACGT" * 25, "ACGTTGCA" * (n // 8)
+    prob = wl.from_strings([([read], [hap])] + [([read], [hap[:120]])] * copies, base_q=30)
+    dev, plan = binding.DeviceProblem(prob), binding.Plan(prob)
+    u = torch.ones(prob.num_pairs, dtype=torch.float64, device="cuda")
+    if ok:
+        got = plan.backward(dev, u)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(got).all())
+    else:
+        with pytest.raises(binding.PHError) as e:
+            plan.backward(dev, u)
+        assert e.value.status == -2 and "too long" in str(e.value)
+    plan.close()
