@@ -103,11 +103,12 @@ typedef struct {
      * +inf sends every pair to the FP64 sweep. */
     double rescue_threshold;
     int use_graph;         /* 1: capture the FP32 launches of ph_forward_batch and the
-                              launch sequence of ph_backward_batch when a set of
-                              buffers comes twice in a row, and replay them as long as
-                              it stays; calls with other buffers launch directly, as do
-                              small plans, whose forward is one or two kernels, and
-                              calls on a stream that is being captured */
+                              launch sequence of ph_backward_batch at the first call
+                              and when other buffers come twice in a row, and replay
+                              them as long as these stay; calls with other buffers
+                              launch directly, as do small plans, whose forward is one
+                              or two kernels, and calls on a stream that is being
+                              captured */
     int plain;             /* 1: one FP32 kernel sized for the longest read, pairs
                               in output order, no binning, no rescue (baseline) */
     int force_p;           /* 0 = tuned; else lanes per pair (4, 8, 16, 32 or 64) for every

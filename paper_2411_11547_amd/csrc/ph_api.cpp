@@ -15,8 +15,9 @@
 //   4. the FP64 sweep over the pairs whose FP32 sum fell below the rescue
 //      threshold, one persistent launch for reads of up to 255 bases, one for
 //      those of up to 511 and two for longer ones.
-// The FP32 launches are captured into a HIP graph when the problem and output
-// pointers come again and replayed while they stay.  Small calls are one launch (k_one).
+// The FP32 launches are captured into a HIP graph by the first call and when other
+// problem and output pointers come again, and replayed while these stay.  Small calls
+// are one launch (k_one).
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -1410,11 +1411,11 @@ ph_status enqueue_backward(ph_plan *p, const ph_problem *pb, const float *log10_
 }
 
 // Whether a call on stream s replays captured launches (graph) or enqueues them
-// itself.  A set of pointers is captured when it comes twice in a row: calls whose
-// buffers alternate, as autograd's do, would capture and instantiate a graph each
-// (0.3 ms and more) and wait for the one that it takes the place of.  That one is
-// let go only after its last launch has run, which no call waits for: until then
-// calls enqueue their launches themselves.
+// itself.  The first set of pointers is captured at once, another when it comes twice
+// in a row: calls whose buffers alternate, as autograd's do, would capture and
+// instantiate a graph each (0.3 ms and more) and wait for the one that it takes the
+// place of.  That one is let go only after its last launch has run, which no call
+// waits for: until then calls enqueue their launches themselves.
 template <typename F>
 ph_status use_captured(ph_plan *p, ph_plan::Captured &c, std::vector<const void *> key, hipStream_t s, bool &graph,
                        F enqueue)
@@ -1424,7 +1425,7 @@ ph_status use_captured(ph_plan *p, ph_plan::Captured &c, std::vector<const void 
     if (!p->opts.use_graph) return PH_OK;
     HIPCHK(hipStreamIsCapturing(s, &cs));
     if (cs != hipStreamCaptureStatusNone) return PH_OK;  // the caller's own graph takes the launches
-    const bool again = key == c.last;
+    const bool again = c.last.empty() || key == c.last;
     c.last = key;
     if (c.exec && key == c.key) {
         c.marked = false;
