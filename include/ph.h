@@ -143,7 +143,7 @@ void ph_plan_opts_default(ph_plan_opts *opts);
  * read and haplotype non-empty (PH_ERR_INVALID), every read at most 65535
  * bases (PH_ERR_UNSUPPORTED; plain mode: 1023); then sizes and allocates
  * device scratch on the current device.  Reads of up to 1023 bases are
- * binned by length; longer reads are swept in windows of 1024 rows whose
+ * binned by length; longer reads are swept in windows of 256 or 1024 rows whose
  * boundary rows (3 values per haplotype column) live in plan scratch.
  * The plan owns its scratch, streams and graphs until ph_plan_destroy.
  * *out receives the plan. */

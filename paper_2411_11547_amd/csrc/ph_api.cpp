@@ -867,10 +867,13 @@ bool one_pair_plan(const ph_plan *p, const int32_t *rb, const int32_t *hb, const
 // The one-pair launches of a call with reads of up to 255 bases and longer ones.
 // Two launches, one after the other, each take at least one pair's sweep; in one,
 // every pair holds the longer reads' tables (25 KB up to 511 bases, 6 a CU; 50 KB
-// beyond, 3 a CU).  One launch wins up to three rounds of 1,536 pairs (reads of
-// 60-300 bases, us, two / one: 200 pairs 93 / 51, 1,900 119 / 80, 4,000 152 /
-// 119), with reads over 511 bases up to the one round of 768 that kOneLongPairs
-// allows (60-600 bases, 100 pairs 345 / 300, 700 pairs 350 / 300).
+// beyond, 3 a CU).  One launch wins up to about three rounds of 1,536 pairs and
+// loses from five (us, two / one; reads of 60-300 bases x 400: 1,500 pairs 80 /
+// 48, 4,000 168 / 112, 6,000 218 / 141, 8,000 185 / 186, 12,000 261 / 266;
+// 60-260 x 360: 4,000 107 / 92, 6,000 130 / 125, 8,000 152 / 166, 12,000 198 /
+// 235; 60-260 x 1,000: 4,000 226 / 198, 8,000 328 / 369), with reads over 511
+// bases up to the one round of 768 that kOneLongPairs allows (60-600 bases, 100
+// pairs 345 / 300, 700 pairs 350 / 300).
 constexpr int kOneUpTo511Pairs = 4096;
 hipError_t launch_one_pairs(const SweepArgs &sa, const OneArgs &oa, const bool *reads, int max_m, int pairs,
                             hipStream_t s)
@@ -1062,8 +1065,16 @@ ph_status plan_create(const ph_shape *shape, const ph_plan_opts *opts_in, int &c
         }
     }
     p->cells = cells;
-    // 3 waves per SIMD of 4-row windows fill the GPU; more items than that take
-    // 16 rows per lane
+    // 3 waves per SIMD of 4-row windows (the few) fill the GPU; more items than
+    // that take 16 rows per lane (the many).  us, few / many, by windows of the
+    // few: reads of 1,100-2,000 x 1,500-3,000 at 654 811 / 1,160, 2,598 1,018 /
+    // 1,319, 3,616 1,157 / 1,419, 5,218 1,446 / 1,528, 7,760 1,837 / 1,951;
+    // 1,030-1,100 x 1,200-1,500 at 2,800 676 / 817, 4,000 807 / 940, 6,000 982 /
+    // 1,016; 4,000-8,000 x 5,000-9,000 at 2,276 3,769 / 4,609, 6,788 7,755 /
+    // 8,283.  With every pair swept again in FP64: 1,044 / 1,078 (2,800), 1,413 /
+    // 1,320 (4,000), 1,957 / 1,640 (6,000), 2,143 / 2,152 (5,218), 2,951 / 2,890
+    // (7,760).  So the line is on the safe side for FP64 and early, by 4-23% of a
+    // call, where nearly all results stay in FP32.
     p->long_few = few_items <= 3072;
     p->windows = max_m / (64 * (p->long_few ? kLongK32Few : kLongK32Many)) + 1;
     p->windows64 = max_m / (64 * kLongK64) + 1;

@@ -876,8 +876,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
     // first row only through beta (with the diagonal) and eps (from above),
     // and both are set to 0 here, which is exact because row 0 has I = 0.  In
     // later windows of a long read the row above is a real stored row and
-    // keeps its terms.  (Rescaled states: the received M and It are cleared
-    // in the first lane of each group, see cell_step_hat.)
+    // keeps its terms.  (Rescaled states: cell_step_hx masks the received M
+    // with `keep` in the first lane of each group.)
     T epI0 = ep[0];
     if constexpr (!HAT) {
         if (t == 0 && r0 == 0) {
@@ -916,8 +916,8 @@ __device__ int sweep_tile(const SweepArgs &A, const int32_t *rec_idx_list, int r
 #pragma unroll
     for (int r = 0; r < K; ++r) M[r] = I[r] = D[r] = 0;
     // row above the lane's first row at column j-1 = 0: the first lane's
-    // row-0 boundary (the edge value) sits in It (rescaled) or Dt (plain)
-    T Md = 0, Id = HAT ? edge : (T)0, Dd = HAT ? (T)0 : edge;
+    // row-0 boundary (the edge value) sits in Xd, below (rescaled), or Dd (plain)
+    T Md = 0, Id = 0, Dd = edge;  // plain states only
     // rescaled states (cell_step_hx): the first row's X at column 0, and the
     // next lane's first-row coefficients
     T Xd = edge, cib = 0, cdb = 0, keb = 0;
