@@ -25,14 +25,13 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Forward GCUPS on 1 MI355X (binned FP32+FP64 rescue vs plain); adjoint GCUPS"
 FLOPS_PER_CELL = 11            # Eq. (1)-(3): 7 multiplications + 4 additions
-# FP32 issue slots per cell of the rescaled-state sweep: 4 FMA + 1 MUL, in slots of 16 lanes per clock per
-# SIMD, the rate of an FP32 FMA whose three vector sources have register numbers of one parity (others, and
-# multiplies, issue 32; the power limit holds FMAs on real data near 22), a multiply as half of one
-FMA_SLOTS_PER_CELL = 4.5
+FP32_INSTR_PER_CELL = 5        # rescaled-state sweep: 4 FMA + 1 MUL
 VITERBI_VALU_PER_CELL = 8      # the max-product cell: 5 MUL + 3 MAX
 PEAK_FP32_TFLOPS = 157.3       # MI355X FP32 vector peak
 PEAK_FP64_TFLOPS = 78.6        # MI355X FP64 vector peak
-PEAK_FMA_LANE_OPS = 256 * 4 * 16 * 2.4e9  # unpacked FP32 FMA: CUs x SIMDs x lanes/clk x clock
+# unpacked FP32 FMA and MUL: CUs x SIMDs x lanes/clk x clock.  Independent chains reach 52-62e12 of it, an FMA
+# whose three sources have register numbers of one parity 29-32e12 (profiles/alu_issue_rates.txt)
+PEAK_FP32_LANE_OPS = 256 * 4 * 32 * 2.4e9
 
 
 # HBM traffic of the FP32 sweep stage, from the committed rocprofv3 counter
@@ -129,23 +128,27 @@ ADJ_FLOPS_PER_CELL = 37  # 11 recompute + 11 adjoint + 15 gradient accumulation 
 def time_pipeline(prob, subsets=3, steps=2):
     """Host-input streaming forward (the paper's workflow, Section III-A):
     pinned host arrays in, scores on the host out, H2D of the next subset
-    overlapped with the current subset's compute.  Not the headline value:
-    it includes the PCIe transfers."""
+    overlapped with the current subset's compute.  Timed with the batch cut
+    into `subsets` equal subsets (the first of them in halves) and, as
+    `default_cut`, with the subset size that Pipeline takes by itself.  Not
+    the headline value: it includes the PCIe transfers."""
     from paper_2411_11547_amd import binding
-    pipe = binding.Pipeline(prob, max_subset_cells=prob.total_cells // subsets + 1)
-    pipe.forward()
-    t0 = time.perf_counter()
-    for _ in range(steps):
+
+    def timed(**cut):
+        pipe = binding.Pipeline(prob, **cut)
         pipe.forward()
-    sec = (time.perf_counter() - t0) / steps
-    ev_ms = pipe.ms()
-    nsub = pipe.num_subsets
-    pipe.close()
+        t0 = time.perf_counter()
+        for _ in range(steps):
+            pipe.forward()
+        sec = (time.perf_counter() - t0) / steps
+        r = {"gcups": round(prob.total_cells / sec / 1e9, 2), "ms_per_call": round(sec * 1e3, 3),
+             "event_ms": round(pipe.ms(), 3), "subsets": pipe.num_subsets}
+        pipe.close()
+        log(f"host-input pipeline: {r['ms_per_call']} ms/call over {r['subsets']} subsets, {r['gcups']} GCUPS")
+        return r
+
     h2d = int(prob.read_offset[-1]) * 5 + int(prob.hap_offset[-1])
-    log(f"host-input pipeline: {sec * 1e3:.2f} ms/call over {nsub} subsets, "
-        f"{prob.total_cells / sec / 1e9:.1f} GCUPS")
-    return {"gcups": round(prob.total_cells / sec / 1e9, 2), "ms_per_call": round(sec * 1e3, 3),
-            "event_ms": round(ev_ms, 3), "subsets": nsub, "pinned": True,
+    return {**timed(max_subset_cells=prob.total_cells // subsets + 1), "default_cut": timed(), "pinned": True,
             "h2d_bytes": h2d, "d2h_bytes": prob.num_pairs * 9,
             "includes": "H2D of bases and qualities, binning, FP32 sweeps, FP64 rescue, D2H of scores"}
 
@@ -409,8 +412,8 @@ def main():
             "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": measured_traffic(prob.name),
             "kernel": "FP32 sweep stage (k_fwd32 over all length bins)",
             "kernel_ms": round(float(st_mean[1]), 4),
-            "fma_slots_per_cell": FMA_SLOTS_PER_CELL,
-            "fma_slot_frac": round(FMA_SLOTS_PER_CELL * cells / t32 / PEAK_FMA_LANE_OPS, 4)}
+            "fp32_instr_per_cell": FP32_INSTR_PER_CELL,
+            "fp32_issue_frac": round(FP32_INSTR_PER_CELL * cells / t32 / PEAK_FP32_LANE_OPS, 4)}
 
     uniform = None if args.no_uniform else uniform_report()
     precision = None if args.no_precision else precision_report()
