@@ -248,6 +248,7 @@ struct ph_plan {
         bool marked = false;
     };
     Captured fwd[2];  // the FP32 stage of the forward ([0]) and of the Viterbi score ([1])
+    bool events_captured = false;  // a caller's capture took the events of a call
 
     hipStream_t last_stream = nullptr;
     bool forward_done = false;
@@ -304,11 +305,21 @@ void drop_captured(ph_plan::Captured &c)
     c.marked = false;
 }
 
-// (a graph that may still run is waited for before it goes)
+// (a graph that may still run is waited for before it goes; events that were last
+// recorded into a caller's capture say nothing about it)
 void drop_graphs(ph_plan *p)
 {
-    if (p->stages_recorded && (p->fwd[0].exec || p->fwd[1].exec)) (void)hipEventSynchronize(p->ev[3]);
-    if (p->adj_recorded && p->adj.exec) (void)hipEventSynchronize(p->ev_adj[1]);
+    const bool fwd = p->fwd[0].exec || p->fwd[1].exec;
+    if (p->events_captured && (fwd || p->adj.exec)) {
+        int dev = p->device;
+        (void)hipGetDevice(&dev);
+        (void)hipSetDevice(p->device);
+        (void)hipDeviceSynchronize();
+        (void)hipSetDevice(dev);
+    } else {
+        if (p->stages_recorded && fwd) (void)hipEventSynchronize(p->ev[3]);
+        if (p->adj_recorded && p->adj.exec) (void)hipEventSynchronize(p->ev_adj[1]);
+    }
     for (auto *c : {&p->fwd[0], &p->fwd[1], &p->adj}) drop_captured(*c);
 }
 
@@ -1435,7 +1446,10 @@ ph_status use_captured(ph_plan *p, ph_plan::Captured &c, std::vector<const void 
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (!p->opts.use_graph) return PH_OK;
     HIPCHK(hipStreamIsCapturing(s, &cs));
-    if (cs != hipStreamCaptureStatusNone) return PH_OK;  // the caller's own graph takes the launches
+    if (cs != hipStreamCaptureStatusNone) {  // the caller's own graph takes the launches
+        p->events_captured = true;
+        return PH_OK;
+    }
     const bool again = c.last.empty() || key == c.last;
     c.last = key;
     if (c.exec && key == c.key) {

@@ -173,3 +173,30 @@ def test_default_plan_inside_a_captured_graph():
         torch.cuda.synchronize()
         assert torch.equal(got, other), k
     plan.close()
+
+
+def test_plan_destroyed_after_a_captured_call():
+    """A call inside a caller's capture takes the plan's events with it: a plan that is
+    destroyed then still waits for the graph that its call before the capture replays."""
+    import torch
+    prob = wl.config1(regions=200)
+    ref, rst = gpu_forward(prob, use_graph=False)
+    dev = binding.DeviceProblem(prob)
+    plan = binding.Plan(prob)
+    out = torch.zeros(prob.num_pairs, dtype=torch.float64, device="cuda")
+    st = torch.zeros(prob.num_pairs, dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        plan.forward(dev, out=out, status=st)
+        assert binned(plan)
+        out.zero_()
+        busy()
+        plan.forward(dev, out=out, status=st)
+        g.capture_begin(capture_error_mode="relaxed")
+        plan.forward(dev, out=out, status=st)
+        g.capture_end()
+        plan.close()
+        assert side.query()
+    assert np.array_equal(st.cpu().numpy(), rst) and np.array_equal(out.cpu().numpy(), ref)
